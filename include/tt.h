@@ -77,9 +77,10 @@ typedef struct tt_opts {
     int32_t max_iter;  /* >= 1 */
     double kappa;      /* Lax-Friedrichs viscosity factor, >= max sqrt(1 + 2|xi|) */
     int32_t tile_k;    /* k-extent of one sweep tile, 1..62; 0 = library default
-                          (tt_default_tile_k) */
+                          (tt_default_tile_k; deeper tiles for large batches).
+                          Results do not depend on it. */
     int32_t flags;     /* bit 0 (TT_FLAG_TIME_SWEEPS): time the sweep kernels with a HIP
-                          event pair around the tile-plane launches of every
+                          event pair around the launches of every
                           directional sweep on the call's stream (tt_sweep_timing) */
     double* eps_hist;  /* optional device buffer [nsrc][max_iter] that receives the
                           convergence measure of every iteration of every source
@@ -87,10 +88,10 @@ typedef struct tt_opts {
                           they were), or NULL */
     int32_t groups;    /* the sources are split into this many contiguous groups,
                           each iterated on its own stream so that the groups'
-                          tile-plane launches run concurrently (fewer idle units
-                          at the narrow ends of every sweep and in the
-                          convergence tail); 0 = automatic (nsrc / 32, at most
-                          4); 1 when TT_FLAG_TIME_SWEEPS is set.  Results do not
+                          sweeps run concurrently (fewer idle units at the
+                          narrow ends of every sweep and in the convergence
+                          tail); 0 = automatic (1 to 4, by grid and batch
+                          size); 1 when TT_FLAG_TIME_SWEEPS is set.  Results do not
                           depend on it. */
     const int32_t* budgets;  /* optional HOST array [nsrc] of per-source iteration
                           budgets, each in [1, max_iter] (e.g. the previous
@@ -333,13 +334,13 @@ int tt_mg_expand(const tt_grid* grid, int32_t H, const int32_t* m, const double*
 /* Sweep-kernel timing gathered by tt_forward (which = 0) and tt_adjoint
  * (which = 1) calls of the calling thread that had TT_FLAG_TIME_SWEEPS set:
  * the summed device time of the timed sweeps (ms, HIP event pairs around the
- * back-to-back tile-plane launches of each directional sweep) and the number
+ * launches of each directional sweep) and the number
  * of sweep-kernel launches they contain.  reset != 0 clears the totals after
  * reading.  Pointers may be NULL. */
 int tt_sweep_timing(int32_t which, double* total_ms, int64_t* launches, int32_t reset);
 
-/* The tile depth (tt_opts.tile_k) that tile_k = 0 selects: which = 0
- * tt_forward, 1 tt_adjoint; 0 for any other value. */
+/* The tile depth (tt_opts.tile_k) that tile_k = 0 selects (large batches take
+ * a deeper one): which = 0 tt_forward, 1 tt_adjoint; 0 for any other value. */
 int32_t tt_default_tile_k(int32_t which);
 
 /* Message for the last nonzero return of the calling thread ("" if none). */

@@ -2,6 +2,7 @@
 // checks, workspace layout, and the iteration loop that polls convergence.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -46,12 +47,23 @@ __device__ __align__(256) unsigned char scratch[kScratchBytes];
         if (e_ != hipSuccess) return fail(TT_EHIP, "%s: %s", #call, hipGetErrorString(e_));   \
     } while (0)
 
-// default tile k-extents (the forward update is long, so shorter tiles with
-// more parallel tiles per plane win; the adjoint step is short, so longer
-// tiles amortise the staging better); measured on the 101^3 spherical batch
+// Default tile depths.  A batch of few tile columns is bound by the chain of
+// tiles from the sweep's first corner to its last, which shorter tiles cut
+// finer; one that fills the chip several times over is bound by what its tiles
+// move, which deeper tiles move less of.  Measured at depths 16 and 28
+// (forward), 16 and 40 (adjoint):
+//   41^3 x 1 source (25 columns)   forward 12.0 / 15.5 ms   adjoint 13.3 / 15.4 ms
+//   61^3 x 32 (2048)                       38.0 / 50.1              57.7 / 60.6
+//   61^3 x 40 (2560)                       49.2 / 53.9
+//   61^3 x 64 (4096)                       59.1 / 56.3             100.1 / 76.8
+//   101^3 x 24 (4056)                     160.5 / 149.8            275.9 / 195.1
+//   101^3 x 128 (21632)                   488.8 / 348.9            828.1 / 589.2
 constexpr int kDefaultTileK = 32;
 constexpr int kDefaultTileKFwd = 16;
-constexpr int kDefaultTileKAdj = 28;
+constexpr int kDefaultTileKAdj = 16;
+constexpr int kDeepTileKFwd = 28;
+constexpr int kDeepTileKAdj = 40;
+constexpr long long kDeepColumns = 3072;
 
 size_t align_up(size_t v) { return (v + 255) & ~(size_t)255; }
 
@@ -92,15 +104,25 @@ int check_opts(const tt_opts* o) {
     return TT_OK;
 }
 
-// number of concurrently iterated source groups of a solve
-int groups_of(const tt_opts* o, int nsrc) {
+// tile columns of a batch: its sweeps' parallelism
+long long batch_columns(const tt_grid* g, int nsrc) {
+    return (long long)((g->n[0] + 5) / 8) * ((g->n[1] + 5) / 8) * nsrc;
+}
+
+// Number of concurrently iterated source groups of a solve.  A sweep launch
+// leaves the chip partly idle at its first and last columns, where a second
+// group's launch can run; a batch of many columns hardly has such ends.
+// Forward with 1 and 2 groups, adjoint with 2 and 4: 61^3 x 32 43 / 38 ms and
+// 69 / 58 ms; 61^3 x 64 56.3 / 58.3 and 76.8 / 78.8; 61^3 x 128 70.6 / 73.4 and
+// 118.3 / 119.6; 101^3 x 128 352 / 349 and 589 / 598.
+int groups_of(const tt_opts* o, const tt_grid* grid, int nsrc, int which) {
     int g;
     if (o && (o->flags & TT_FLAG_TIME_SWEEPS))
         g = 1;
     else if (o && o->groups > 0)
         g = o->groups;
     else
-        g = nsrc / 32 < 1 ? 1 : (nsrc / 32 > 4 ? 4 : nsrc / 32);
+        g = std::max(1, std::min(nsrc / 8, (which == 0 ? 1 : 2) * (batch_columns(grid, nsrc) < kDeepColumns ? 2 : 1)));
     return g > nsrc ? nsrc : g;
 }
 
@@ -122,12 +144,7 @@ tt::Geo make_geo(const tt_grid* g, int tk) {
     G.tk = tk;
     G.nt[0] = (G.m[0] + tt::kBI - 1) / tt::kBI;
     G.nt[1] = (G.m[1] + tt::kBJ - 1) / tt::kBJ;
-    G.nt[2] = 0;
-    for (int sd = 0; sd <= G.nt[0] + G.nt[1] - 2; ++sd) {
-        const int c = tt::col_tile_hi(G, sd) - tt::col_tile_lo(G, sd) + 1;
-        G.nt[2] = c > G.nt[2] ? c : G.nt[2];
-    }
-    G.ntiles = G.nt[0] * G.nt[1] * G.nt[2];
+    G.ncols = G.nt[0] * G.nt[1];
     G.N = (long long)G.n[0] * G.n[1] * G.n[2];
     G.si = (long long)G.n[1] * G.n[2];
     G.sj = G.n[2];
@@ -144,7 +161,7 @@ tt::Geo make_geo(const tt_grid* g, int tk) {
 
 // Workspace layout (each region 256-byte aligned):
 //   Src[nsrc] | tab0[n0] | tab1[n1] | tab2[n2] | active[nsrc] | iter[nsrc] | counter |
-//   part[nsrc*nslots] | model[4*Sa*4] (forward) | part2[nsrc*nslots] (adjoint) |
+//   part[nsrc*nslots] (sums, sweep progress, queues) | model[4*Sa*4] (forward) | part2[nsrc*nslots] (adjoint) |
 //   coef[nsrc*4*Sa*6] (or [nsrc*N*6] compact) | diag[nsrc*N] | rhs[nsrc*N] | box[nsrc*6] | bnd_in, bnd_rhs[nsrc*NB] (adjoint)
 struct Layout {
     size_t off_src, off_t0, off_t1, off_t2, off_active, off_iter, off_counter, off_part, off_part2, off_coef,
@@ -191,61 +208,8 @@ Layout layout(const tt::Geo& G, int nsrc, int nslots, int which, bool compact = 
 void fill_plan(tt::Plan& P, const tt::Geo& G, int nsrc) {
     P.G = G;
     P.nsrc = nsrc;
-    // tile-plane p holds the tiles (TI, TJ, p - s) of the tile columns with
-    // s = TI + TJ and lo(s) <= p - s <= hi(s); s + lo(s) and s + hi(s) grow with
-    // s, so those s form one run
-    const int smax = G.nt[0] + G.nt[1] - 2;
-    const int pmax = smax + tt::col_tile_hi(G, smax);
-    P.plane_count.clear();
-    P.plane_id.clear();
-    P.plane_s0.clear();
-    for (int p = 0; p <= pmax; ++p) {
-        int cnt = 0, s0 = -1;
-        for (int sd = 0; sd <= smax; ++sd) {
-            if (sd + tt::col_tile_lo(G, sd) > p || sd + tt::col_tile_hi(G, sd) < p) continue;
-            if (s0 < 0) s0 = sd;
-            cnt += tt::diag_count(G, sd);
-        }
-        if (cnt == 0) continue;
-        P.plane_count.push_back(cnt);
-        P.plane_id.push_back(p);
-        P.plane_s0.push_back(s0);
-    }
-    P.nplanes = (int)P.plane_count.size();
-    P.max_plane_tiles = 0;
-    for (int c : P.plane_count) P.max_plane_tiles = c > P.max_plane_tiles ? c : P.max_plane_tiles;
     P.nbblocks = (int)((G.NB + tt::kBndThreads - 1) / tt::kBndThreads);
-    P.nslots = 8 * G.ntiles + 8 * P.nbblocks;
-}
-
-// Host check of the tile-plane enumeration before any sweep is launched:
-// every tile the kernels decode lies in the grid's tile columns and in its
-// column's slab range, its plane number is TI + TJ + TK, and the planes cover
-// each tile exactly once.
-int check_tiling(const tt::Plan& P) {
-    const tt::Geo& G = P.G;
-    std::vector<unsigned char> seen((size_t)G.ntiles, 0);
-    long long total = 0;
-    for (int q = 0; q < P.nplanes; ++q) {
-        for (int b = 0; b < P.plane_count[q]; ++b) {
-            int TI, TJ, TK;
-            tt::tile_decode(G, P.plane_id[q], P.plane_s0[q], b, TI, TJ, TK);
-            const int sd = TI + TJ;
-            const int rel = TK - tt::col_tile_lo(G, sd);
-            if (TI < 0 || TI >= G.nt[0] || TJ < 0 || TJ >= G.nt[1] || rel < 0 || TK > tt::col_tile_hi(G, sd) ||
-                rel >= G.nt[2] || TI + TJ + TK != P.plane_id[q])
-                return fail(TT_EINVAL, "internal: tile %d of tile-plane %d decodes outside the grid", b, P.plane_id[q]);
-            unsigned char& f = seen[((size_t)TI * G.nt[1] + TJ) * G.nt[2] + rel];
-            if (f) return fail(TT_EINVAL, "internal: tile-plane %d repeats a tile", P.plane_id[q]);
-            f = 1;
-            ++total;
-        }
-    }
-    long long want = 0;
-    for (int sd = 0; sd <= G.nt[0] + G.nt[1] - 2; ++sd)
-        want += (long long)tt::diag_count(G, sd) * (tt::col_tile_hi(G, sd) - tt::col_tile_lo(G, sd) + 1);
-    if (total != want) return fail(TT_EINVAL, "internal: tile-planes cover %lld of %lld tiles", total, want);
-    return TT_OK;
+    P.nslots = 2 * G.ncols + P.nbblocks + 1;
 }
 
 void bind_workspace(tt::Plan& P, void* ws, const Layout& L) {
@@ -271,10 +235,12 @@ void bind_workspace(tt::Plan& P, void* ws, const Layout& L) {
     P.T.t2 = P.tab2;
 }
 
-int tile_k_of(const tt_opts* o, int which) {
-    int tk = (o && o->tile_k > 0) ? o->tile_k
-                                  : (which == 0 ? kDefaultTileKFwd : (which == 1 ? kDefaultTileKAdj : kDefaultTileK));
-    return tk > tt::kMaxTileK ? tt::kMaxTileK : tk;
+// tile depth of a call on this grid and batch (nothing is sized by it)
+int tile_k_of(const tt_opts* o, int which, const tt_grid* g, int nsrc) {
+    if (o && o->tile_k > 0) return o->tile_k;
+    if (which > 1) return kDefaultTileK;
+    if (batch_columns(g, nsrc) >= kDeepColumns) return which == 0 ? kDeepTileKFwd : kDeepTileKAdj;
+    return which == 0 ? kDefaultTileKFwd : kDefaultTileKAdj;
 }
 
 // pinned host words that receive the active-source count of each iteration
@@ -643,7 +609,7 @@ int forward_run(const tt::Geo& G, const double* s, const double* xi, const doubl
     return rc;
 }
 
-// Argument and tiling checks shared by the forward entry points.
+// Argument checks shared by the forward entry points.
 int forward_checks(const tt_grid* grid, int32_t nsrc, const tt_opts* opts, std::initializer_list<const void*> ptrs,
                    tt::Geo* G) {
     int rc = check_grid(grid);
@@ -651,11 +617,8 @@ int forward_checks(const tt_grid* grid, int32_t nsrc, const tt_opts* opts, std::
     if (nsrc < 0) return fail(TT_EINVAL, "nsrc < 0");
     if (nsrc > 65535) return fail(TT_EINVAL, "nsrc > 65535");
     if (nsrc > 0 && (rc = check_ptrs(ptrs))) return rc;
-    *G = make_geo(grid, tile_k_of(opts, 0));
-    tt::Plan P;
-    fill_plan(P, *G, 1);
-    if (P.max_plane_tiles > 65535) return fail(TT_EINVAL, "too many tiles per tile-plane; raise opts.tile_k");
-    return check_tiling(P);
+    *G = make_geo(grid, tile_k_of(opts, 0, grid, nsrc));
+    return TT_OK;
 }
 
 // Device address of this device's scratch array (hipGetSymbolAddress once per
@@ -703,8 +666,8 @@ size_t tt_workspace_size(const tt_grid* grid, int32_t nsrc, const tt_opts* opts,
     if (check_grid(grid) || nsrc < 1 || which < 0 || which > 3) return 0;
     if (opts && (opts->groups < 0 || opts->groups > TT_MAX_GROUPS)) return 0;
     if (opts && (opts->tile_k < 0 || opts->tile_k > tt::kMaxTileK)) return 0;
-    tt::Geo G = make_geo(grid, tile_k_of(opts, which));
-    return grouped_total(G, nsrc, which <= 1 ? groups_of(opts, nsrc) : 1, which, which == 1 && compact_of(opts));
+    tt::Geo G = make_geo(grid, tile_k_of(opts, which, grid, nsrc));
+    return grouped_total(G, nsrc, which <= 1 ? groups_of(opts, grid, nsrc, which) : 1, which, which == 1 && compact_of(opts));
 }
 
 int tt_source_params(const tt_grid* grid, const double* s, const double* xi, const double* eta, int32_t nsrc,
@@ -729,7 +692,7 @@ int tt_forward(const tt_grid* grid, const double* s, const double* xi, const dou
     int rc = forward_checks(grid, nsrc, opts, {s, xi, eta, src_pos, src_par, tau, status, ws}, &G);
     if (rc || nsrc == 0) return rc;
     return forward_run(G, s, xi, eta, nsrc, src_pos, src_par, tau_init, opts, tau, status, ws, ws_bytes,
-                       groups_of(opts, nsrc), (hipStream_t)stream);
+                       groups_of(opts, grid, nsrc, 0), (hipStream_t)stream);
 }
 
 int tt_forward_noalloc(const tt_grid* grid, const double* s, const double* xi, const double* eta, int32_t nsrc,
@@ -875,14 +838,8 @@ int tt_adjoint(const tt_grid* grid, const double* s, const double* xi, const dou
     if (nsrc > 65535) return fail(TT_EINVAL, "nsrc > 65535");
     if ((rc = check_ptrs({s, xi, eta, src_pos, src_par, tau, lam, status, ws}))) return rc;
     if (nrec > 0 && (!rec_pos || !R)) return fail(TT_EINVAL, "rec_pos/R NULL with nrec > 0");
-    tt::Geo G = make_geo(grid, tile_k_of(opts, 1));
-    {
-        tt::Plan P;
-        fill_plan(P, G, 1);
-        if (P.max_plane_tiles > 65535) return fail(TT_EINVAL, "too many tiles per tile-plane; raise opts.tile_k");
-        if ((rc = check_tiling(P))) return rc;
-    }
-    const int groups = groups_of(opts, nsrc);
+    tt::Geo G = make_geo(grid, tile_k_of(opts, 1, grid, nsrc));
+    const int groups = groups_of(opts, grid, nsrc, 1);
     hipStream_t caller = (hipStream_t)stream;
     std::vector<Group> gs;
     if ((rc = make_groups(G, nsrc, groups, 1, ws, ws_bytes, opts, caller, gs))) return rc;

@@ -31,9 +31,9 @@ struct Geo {
     int n[3];          // nodes per axis
     int m[3];          // interior nodes per axis (n - 2)
     int coord;         // 0 Cartesian, 1 spherical
-    int nt[3];         // tile columns along i' and j'; nt[2] = most tiles of one tile column
+    int nt[2];         // tile columns along i' and j'
     int tk;            // hyperplane steps of a tile (its extent along u = i' + j' + k')
-    int ntiles;        // nt0 * nt1 * nt2 (partial-sum slots per directional sweep)
+    int ncols;         // tile columns: nt0 * nt1
     long long N;       // n0 * n1 * n2
     long long si, sj;  // strides of axes 0 and 1 (axis 2 has stride 1)
     long long NB;      // boundary nodes
@@ -50,9 +50,9 @@ struct Geo {
 // TI + TJ = s spans u in [8 s, 8 s + 14 + m2) (full columns; ragged ones end
 // earlier), i.e. slabs lo(s)..hi(s).  A tile reads its upstream neighbours'
 // nodes at u - 1 (slabs TK - 1 and TK of the neighbouring columns) and its
-// downstream ones' at u + 1 (slabs TK and TK + 1), so all tiles with the same
-// tile-plane number TI + TJ + TK are independent and each depends only on
-// lower tile-planes.
+// downstream ones' old values at u + 1 (slabs TK and TK + 1): it may start once
+// slab TK of the two upstream columns and its own slab TK - 1 are done, and a
+// downstream column cannot overwrite what it reads before it is done itself.
 __host__ __device__ inline int col_tile_lo(const Geo& G, int s) { return (kBI * s) / G.tk; }
 __host__ __device__ inline int col_tile_hi(const Geo& G, int s) {
     return (kBI * s + (kBI - 1) + (kBJ - 1) + G.m[2] - 1) / G.tk;
@@ -63,19 +63,17 @@ __host__ __device__ inline int diag_count(const Geo& G, int s) {
     const int hi = s < G.nt[0] - 1 ? s : G.nt[0] - 1;
     return hi - diag_first(G, s) + 1;
 }
-// tile b of tile-plane p whose first tile column sum is s0 (tiles ordered by s,
-// then TI); the host enumerates the planes so that b is always in range
-__host__ __device__ inline void tile_decode(const Geo& G, int p, int s0, int b, int& TI, int& TJ, int& TK) {
-    const int smax = G.nt[0] + G.nt[1] - 2;
-    int s = s0;
-    for (; s < smax; ++s) {
+// tile column number b in [0, ncols): columns ordered by TI + TJ, then TI, so
+// that both upstream neighbours of a column have lower numbers
+__host__ __device__ inline void col_decode(const Geo& G, int b, int& TI, int& TJ) {
+    int s = 0;
+    for (; s < G.nt[0] + G.nt[1] - 2; ++s) {
         const int c = diag_count(G, s);
         if (b < c) break;
         b -= c;
     }
     TI = diag_first(G, s) + b;
     TJ = s - TI;
-    TK = p - s;
 }
 // LDS doubles per staged column: the tk + 2 entries, rounded up to an even
 // count (the window is staged two doubles per lane and load)
@@ -87,6 +85,7 @@ struct Src {
     double E[9];       // rows: source-frame unit vectors r^_s, theta^_s, phi^_s
     double mi11, mi12, mi22;  // lower-right block of M0^{-1}
     double s0;
+    double rs;         // the source's radius (spherical)
     int fb[3];         // base corner of the fixed cell
     int pad;
 };
@@ -234,28 +233,45 @@ __device__ __forceinline__ void local_state(const Geo& G, const Src& S, const Co
 // the column's constants, so an update has no division.
 //
 // The factor enters through T0 = s0 Q rq and its scaled gradient t = s0 rq u
-// (rq = 1 / sqrt(Q), u = the gradient direction of the factor() notes without
-// the s0 rq), so P_a = T0 q_a + tau t_a = s0 rq R_a with R_a = Q q_a + tau u_a and
-// H = s0 rq sqrt(R . M R): the update forms R, not T0 and t.  Along a spherical
-// column X = (rct c2, rct s2, rst), so d = E (X - Xs) is d_i = A_i c2 + B_i s2 + C_i
-// with column constants A, B, C.
+// (rq = 1 / sqrt(Q), u = m on the node's unit vectors, m = M0^{-1} d), so
+// P_a = T0 q_a + tau t_a = s0 rq R_a with R_a = Q q_a + tau u_a and
+// H = s0 rq sqrt(R . M R): the update forms R, not T0 and t, and R in units of
+// the axis-0 difference weight v0 = 1 / (2 h_0), which then drops out of R_0.
+//
+// Along a spherical column X = (rct c2, rct s2, rst), so d = E (X - Xs) is
+// d_i = A_i c2 + B_i s2 + C_i with column constants A, B, C.  u needs no
+// projection through the embedding.  With ths, rs the source's latitude and
+// radius, X = (rs + d_0, d_1, d_2) in the source frame, so that
+//   u_0 = r^ . m = (Q + rs d_0) / r,
+// the axis z = (sin ths, cos ths, 0) = sin th r^ + cos th theta^ gives
+//   u_1 = (sin ths d_0 + cos ths m_1 - sin th u_0) / cos th,
+// and phi^ = z x X / (r cos th) gives
+//   u_2 = (g m_2 - d_2 (cos ths d_0 - sin ths m_1)) / (r cos th),
+//   g = cos ths (rs + d_0) - sin ths d_1:
+// 66 FP64 instructions an update where the projection took 79.
 struct LfCol {
-    double v1, v2;      // g_a / (2 h_a) of axes 1, 2 (central differences)
+    double v1, v2;      // g_a h_0 / h_a of axes 1, 2 (differences in units of v0)
     double w0, w1, w2;  // averaging weights w_a
     double rho;
+    double sv;          // s0 v0
     double A[3], B[3], C[3];  // d_i along the column (spherical); Cartesian: C = (x0, y) - Xs
+    // u in units of v0: u_0 = uq Q + ud d_0, u_1 = p0 d_0 + p1 m_1 + p2 u_0,
+    // u_2 = (gc + g0 d_0 - g1 d_1) m_2 - d_2 (g0 d_0 - g1 m_1)   (spherical; Cartesian: u = ud d)
+    double uq, ud, p0, p1, p2, gc, g0, g1;
 };
 
 template <int COORD>
 __device__ __forceinline__ LfCol lf_col(const Geo& G, const Src& S, const Col& c, double kappa) {
     LfCol W;
     const double iC = 1.0 / (G.invh[0] + c.g1 * G.invh[1] + c.g2 * G.invh[2]);
-    W.v1 = c.g1 * G.inv2h[1];
-    W.v2 = c.g2 * G.inv2h[2];
+    const double iv0 = 2.0 * G.h[0];
     W.w0 = G.inv2h[0] * iC;
-    W.w1 = W.v1 * iC;
-    W.w2 = W.v2 * iC;
+    W.w1 = c.g1 * G.inv2h[1] * iC;
+    W.w2 = c.g2 * G.inv2h[2] * iC;
+    W.v1 = c.g1 * (G.h[0] * G.invh[1]);
+    W.v2 = c.g2 * (G.h[0] * G.invh[2]);
     W.rho = iC / (kappa * S.s0);
+    W.sv = S.s0 * G.inv2h[0];
     if (COORD == 1) {
         const double D2 = c.rst - S.Xs[2];
         for (int i = 0; i < 3; ++i) {
@@ -263,18 +279,45 @@ __device__ __forceinline__ LfCol lf_col(const Geo& G, const Src& S, const Col& c
             W.B[i] = c.rct * S.E[3 * i + 1];
             W.C[i] = D2 * S.E[3 * i + 2] - (S.Xs[0] * S.E[3 * i] + S.Xs[1] * S.E[3 * i + 1]);
         }
+        const double sts = S.E[2], cts = S.E[5];  // z on r^_s, theta^_s
+        const double ict = c.g2 * c.x0;            // 1 / cos th
+        W.uq = iv0 * c.g1;
+        W.ud = iv0 * c.g1 * S.rs;
+        W.p0 = iv0 * sts * ict;
+        W.p1 = iv0 * cts * ict;
+        W.p2 = -(c.st * ict);
+        W.g0 = iv0 * cts * c.g2;
+        W.g1 = iv0 * sts * c.g2;
+        W.gc = W.g0 * S.rs;
     } else {
         W.A[0] = W.A[1] = W.A[2] = W.B[0] = W.B[1] = W.B[2] = W.C[2] = 0.0;
         W.C[0] = c.x0 - S.Xs[0];
         W.C[1] = c.ct - S.Xs[1];
+        W.uq = W.p0 = W.p1 = W.p2 = W.gc = W.g0 = W.g1 = 0.0;
+        W.ud = iv0;
     }
     return W;
 }
 
+// 1 / sqrt(x) and sqrt(x) for normal x > 0 from the hardware estimate y (good
+// to about 2^-23) by one third-order step: with e = 1 - x y^2 the root is
+// y (1 - e)^(-1/2) = y (1 + e (1/2 + 3/8 e)) + O(e^3), e^3 ~ 2^-67.
+__device__ __forceinline__ double rsqrt_3(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-(x * y), y, 1.0);
+    return fma(y, e * fma(0.375, e, 0.5), y);
+}
+__device__ __forceinline__ double sqrt_3(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    const double t = x * y;
+    const double e = fma(-t, y, 1.0);
+    return fma(t, e * fma(0.375, e, 0.5), t);
+}
+
 template <int COORD>
-__device__ __forceinline__ double lf_update(const Geo& G, const Src& S, const Col& c, const LfCol& W, double c2,
-                                            double s2, double sx, double ma, double mb, double mc, double tx,
-                                            double up0, double dn0, double up1, double dn1, double up2, double dn2) {
+__device__ __forceinline__ double lf_update(const Src& S, const LfCol& W, double c2, double s2, double sx, double ma,
+                                            double mb, double mc, double tx, double up0, double dn0, double up1,
+                                            double dn1, double up2, double dn2) {
     double d0, d1, d2;
     if (COORD == 1) {
         d0 = fma(c2, W.A[0], fma(s2, W.B[0], W.C[0]));
@@ -285,34 +328,32 @@ __device__ __forceinline__ double lf_update(const Geo& G, const Src& S, const Co
         d1 = W.C[1];
         d2 = c2 - S.Xs[2];
     }
-    const double m1 = S.mi11 * d1 + S.mi12 * d2;
-    const double m2 = S.mi12 * d1 + S.mi22 * d2;
-    const double Q = d0 * d0 + d1 * m1 + d2 * m2;  // > 0: the sweeps skip the fixed cell
-    const double rq = rsqrt_nr(Q);
+    // (every contraction is spelled out: all instances round alike)
+    const double m1 = fma(S.mi11, d1, S.mi12 * d2);
+    const double m2 = fma(S.mi12, d1, S.mi22 * d2);
+    const double Q = fma(d2, m2, fma(d1, m1, d0 * d0));  // > 0: the sweeps skip the fixed cell
+    const double rq = rsqrt_3(Q);
     double u0, u1, u2;
     if (COORD == 1) {
-        // E^T m in the embedding, then on the node's local unit vectors
-        // r^ = (ct c2, ct s2, st), theta^ = (-st c2, -st s2, ct), phi^ = (-s2, c2, 0)
-        const double G0 = d0 * S.E[0] + m1 * S.E[3] + m2 * S.E[6];
-        const double G1 = d0 * S.E[1] + m1 * S.E[4] + m2 * S.E[7];
-        const double G2 = d0 * S.E[2] + m1 * S.E[5] + m2 * S.E[8];
-        const double hz = G0 * c2 + G1 * s2;
-        u0 = c.ct * hz + c.st * G2;
-        u1 = c.ct * G2 - c.st * hz;
-        u2 = G1 * c2 - G0 * s2;
+        u0 = fma(W.uq, Q, W.ud * d0);
+        u1 = fma(W.p2, u0, fma(W.p1, m1, W.p0 * d0));
+        const double gd = W.g0 * d0;
+        u2 = fma(fma(-W.g1, d1, gd + W.gc), m2, -d2 * fma(-W.g1, m1, gd));
     } else {
-        u0 = d0;
-        u1 = m1;
-        u2 = m2;
+        u0 = W.ud * d0;
+        u1 = W.ud * m1;
+        u2 = W.ud * m2;
     }
-    const double R0 = Q * ((dn0 - up0) * G.inv2h[0]) + tx * u0;
-    const double R1 = Q * ((dn1 - up1) * W.v1) + tx * u1;
-    const double R2 = Q * ((dn2 - up2) * W.v2) + tx * u2;
+    const double R0 = fma(Q, dn0 - up0, tx * u0);
+    const double R1 = fma(Q, (dn1 - up1) * W.v1, tx * u1);
+    const double R2 = fma(Q, (dn2 - up2) * W.v2, tx * u2);
     // (ma, mb, mc) = (1 - 2 xi, 2 eta, 1 + 2 xi): the lower-right block of M
-    const double MR1 = ma * R1 + mb * R2;
-    const double MR2 = mb * R1 + mc * R2;
-    const double H = (S.s0 * rq) * sqrt_nr(R0 * R0 + R1 * MR1 + R2 * MR2);
-    return (sx - H) * (W.rho * rq) + ((up0 + dn0) * W.w0 + (up1 + dn1) * W.w1 + (up2 + dn2) * W.w2);
+    const double MR1 = fma(ma, R1, mb * R2);
+    const double MR2 = fma(mb, R1, mc * R2);
+    // (+ DBL_MIN: the root of 0 stays finite; Hamiltonians that small do not occur)
+    const double V = fma(R2, MR2, fma(R1, MR1, fma(R0, R0, 2.2250738585072014e-308)));
+    const double f = fma(-(W.sv * rq), sqrt_3(V), sx);  // s - H
+    return fma(f, W.rho * rq, fma(up2 + dn2, W.w2, fma(up1 + dn1, W.w1, (up0 + dn0) * W.w0)));
 }
 
 // ----- state of one batched solve (host side) -----
@@ -320,10 +361,8 @@ struct Plan {
     Geo G;
     Tabs T;
     int nsrc = 0;
-    int nplanes = 0;          // non-empty tile-planes per sweep
-    int max_plane_tiles = 0;  // largest tile-plane
     int nbblocks = 0;         // boundary-pass blocks per source
-    int nslots = 0;           // partial-sum slots per source per iteration
+    int nslots = 0;           // 8-byte slots per source in part (see SweepArgs)
     double kappa = 1.0, tol = 1e-6;
     int max_iter = 1;         // iteration budget of this group
     int hist_stride = 1;      // row length of eps_hist (the call's max_iter)
@@ -347,11 +386,8 @@ struct Plan {
     double* bnd_rhs = nullptr; // adjoint: right-hand side of the boundary nodes, [nsrc][NB]
     bool continuous = false;  // adjoint: upwind discretisation of Eq. (5) instead of the exact transpose
     bool compact = false;     // adjoint: one node-order copy of the coefficient records
-    std::vector<int> plane_count;  // tiles of each non-empty tile-plane
-    std::vector<int> plane_id;     // its tile-plane number TI + TJ + TK
-    std::vector<int> plane_s0;     // its first tile column sum TI + TJ
     // optional timing of the sweep kernels: an event pair around the
-    // tile-plane launches of each directional sweep, with the launch count
+    // launches of each directional sweep, with the launch count
     std::vector<std::pair<std::pair<hipEvent_t, hipEvent_t>, int>>* timing = nullptr;
 };
 
@@ -371,8 +407,12 @@ struct SweepArgs {
     int* active;
     int* iter;
     int32_t* status;
+    // per source nslots 8-byte slots: the convergence sums of the ncols tile
+    // columns and nbblocks boundary blocks over the iteration's directions so
+    // far, the columns' sweep progress (ncols 64-bit words), and the ticket and
+    // owner words of the source's work queue (sweep_claim)
     double* part;
-    double* part2;
+    double* part2;          // adjoint: sums of |lambda| in the last direction, same first two ranges
     int* counter;
     double* eps_hist;       // optional [nsrc][hist_stride]
     int nslots, nbblocks, nsrc, max_iter, hist_stride;

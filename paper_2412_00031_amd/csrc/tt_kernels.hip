@@ -10,12 +10,12 @@
 //     coordinates, ragged last ones), and each tile column into slabs of tk
 //     consecutive hyperplanes u = i' + j' + k' (sheared tiles: the 14-step ramp
 //     of a skewed 8 x 8 walk is paid once per column, not once per tile);
-//   - tiles with the same TI'+TJ'+TK' form a tile-plane; one launch processes
-//     one tile-plane of every active source.  grid.x is the source, so
-//     consecutive workgroups are one tile of consecutive sources: workgroups
-//     are dealt to the 8 XCDs round-robin, hence every tile of a source runs
-//     on the same XCD (its field stays in that XCD's L2) and the sources that
-//     share an XCD read the same model lines;
+//   - one launch runs a whole directional sweep of all sources: each wave
+//     takes a tile column of a source and marches it slab by slab, waiting for
+//     the two upstream columns to pass each slab (see "sweep scheduling"
+//     below); the columns of a source are marched by waves of one XCD, so its
+//     field moves through that XCD's L2, and consecutive tickets are one
+//     column of consecutive sources, which read the same model lines;
 //   - inside a tile one 64-lane wave owns the 8 x 8 columns; the tile and its
 //     one-node halo are staged in LDS with contiguous column loads, then at
 //     step t lane (li, lj) updates the node of its column on hyperplane
@@ -134,6 +134,7 @@ __global__ void k_src_setup(Geo G, const double* __restrict__ pos, const double*
     const double det = b * c - f * f;
     S.mi11 = c / det; S.mi12 = -f / det; S.mi22 = b / det;
     S.s0 = par[3 * q];
+    S.rs = p0;
     S.fb[0] = cell_base(G, 0, p0);
     S.fb[1] = cell_base(G, 1, p1);
     S.fb[2] = cell_base(G, 2, p2);
@@ -179,8 +180,7 @@ __global__ void k_solve_init(SweepArgs a, const double* init, double v0, double 
         const int j = (int)(q % a.G.n[1]), i = (int)(q / a.G.n[1]);
         f[x] = in_fixed(S, i, j, k) ? vfix : (ti ? ti[x] : v0);
     }
-    // partial-sum slots start at zero: slots of slab indices a short tile
-    // column does not have are never written
+    // sums, sweep progress and queue words start at zero
     for (long long x = (long long)blockIdx.x * blockDim.x + threadIdx.x; x < a.nslots;
          x += (long long)gridDim.x * blockDim.x) {
         a.part[(long long)src * a.nslots + x] = 0.0;
@@ -209,6 +209,7 @@ struct Dir {
 
 struct TileCtx {
     int TI, TJ, TK, lane, li, lj, ext_i, ext_j;
+    int ip, jp;    // this lane's column (sweep-relative; the tile corner's if the lane owns none)
     int t0, t1;    // wave-uniform walk: steps t0 <= t < t1 (u = TK tk + t)
     int kp0;       // this lane's k' at step 0 (k' = kp0 + t)
     int kplo, kphi;  // record fetch clamp: this lane's k' range in the tile (a valid k' if empty)
@@ -220,35 +221,29 @@ struct TileCtx {
     // forward fetches: record and axis-2 table index at step 0, and the step
     // range [tlo, thi] that the clamp of k' to [kplo, kphi] allows
     int rr0, tt0, tlo, thi;
-    int slot;          // partial-sum slot of the tile within one directional sweep
+    // this lane updates its node at the steps ta <= t < ta + tn except tf, tf + 1 (the fixed cell)
+    int ta, tf;
+    unsigned tn;
 };
 
+// the column's part of the context
 template <int DIR>
-__device__ __forceinline__ TileCtx tile_ctx(const Geo& G, const Src& S, int plane, int s0) {
+__device__ __forceinline__ TileCtx col_ctx(const Geo& G, const Src& S, int TI, int TJ) {
     using D = Dir<DIR>;
     TileCtx c;
-    tile_decode(G, plane, s0, blockIdx.y, c.TI, c.TJ, c.TK);
+    c.TI = TI;
+    c.TJ = TJ;
     c.lane = threadIdx.x;
     c.li = c.lane >> 3;
     c.lj = c.lane & 7;
     c.ext_i = min(kBI, G.m[0] - c.TI * kBI);
     c.ext_j = min(kBJ, G.m[1] - c.TJ * kBJ);
     c.colv = c.li < c.ext_i && c.lj < c.ext_j;
-    const int ip = c.TI * kBI + (c.colv ? c.li : 0), jp = c.TJ * kBJ + (c.colv ? c.lj : 0);
-    c.i = D::s0 > 0 ? 1 + ip : G.n[0] - 2 - ip;
-    c.j = D::s1 > 0 ? 1 + jp : G.n[1] - 2 - jp;
+    c.ip = c.TI * kBI + (c.colv ? c.li : 0);
+    c.jp = c.TJ * kBJ + (c.colv ? c.lj : 0);
+    c.i = D::s0 > 0 ? 1 + c.ip : G.n[0] - 2 - c.ip;
+    c.j = D::s1 > 0 ? 1 + c.jp : G.n[1] - 2 - c.jp;
     c.fcol = (unsigned)(c.i - S.fb[0]) <= 1u && (unsigned)(c.j - S.fb[1]) <= 1u;
-    const int U0 = c.TK * G.tk;
-    const int ucol = kBI * (c.TI + c.TJ);  // u of the column's first node (i', j' at the tile corner, k' = 0)
-    c.t0 = max(0, ucol - U0);
-    c.t1 = min(G.tk, ucol + (c.ext_i - 1) + (c.ext_j - 1) + G.m[2] - U0);
-    c.kp0 = U0 - ip - jp;
-    // prefetches past the walk re-read the lane's last record of this tile
-    // (a cache hit) instead of the next slab's
-    c.kplo = max(0, c.kp0 + c.t0);
-    c.kphi = min(G.m[2] - 1, c.kp0 + c.t1 - 1);
-    if (c.kplo > c.kphi) c.kplo = c.kphi = min(max(c.kp0 + c.t0, 0), G.m[2] - 1);
-    c.kq0 = U0 - ucol + 1;
     c.kbase = D::s2 > 0 ? 1 : G.n[2] - 2;
     // record index ((i W + w) n1p + j + joff) in the aligned layout of this sweep,
     // w = j + k (family 0) or j - k + n2 - 1 (family 1), k = kbase + s2 k': linear
@@ -256,12 +251,190 @@ __device__ __forceinline__ TileCtx tile_ctx(const Geo& G, const Src& S, int plan
     const int w0 = D::fam == 0 ? c.j + c.kbase : c.j - c.kbase + G.n[2] - 1;
     c.rbase = (c.i * G.W + w0) * G.n1p + c.j + G.joff[D::s1 > 0 ? 0 : 1];
     c.rstep = D::s1 * G.n1p;
+    return c;
+}
+
+// the slab's part
+template <int DIR>
+__device__ __forceinline__ void slab_ctx(const Geo& G, const Src& S, TileCtx& c, int TK) {
+    using D = Dir<DIR>;
+    c.TK = TK;
+    const int U0 = TK * G.tk;
+    const int ucol = kBI * (c.TI + c.TJ);  // u of the column's first node (i', j' at the tile corner, k' = 0)
+    c.t0 = max(0, ucol - U0);
+    c.t1 = min(G.tk, ucol + (c.ext_i - 1) + (c.ext_j - 1) + G.m[2] - U0);
+    c.kp0 = U0 - c.ip - c.jp;
+    // prefetches past the walk re-read the lane's last record of this tile
+    // (a cache hit) instead of the next slab's
+    c.kplo = max(0, c.kp0 + c.t0);
+    c.kphi = min(G.m[2] - 1, c.kp0 + c.t1 - 1);
+    if (c.kplo > c.kphi) c.kplo = c.kphi = min(max(c.kp0 + c.t0, 0), G.m[2] - 1);
+    c.kq0 = U0 - ucol + 1;
     c.rr0 = c.rbase + c.rstep * c.kp0;
     c.tt0 = c.kbase + D::s2 * c.kp0;
     c.tlo = c.kplo - c.kp0;
     c.thi = c.kphi - c.kp0;
-    c.slot = (c.TI * G.nt[1] + c.TJ) * G.nt[2] + (c.TK - col_tile_lo(G, c.TI + c.TJ));
-    return c;
+    c.ta = max(c.t0, -c.kp0);
+    c.tn = c.colv ? (unsigned)max(min(c.t1, G.m[2] - c.kp0) - c.ta, 0) : 0u;
+    // k = kbase + s2 (kp0 + t) in {fb, fb + 1}
+    const int tb = D::s2 * (S.fb[2] - c.kbase) - c.kp0;
+    c.tf = c.fcol ? (D::s2 > 0 ? tb : tb - 1) : -4;
+}
+
+// is step t one of this lane's updates?  (a padded walk's t < t1 + 6, so that -4 never matches)
+__device__ __forceinline__ bool step_on(const TileCtx& c, int t) {
+    return (unsigned)(t - c.ta) < c.tn && (unsigned)(t - c.tf) > 1u;
+}
+
+// ------------------------------------------------------- sweep scheduling
+// One launch runs a directional sweep of up to kMarchSources sources.  Its
+// workgroups are one wave each; a wave takes a tile column of a source, marches
+// it slab by slab from its first to its last, and takes the next.  Between
+// slabs it waits for the two upstream columns, which other waves march, to
+// have passed the slab it is about to walk.
+//
+// What this replaces is a launch per tile-plane: at one 41^3 source a sweep
+// was 17 dependent launches of 7.5 us, at 128 101^3 sources 52000 launches per
+// solve, which the host could not enqueue faster than 7.5 us apiece.
+//
+// Who may wait for whom.  The sources are dealt to nb <= 8 batches (source
+// c0 + b + nb q belongs to batch b).  A batch is claimed by one XCD (the first
+// wave to ask sets its owner word) and worked on by waves of that XCD only; its
+// columns are handed out by a ticket counter, ordered by TI + TJ, then TI,
+// then source.  A column's upstream neighbours have lower tickets, so whoever
+// holds them is already running, never waits for a later ticket, and finishes:
+// every wait ends, however many waves are resident.
+//
+// How a slab's values reach the next wave.  All waves of a batch share the
+// XCD's L2: a wave's stores are in that L2 once s_waitcnt vmcnt(0) has passed,
+// then it stores its progress word; a waiting wave polls that word past its L1
+// (agent-scope load) and invalidates its L1 (agent-scope acquire) before it
+// stages the tile.  8 KB handed over this way take 1.0 us from wave to wave; a
+// release that works across XCDs (it writes the whole L2 back) takes 1.5 us on
+// an idle chip and 8.7 us with 256 such chains.
+constexpr int kMarchBatches = 8;                    // one per XCD
+constexpr int kMarchSources = 64 * kMarchBatches;   // sources of one launch: a batch's active mask is one wave ballot
+constexpr unsigned long long kWaitTicks = 400000000ull;  // 4 s of the 100 MHz clock: no wait lasts that long
+
+__device__ __forceinline__ unsigned* queue_words(const SweepArgs& a, int src) {
+    return reinterpret_cast<unsigned*>(a.part + (long long)src * a.nslots + 2 * a.G.ncols + a.nbblocks);
+}
+
+// between two sweeps: every queue back to "no ticket taken, no owner"
+__device__ __forceinline__ void queue_reset(const SweepArgs& a, int src) {
+    if (threadIdx.x < 2) queue_words(a, src)[threadIdx.x] = 0u;
+}
+
+// convergence sums run over the iteration's directions
+__device__ __forceinline__ void part_add(double* slot, int dir, double v) { *slot = dir == 0 ? v : *slot + v; }
+
+__device__ __forceinline__ unsigned long long* progress_words(const SweepArgs& a, int src) {
+    return reinterpret_cast<unsigned long long*>(a.part + (long long)src * a.nslots + a.G.ncols + a.nbblocks);
+}
+
+// The __syncthreads() in these helpers cost nothing in a workgroup of one wave
+// (no instruction); they keep the wave together.  Without them the compiler
+// joins the "lane 0 only" branch at the end of one column with that at the
+// start of the next, lanes 1..63 run ahead with a ticket of their own, and the
+// ballots below see half a wave.
+
+// does this wave's XCD own the batch whose queue is q (claiming it if nobody does)?
+__device__ __forceinline__ bool sweep_claim(unsigned* q, unsigned me) {
+    __syncthreads();
+    unsigned own = 0u;
+    if (threadIdx.x == 0 && __hip_atomic_compare_exchange_strong(q + 1, &own, me, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                                 __HIP_MEMORY_SCOPE_AGENT))
+        own = me;
+    __syncthreads();
+    return (unsigned)__builtin_amdgcn_readfirstlane((int)own) == me;
+}
+
+__device__ __forceinline__ unsigned sweep_ticket(unsigned* q) {
+    __syncthreads();
+    unsigned t = 0u;
+    if (threadIdx.x == 0) t = __hip_atomic_fetch_add(q, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    return (unsigned)__builtin_amdgcn_readfirstlane((int)t);
+}
+
+// Wait until both upstream columns have passed slab TK of this sweep (word >=
+// target), then drop stale L1 lines.  up: this lane's neighbour's word (lanes
+// 0 and 1) or NULL.  false if the wait was given up (never, unless a wave was
+// lost): the caller carries on, so that the launch ends, and poisons its
+// convergence sum, so that the source cannot be reported converged.
+__device__ __forceinline__ bool wait_upstream(const unsigned long long* up, unsigned long long target) {
+    unsigned long long start = 0;
+    bool ok = true;
+    for (;;) {
+        const unsigned long long v =
+            up ? __hip_atomic_load(up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : ~0ull;
+        if (__all(v >= target)) break;
+        __builtin_amdgcn_s_sleep(1);
+        const unsigned long long now = __builtin_amdgcn_s_memrealtime();
+        if (start == 0) start = now;
+        if (now - start > kWaitTicks) {
+            ok = false;
+            break;
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    return ok;
+}
+
+// this wave's stores are in the XCD's L2, then its column's progress says so
+__device__ __forceinline__ void publish(unsigned long long* word, unsigned long long value) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (threadIdx.x == 0) __hip_atomic_store(word, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __syncthreads();
+}
+
+// Hand out this launch's columns: column(src, TI, TJ) for every one of this
+// wave's tickets.  XCDs start at different batches, so that each gets one.
+template <class F>
+__device__ __forceinline__ void march(const SweepArgs& a, const Geo& G, int c0, int cn, F column) {
+    const int xcd = __builtin_amdgcn_s_getreg(20 | (31 << 11)) & 15;  // XCC_ID
+    const int nb = min(kMarchBatches, cn);
+    for (int e = 0; e < nb; ++e) {
+        const int b = (xcd + e) % nb;
+        unsigned* q = queue_words(a, c0 + b);
+        if (!sweep_claim(q, (unsigned)xcd + 1u)) continue;
+        const int mine = b + nb * (int)threadIdx.x;
+        const unsigned long long mask = __ballot(mine < cn && a.active[c0 + min(mine, cn - 1)]);
+        const unsigned nact = (unsigned)__popcll(mask), ntask = nact * (unsigned)G.ncols;
+        // this lane's source is the rank-th active one of the batch
+        const unsigned rank = (unsigned)__popcll(mask & ((1ull << threadIdx.x) - 1ull));
+        const bool act = (mask >> threadIdx.x) & 1ull;
+        if (nact == 0) continue;
+        for (;;) {
+            const unsigned t = sweep_ticket(q);
+            if (t >= ntask) break;
+            const unsigned col = t / nact, k = t - col * nact;
+            const int l = __ffsll((unsigned long long)__ballot(act && rank == k)) - 1;
+            int TI, TJ;
+            col_decode(G, (int)col, TI, TJ);
+            column(c0 + b + nb * l, TI, TJ);
+        }
+    }
+}
+
+// March one tile column: tile(TK) for every slab in order, each after its wait.
+template <int DIR, class F>
+__device__ __forceinline__ bool march_column(const SweepArgs& a, const Geo& G, int src, int TI, int TJ, F tile) {
+    unsigned long long* prog = progress_words(a, src);
+    unsigned long long* own = prog + TI * G.nt[1] + TJ;
+    const unsigned long long* up = nullptr;
+    if (threadIdx.x == 0 && TI > 0) up = own - G.nt[1];
+    if (threadIdx.x == 1 && TJ > 0) up = own - 1;
+    // progress of sweep number e of the solve: (e << 16) + slabs passed, so
+    // that a finished earlier sweep's word is below every target of this one
+    const unsigned long long base = ((unsigned long long)a.iter[src] * 8 + DIR + 1) << 16;
+    const int hi = col_tile_hi(G, TI + TJ);
+    bool ok = true;
+    for (int TK = col_tile_lo(G, TI + TJ); TK <= hi; ++TK) {
+        ok = tile(TK, up, base + TK + 1) && ok;
+        publish(own, TK < hi ? base + TK + 1 : base + 0xffffu);
+    }
+    return ok;
 }
 
 // Staged tile: the (8+2) x (8+2) columns of the tile and its i'/j' halo, each
@@ -328,7 +501,10 @@ __device__ __forceinline__ void stage_tile(const Geo& G, const TileCtx& c, const
     const int si = (int)G.si, sj = (int)G.sj;
     const int oi = stage_origin<D::s0>(G, 0, c.TI), oj = stage_origin<D::s1>(G, 1, c.TJ);
     const int lo = (int)(xlo > -1 ? xlo : -1), hi = (int)(xhi < G.N ? xhi : G.N);
-    const int dc = c.lane / hp, q = 2 * (c.lane - dc * hp);
+    // (opaque: or the addresses of every load are kept over the whole column, in 100 registers)
+    int lane = c.lane;
+    asm volatile("" : "+v"(lane));
+    const int dc = lane / hp, q = 2 * (lane - dc * hp);
     const bool lane_on = dc < cpi;
     int ci = dc / kTC, cj = dc - ci * kTC;
     // lower slot q holds entry kk = q (s2 > 0) or Lp - 1 - q (s2 < 0) of the
@@ -390,7 +566,9 @@ __device__ __forceinline__ void unstage_tile(const Geo& G, const TileCtx& c, dou
     const int base = (int)nidx(G, stage_origin<D::s0>(G, 0, c.TI) + D::s0, stage_origin<D::s1>(G, 1, c.TJ) + D::s1,
                                c.kbase);
     const unsigned kmax = (unsigned)G.m[2];
-    const int g = c.lane >> 4, r = c.lane & 15;
+    int lane = c.lane;
+    asm volatile("" : "+v"(lane));  // as in stage_tile
+    const int g = lane >> 4, r = lane & 15;
     const bool colj0 = g < c.ext_j, colj1 = g + 4 < c.ext_j;
     // node (li, lj, entry q + 1): element base + li si + lj sj + s2 k', with
     // k' = kq0 - 1 - li - lj + q, and slot ((li + 1) kTC + lj + 1) Lp + q + 1
@@ -480,72 +658,70 @@ __device__ __forceinline__ void fwd_fetch(const TileCtx& c, const double* __rest
 // so that LDS offsets become immediates and the staging and write-back index
 // arithmetic folds; the host picks an instance whose TKC equals the depth.
 template <int COORD, int DIR, int TKC>
-__global__ void __launch_bounds__(64) k_fwd_sweep(SweepArgs a, int plane, int s0) {
+__global__ void __launch_bounds__(64, 3) k_fwd_sweep(SweepArgs a, int c0, int cn) {
     using D = Dir<DIR>;
     extern __shared__ double lds[];
-    const int src = blockIdx.x;
-    if (!a.active[src]) return;
     Geo G = a.G;
     if (TKC > 0) G.tk = TKC;
-    const Src S = a.src[src];
-    const TileCtx c = tile_ctx<DIR>(G, S, plane, s0);
-    if (c.t1 <= c.t0) {  // a ragged column's slab with no nodes
-        if (c.lane == 0) a.part[(long long)src * a.nslots + DIR * G.ntiles + c.slot] = 0.0;
-        return;
-    }
-    const Col cl = make_col(G, a.T, c.i, c.j);
-    const LfCol W = lf_col<COORD>(G, S, cl, a.kappa);
-    double* __restrict__ fld = a.field + (long long)src * G.N;
     const double* __restrict__ mdl = a.model + (long long)D::lay * G.Sa * 4;
     const double2* __restrict__ t2 = a.T.t2;
     const int Lp = tile_pitch(G.tk);
-    const int kmax = G.m[2];
-
-    FwdSlot ring[kPre];
+    march(a, G, c0, cn, [&](int src, int TI, int TJ) {
+        const Src S = a.src[src];
+        TileCtx c = col_ctx<DIR>(G, S, TI, TJ);
+        const Col cl = make_col(G, a.T, c.i, c.j);
+        const LfCol W = lf_col<COORD>(G, S, cl, a.kappa);
+        double* __restrict__ fld = a.field + (long long)src * G.N;
+        const int own = ((c.li + 1) * kTC + c.lj + 1) * Lp;
+        double eps = 0.0;
+        const bool ok = march_column<DIR>(a, G, src, TI, TJ, [&](int TK, const unsigned long long* up, unsigned long long target) {
+            slab_ctx<DIR>(G, S, c, TK);
+            if (c.t1 <= c.t0) return true;  // a ragged column's slab with no nodes
+            FwdSlot ring[kPre];
 #pragma unroll
-    for (int u = 0; u < kPre; ++u) fwd_fetch<DIR>(c, mdl, t2, c.t0 + u, ring[u]);
-    stage_tile<DIR>(G, c, fld, -(long long)src * G.N, (long long)(a.nsrc - src) * G.N - 2, lds);
-    __syncthreads();
+            for (int u = 0; u < kPre; ++u) fwd_fetch<DIR>(c, mdl, t2, c.t0 + u, ring[u]);
+            const bool waited = wait_upstream(up, target);
+            stage_tile<DIR>(G, c, fld, -(long long)src * G.N, (long long)(a.nsrc - src) * G.N - 2, lds);
+            __syncthreads();
 
-    const int own = ((c.li + 1) * kTC + c.lj + 1) * Lp;
-    double eps = 0.0;
-    // the step count is padded to a multiple of kPre: no branch encloses a load
-    for (int tb = c.t0; tb < c.t1; tb += kPre) {
+            // The step count is padded to a multiple of kPre and no step has a branch:
+            // every lane forms an update, one that has none to make stores it into the
+            // window's corner column, which nothing reads.  (The LDS reads of a padded
+            // step stay inside the window: at most 3 entries past a column that others
+            // follow.)  So the factor of one step fills the waits of the step before:
+            // 553 cycles a step of a lone wave with a branch around each update.
+            for (int tb = c.t0; tb < c.t1; tb += kPre) {
 #pragma unroll
-        for (int u = 0; u < kPre; ++u) {
-            const int t = tb + u;
-            {
-                FwdSlot& r = ring[u];
-                const int kp = c.kp0 + t;
-                if (c.colv && t < c.t1 && (unsigned)kp < (unsigned)kmax) {
-                    const int ka = c.kbase + D::s2 * kp;
-                    if (!(c.fcol && (unsigned)(ka - S.fb[2]) <= 1u)) {
-                        // sweep-relative neighbours: "up" = already updated this sweep
-                        // slot of entry t (mirrored columns when s2 < 0): entry t + 1 is at o + s2
-                        constexpr int sg = D::s2;
-                        const int o = sg > 0 ? own + t : own + Lp - 1 - t;
-                        const double cur = lds[o + sg];
-                        const double up_i = lds[o - kTC * Lp], dn_i = lds[o + kTC * Lp + 2 * sg];
-                        const double up_j = lds[o - Lp], dn_j = lds[o + Lp + 2 * sg];
-                        const double up_k = lds[o], dn_k = lds[o + 2 * sg];
-                        const double m0 = D::s0 > 0 ? up_i : dn_i, p0 = D::s0 > 0 ? dn_i : up_i;
-                        const double m1 = D::s1 > 0 ? up_j : dn_j, p1 = D::s1 > 0 ? dn_j : up_j;
-                        const double m2 = D::s2 > 0 ? up_k : dn_k, p2 = D::s2 > 0 ? dn_k : up_k;
-                        const double nv = lf_update<COORD>(G, S, cl, W, r.c2, r.s2, r.sx, r.ma, r.mb, r.mc, cur, m0,
-                                                           p0, m1, p1, m2, p2);
-                        lds[o + sg] = nv;
-                        eps += fabs(nv - cur);
-                    }
+                for (int u = 0; u < kPre; ++u) {
+                    const int t = tb + u;
+                    FwdSlot& r = ring[u];
+                    // sweep-relative neighbours: "up" = already updated this sweep
+                    // slot of entry t (mirrored columns when s2 < 0): entry t + 1 is at o + s2
+                    constexpr int sg = D::s2;
+                    const int o = sg > 0 ? own + t : own + Lp - 1 - t;
+                    const double cur = lds[o + sg];
+                    const double up_i = lds[o - kTC * Lp], dn_i = lds[o + kTC * Lp + 2 * sg];
+                    const double up_j = lds[o - Lp], dn_j = lds[o + Lp + 2 * sg];
+                    const double up_k = lds[o], dn_k = lds[o + 2 * sg];
+                    const double m0 = D::s0 > 0 ? up_i : dn_i, p0 = D::s0 > 0 ? dn_i : up_i;
+                    const double m1 = D::s1 > 0 ? up_j : dn_j, p1 = D::s1 > 0 ? dn_j : up_j;
+                    const double m2 = D::s2 > 0 ? up_k : dn_k, p2 = D::s2 > 0 ? dn_k : up_k;
+                    const double nv = lf_update<COORD>(S, W, r.c2, r.s2, r.sx, r.ma, r.mb, r.mc, cur, m0, p0, m1, p1,
+                                                       m2, p2);
+                    const bool on = step_on(c, t);
+                    lds[on ? o + sg : 0] = nv;
+                    eps += on ? fabs(nv - cur) : 0.0;
+                    fwd_fetch<DIR>(c, mdl, t2, t + kPre, r);
                 }
-                fwd_fetch<DIR>(c, mdl, t2, t + kPre, r);
             }
-        }
-    }
-    __syncthreads();
-    unstage_tile<DIR>(G, c, fld, lds, Lp);
-    fwd_kface_nodes<DIR>(G, S, c, fld, lds, own, Lp, eps);
-    eps = wave_sum(eps);
-    if (c.lane == 0) a.part[(long long)src * a.nslots + DIR * G.ntiles + c.slot] = eps;
+            __syncthreads();
+            unstage_tile<DIR>(G, c, fld, lds, Lp);
+            fwd_kface_nodes<DIR>(G, S, c, fld, lds, own, Lp, eps);
+            return waited;
+        });
+        eps = wave_sum(ok ? eps : HUGE_VAL);
+        if (c.lane == 0) part_add(a.part + (long long)src * a.nslots + TI * G.nt[1] + TJ, DIR, eps);
+    });
 }
 
 // model records (s, 1 - 2 xi, 2 eta, 1 + 2 xi) in the four aligned layouts
@@ -585,6 +761,7 @@ __device__ __forceinline__ double fwd_bval(const Geo& G, const Src& S, const dou
 __global__ void __launch_bounds__(kBndThreads) k_fwd_bnd(SweepArgs a, int dir) {
     __shared__ double sh[4];
     const int src = blockIdx.y;
+    if (blockIdx.x == 0) queue_reset(a, src);
     if (!a.active[src]) return;
     const Geo& G = a.G;
     const Src S = a.src[src];
@@ -603,7 +780,7 @@ __global__ void __launch_bounds__(kBndThreads) k_fwd_bnd(SweepArgs a, int dir) {
         }
     }
     d = block_sum256(d, sh);
-    if (threadIdx.x == 0) a.part[(long long)src * a.nslots + 8 * G.ntiles + dir * a.nbblocks + blockIdx.x] = d;
+    if (threadIdx.x == 0) part_add(a.part + (long long)src * a.nslots + G.ncols + blockIdx.x, dir, d);
 }
 
 __device__ __forceinline__ double fixed_sum(const double* p, int cnt, double* sh) {
@@ -633,7 +810,7 @@ __global__ void __launch_bounds__(256) k_fwd_finalize(SweepArgs a) {
     __shared__ double sh[4];
     const int src = blockIdx.x;
     if (!a.active[src]) return;
-    const double tot = fixed_sum(a.part + (long long)src * a.nslots, a.nslots, sh);
+    const double tot = fixed_sum(a.part + (long long)src * a.nslots, a.G.ncols + a.nbblocks, sh);
     if (threadIdx.x == 0) finish_iteration(a, src, tot / (double)a.G.N);
 }
 
@@ -841,8 +1018,9 @@ __device__ __forceinline__ bool tile_meets_box(const Geo& G, const TileCtx& c, c
 }
 
 template <int DIR, bool RHS, bool COMPACT>
-__device__ __forceinline__ void adj_tile(const SweepArgs& a, const Geo& G, const Src& S, const TileCtx& c, int src,
-                                         double* lds) {
+__device__ __forceinline__ bool adj_tile(const SweepArgs& a, const Geo& G, const Src& S, const TileCtx& c, int src,
+                                         double* lds, const unsigned long long* up, unsigned long long target,
+                                         double& dsum, double& asum) {
     using D = Dir<DIR>;
     constexpr bool last = (DIR == 7);
     double* __restrict__ fld = a.field + (long long)src * G.N;
@@ -851,86 +1029,78 @@ __device__ __forceinline__ void adj_tile(const SweepArgs& a, const Geo& G, const
     const double* __restrict__ rh = a.rhs + (long long)src * G.N;
     const long long xb = nidx(G, c.i, c.j, c.kbase);
     const int Lp = tile_pitch(G.tk);
-    const int kmax = G.m[2];
 
     AdjSlot ring[kPreAdj];
 #pragma unroll
     for (int u = 0; u < kPreAdj; ++u) adj_fetch<DIR, RHS, COMPACT>(c, cf, rh, xb, c.t0 + u, ring[u]);
+    const bool waited = wait_upstream(up, target);
     stage_tile<DIR>(G, c, fld, -(long long)src * G.N, (long long)(a.nsrc - src) * G.N - 2, lds);
     __syncthreads();
 
     const int own = ((c.li + 1) * kTC + c.lj + 1) * Lp;
-    double dsum = 0.0, asum = 0.0;
     // the step count is padded to a multiple of kPreAdj: no branch encloses a load
     for (int tb = c.t0; tb < c.t1; tb += kPreAdj) {
 #pragma unroll
         for (int u = 0; u < kPreAdj; ++u) {
             const int t = tb + u;
-            {
-                AdjSlot& r = ring[u];
-                const int kp = c.kp0 + t;
-                if (c.colv && t < c.t1 && (unsigned)kp < (unsigned)kmax) {
-                    const int ka = c.kbase + D::s2 * kp;
-                    if (!(c.fcol && (unsigned)(ka - S.fb[2]) <= 1u)) {
-                        // slot of entry t (mirrored columns when s2 < 0): entry t + 1 is at o + s2
-                        constexpr int sg = D::s2;
-                        const int o = sg > 0 ? own + t : own + Lp - 1 - t;
-                        const double cur = lds[o + sg];
-                        const double up_i = lds[o - kTC * Lp], dn_i = lds[o + kTC * Lp + 2 * sg];
-                        const double up_j = lds[o - Lp], dn_j = lds[o + Lp + 2 * sg];
-                        const double up_k = lds[o], dn_k = lds[o + 2 * sg];
-                        // record: coefficients of lambda(x + e_a), lambda(x - e_a) at 2a, 2a + 1,
-                        // divided by the diagonal like the right-hand side.  The
-                        // sweep-downstream terms (values of the previous sweep) go first, the
-                        // upstream ones (updated on the previous step) last.
-                        constexpr int di = D::s0 > 0 ? 0 : 1, dj = D::s1 > 0 ? 2 : 3, dk = D::s2 > 0 ? 4 : 5;
-                        double acc = r.b;
-                        acc -= r.r[di] * dn_i;
-                        acc -= r.r[dj] * dn_j;
-                        acc -= r.r[dk] * dn_k;
-                        acc -= r.r[di ^ 1] * up_i;
-                        acc -= r.r[dj ^ 1] * up_j;
-                        acc -= r.r[dk ^ 1] * up_k;
-                        const double nv = acc;
-                        lds[o + sg] = nv;
-                        dsum += fabs(nv - cur);
-                        if (last) asum += fabs(nv);
-                    }
-                }
-                adj_fetch<DIR, RHS, COMPACT>(c, cf, rh, xb, t + kPreAdj, r);
-            }
+            AdjSlot& r = ring[u];
+            // slot of entry t (mirrored columns when s2 < 0): entry t + 1 is at o + s2
+            constexpr int sg = D::s2;
+            const int o = sg > 0 ? own + t : own + Lp - 1 - t;
+            const double cur = lds[o + sg];
+            const double up_i = lds[o - kTC * Lp], dn_i = lds[o + kTC * Lp + 2 * sg];
+            const double up_j = lds[o - Lp], dn_j = lds[o + Lp + 2 * sg];
+            const double up_k = lds[o], dn_k = lds[o + 2 * sg];
+            // record: coefficients of lambda(x + e_a), lambda(x - e_a) at 2a, 2a + 1,
+            // divided by the diagonal like the right-hand side.  The
+            // sweep-downstream terms (values of the previous sweep) go first, the
+            // upstream ones (updated on the previous step) last.
+            constexpr int di = D::s0 > 0 ? 0 : 1, dj = D::s1 > 0 ? 2 : 3, dk = D::s2 > 0 ? 4 : 5;
+            double acc = r.b;
+            acc -= r.r[di] * dn_i;
+            acc -= r.r[dj] * dn_j;
+            acc -= r.r[dk] * dn_k;
+            acc -= r.r[di ^ 1] * up_i;
+            acc -= r.r[dj ^ 1] * up_j;
+            acc -= r.r[dk ^ 1] * up_k;
+            const double nv = acc;
+            const bool on = step_on(c, t);
+            lds[on ? o + sg : 0] = nv;  // no branch in a step, as in k_fwd_sweep
+            dsum += on ? fabs(nv - cur) : 0.0;
+            if (last) asum += on ? fabs(nv) : 0.0;
+            adj_fetch<DIR, RHS, COMPACT>(c, cf, rh, xb, t + kPreAdj, r);
         }
     }
     __syncthreads();
     unstage_tile<DIR>(G, c, fld, lds, Lp);
-    dsum = wave_sum(dsum);
-    asum = wave_sum(asum);
-    if (c.lane == 0) {
-        a.part[(long long)src * a.nslots + DIR * G.ntiles + c.slot] = dsum;
-        if (last) a.part2[(long long)src * a.nslots + c.slot] = asum;
-    }
+    return waited;
 }
 
 // TKC: compile-time tile depth as for k_fwd_sweep (0: from the geometry)
 template <int COORD, int DIR, bool COMPACT, int TKC>
-__global__ void __launch_bounds__(64) k_adj_sweep(SweepArgs a, int plane, int s0) {
+__global__ void __launch_bounds__(64, 3) k_adj_sweep(SweepArgs a, int c0, int cn) {
     extern __shared__ double lds[];
-    const int src = blockIdx.x;
-    if (!a.active[src]) return;
     Geo G = a.G;
     if (TKC > 0) G.tk = TKC;
-    const Src S = a.src[src];
-    const TileCtx c = tile_ctx<DIR>(G, S, plane, s0);
-    if (c.t1 <= c.t0) {  // a ragged column's slab with no nodes
+    march(a, G, c0, cn, [&](int src, int TI, int TJ) {
+        const Src S = a.src[src];
+        TileCtx c = col_ctx<DIR>(G, S, TI, TJ);
+        double dsum = 0.0, asum = 0.0;
+        const bool ok = march_column<DIR>(a, G, src, TI, TJ, [&](int TK, const unsigned long long* up, unsigned long long target) {
+            slab_ctx<DIR>(G, S, c, TK);
+            if (c.t1 <= c.t0) return true;  // a ragged column's slab with no nodes
+            // wave-uniform: only tiles that meet the right-hand side read it
+            if (tile_meets_box<DIR>(G, c, a.box + src * 6))
+                return adj_tile<DIR, true, COMPACT>(a, G, S, c, src, lds, up, target, dsum, asum);
+            return adj_tile<DIR, false, COMPACT>(a, G, S, c, src, lds, up, target, dsum, asum);
+        });
+        dsum = wave_sum(ok ? dsum : HUGE_VAL);
+        asum = wave_sum(asum);
         if (c.lane == 0) {
-            a.part[(long long)src * a.nslots + DIR * G.ntiles + c.slot] = 0.0;
-            if (DIR == 7) a.part2[(long long)src * a.nslots + c.slot] = 0.0;
+            part_add(a.part + (long long)src * a.nslots + TI * G.nt[1] + TJ, DIR, dsum);
+            if (DIR == 7) a.part2[(long long)src * a.nslots + TI * G.nt[1] + TJ] = asum;
         }
-        return;
-    }
-    // wave-uniform: only tiles that meet the right-hand side read it
-    if (tile_meets_box<DIR>(G, c, a.box + src * 6)) adj_tile<DIR, true, COMPACT>(a, G, S, c, src, lds);
-    else adj_tile<DIR, false, COMPACT>(a, G, S, c, src, lds);
+    });
 }
 
 // Transposed boundary pass: lambda_b = rhs_b - sum_{rows r != b} J_{r, b} lambda_r,
@@ -971,6 +1141,7 @@ __device__ double adj_bval(const Geo& G, const Src& S, const double* lam, const 
 __global__ void __launch_bounds__(kBndThreads) k_adj_bnd(SweepArgs a, int dir) {
     __shared__ double sh[4];
     const int src = blockIdx.y;
+    if (blockIdx.x == 0) queue_reset(a, src);
     if (!a.active[src]) return;
     const Geo& G = a.G;
     const Src S = a.src[src];
@@ -993,8 +1164,8 @@ __global__ void __launch_bounds__(kBndThreads) k_adj_bnd(SweepArgs a, int dir) {
     d = block_sum256(d, sh);
     const double as = (dir == 7) ? block_sum256(av, sh) : 0.0;
     if (threadIdx.x == 0) {
-        a.part[(long long)src * a.nslots + 8 * G.ntiles + dir * a.nbblocks + blockIdx.x] = d;
-        if (dir == 7) a.part2[(long long)src * a.nslots + G.ntiles + blockIdx.x] = as;
+        part_add(a.part + (long long)src * a.nslots + G.ncols + blockIdx.x, dir, d);
+        if (dir == 7) a.part2[(long long)src * a.nslots + G.ncols + blockIdx.x] = as;
     }
 }
 
@@ -1002,8 +1173,8 @@ __global__ void __launch_bounds__(256) k_adj_finalize(SweepArgs a) {
     __shared__ double sh[4];
     const int src = blockIdx.x;
     if (!a.active[src]) return;
-    const double dtot = fixed_sum(a.part + (long long)src * a.nslots, a.nslots, sh);
-    const double atot = fixed_sum(a.part2 + (long long)src * a.nslots, a.G.ntiles + a.nbblocks, sh);
+    const double dtot = fixed_sum(a.part + (long long)src * a.nslots, a.G.ncols + a.nbblocks, sh);
+    const double atot = fixed_sum(a.part2 + (long long)src * a.nslots, a.G.ncols + a.nbblocks, sh);
     if (threadIdx.x == 0) finish_iteration(a, src, dtot / (atot > 1e-300 ? atot : 1e-300));
 }
 
@@ -1123,6 +1294,7 @@ __global__ void __launch_bounds__(256) k_cadj_coef(SweepArgs a, const double* __
 // from the values present before the pass, into tmp [nsrc][NB] ...
 __global__ void __launch_bounds__(kBndThreads) k_cadj_bnd_calc(SweepArgs a, double* __restrict__ tmp_all) {
     const int src = blockIdx.y;
+    if (blockIdx.x == 0) queue_reset(a, src);
     if (!a.active[src]) return;
     const Geo& G = a.G;
     const long long b = (long long)blockIdx.x * kBndThreads + threadIdx.x;
@@ -1170,8 +1342,8 @@ __global__ void __launch_bounds__(kBndThreads) k_cadj_bnd_store(SweepArgs a, con
     d = block_sum256(d, sh);
     const double as = (dir == 7) ? block_sum256(av, sh) : 0.0;
     if (threadIdx.x == 0) {
-        a.part[(long long)src * a.nslots + 8 * G.ntiles + dir * a.nbblocks + blockIdx.x] = d;
-        if (dir == 7) a.part2[(long long)src * a.nslots + G.ntiles + blockIdx.x] = as;
+        part_add(a.part + (long long)src * a.nslots + G.ncols + blockIdx.x, dir, d);
+        if (dir == 7) a.part2[(long long)src * a.nslots + G.ncols + blockIdx.x] = as;
     }
 }
 
@@ -1307,7 +1479,18 @@ void launch_fwd_init(const Plan& P, const SweepArgs& a, const double* tau_init, 
 
 static size_t tile_lds_bytes(const Geo& G) { return (size_t)stage_bytes(G.tk); }
 
-// Event pair around the tile-plane launches of one directional sweep when
+// Workgroups (one wave each) of a sweep launch over cn sources: as many as the
+// chip's LDS holds, but no more than there are tile columns on each XCD.
+static unsigned march_blocks(const Plan& P, int cn) {
+    const long long fit = 256LL * std::min<long long>(16, 163840 / (long long)tile_lds_bytes(P.G));
+    const int nb = std::min(kMarchBatches, cn);
+    const long long want = (long long)kMarchBatches * ((cn + nb - 1) / nb) * P.G.ncols;
+    return (unsigned)std::min(fit, want);
+}
+
+static int march_launches(const Plan& P) { return (P.nsrc + kMarchSources - 1) / kMarchSources; }
+
+// Event pair around the launches of one directional sweep when
 // timing is on; the launch count of the group is recorded with it.
 struct TimedLaunch {
     const Plan& P;
@@ -1370,6 +1553,7 @@ SweepFn adj_sweep_fn_c(int tk, int d, bool compact) {
     const auto seq = std::make_integer_sequence<int, 8>{};
     if (compact) return pick_adj<COORD, true, 0>(d, seq);
     switch (tk) {
+        case 16: return pick_adj<COORD, false, 16>(d, seq);
         case 28: return pick_adj<COORD, false, 28>(d, seq);
         case 32: return pick_adj<COORD, false, 32>(d, seq);
         case 40: return pick_adj<COORD, false, 40>(d, seq);
@@ -1385,11 +1569,12 @@ SweepFn adj_sweep_fn(int coord, int tk, int d, bool compact) {
 void launch_fwd_iteration(const Plan& P, const SweepArgs& a, hipStream_t st) {
     for (int d = 0; d < 8; ++d) {
         {
-        TimedLaunch tl(P, st, P.nplanes);
+        TimedLaunch tl(P, st, march_launches(P));
         const SweepFn fn = fwd_sweep_fn(P.G.coord, P.G.tk, d);
-        for (int p = 0; p < P.nplanes; ++p)
-            hipLaunchKernelGGL(fn, dim3(P.nsrc, P.plane_count[p]), dim3(64), tile_lds_bytes(P.G), st, a,
-                               P.plane_id[p], P.plane_s0[p]);
+        for (int c0 = 0; c0 < P.nsrc; c0 += kMarchSources) {
+            const int cn = std::min(kMarchSources, P.nsrc - c0);
+            hipLaunchKernelGGL(fn, dim3(march_blocks(P, cn)), dim3(64), tile_lds_bytes(P.G), st, a, c0, cn);
+        }
         }
         hipLaunchKernelGGL(k_fwd_bnd, dim3(P.nbblocks, P.nsrc), dim3(kBndThreads), 0, st, a, d);
     }
@@ -1418,11 +1603,12 @@ void launch_adj_init(const Plan& P, const SweepArgs& a, const double* tau, int n
 void launch_adj_iteration(const Plan& P, const SweepArgs& a, hipStream_t st) {
     for (int d = 0; d < 8; ++d) {
         {
-        TimedLaunch tl(P, st, P.nplanes);
+        TimedLaunch tl(P, st, march_launches(P));
         const SweepFn fn = adj_sweep_fn(P.G.coord, P.G.tk, d, P.compact);
-        for (int p = 0; p < P.nplanes; ++p)
-            hipLaunchKernelGGL(fn, dim3(P.nsrc, P.plane_count[p]), dim3(64), tile_lds_bytes(P.G), st, a,
-                               P.plane_id[p], P.plane_s0[p]);
+        for (int c0 = 0; c0 < P.nsrc; c0 += kMarchSources) {
+            const int cn = std::min(kMarchSources, P.nsrc - c0);
+            hipLaunchKernelGGL(fn, dim3(march_blocks(P, cn)), dim3(64), tile_lds_bytes(P.G), st, a, c0, cn);
+        }
         }
         if (P.continuous) {
             hipLaunchKernelGGL(k_cadj_bnd_calc, dim3(P.nbblocks, P.nsrc), dim3(kBndThreads), 0, st, a, P.bnd_in);
