@@ -257,12 +257,282 @@ __global__ __launch_bounds__(256) void k_conv3_wgrad(const uint16_t* __restrict_
         }
 }
 
-// out[j] = sum over slices (in order) of part[slice][j]
-__global__ void k_sum_slices(const float* __restrict__ part, long long nslices, long long n, float* __restrict__ out) {
-    for (long long j = blockIdx.x * (long long)blockDim.x + threadIdx.x; j < n; j += (long long)gridDim.x * blockDim.x) {
-        float s = 0.0f;
-        for (long long q = 0; q < nslices; ++q) s += part[q * n + j];
-        out[j] = s;
+// ------------------------------------------- wgrad from LDS-staged rows
+// The same sums with the rows staged once for all taps.  K = 32 positions of a
+// row per v_mfma_f32_16x16x32_bf16; both operands need, per lane, one channel of
+// 8 consecutive positions, i.e. columns of the channels-last rows:
+// ds_read_tr16_b64 reads them transposed (16 lanes name the 8-byte pieces of a
+// 4-position x 16-channel block, lane li gets its column li), so a tap's shift
+// dx is a row offset.  The 9 input rows around a gradient row stay in LDS while
+// y advances (3 new rows and the gradient row a step, fetched to registers while
+// the matrix cores work on the step before); the taps are dealt to the 4 waves,
+// the 28th "tap" (wave 3) has ones for its input and so sums the gradient: the
+// bias gradient.
+// Bound by LDS reads (a 1 KB operand per matrix instruction at one output
+// block).  The per-tap kernel above re-reads x 27 times in 2-byte pieces: the 14
+// weight gradients of an 8 x 56^3 pass took 13.1 ms there (and their bias sums
+// 3.4 ms), 0.94 ms here; the 32 -> 16 one 167 us.
+typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
+typedef short s8_t __attribute__((ext_vector_type(8)));
+typedef __attribute__((address_space(3))) s4_t lds_s4_t;
+typedef uint32_t u4_t __attribute__((ext_vector_type(4)));
+
+// operand of 32 positions: rows 8g..8g+7 of the 16-channel block at p (32-byte
+// rows `step` rows apart), column li; p already holds this lane's piece
+__device__ __forceinline__ bf8_t tr_frag(const uint16_t* p, int step) {
+    const s4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4_t*)p);
+    const s4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4_t*)(p + 64 * step));
+    return __builtin_bit_cast(bf8_t, s8_t{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w});
+}
+
+constexpr int kWgX = 64;  // positions of a row chunk
+
+// IB x OB: the 16-channel blocks of this workgroup (blockIdx.y: which of them)
+template <int IB, int OB>
+__global__ __launch_bounds__(256) void k_conv3_wgrad_rows(const uint16_t* __restrict__ x, int D, int H, int W,
+                                                          long long nrows, int cxt, int cxo, int cin,
+                                                          const uint16_t* __restrict__ gz, int cgt, int cgo, int cout,
+                                                          long long rows_per_slice, int nob, float* __restrict__ part,
+                                                          float* __restrict__ bpart) {
+    constexpr int XR = kWgX + 2;          // staged positions of an input row
+    constexpr int NX = XR * IB * 2;       // 16-byte pieces of an input row
+    constexpr int NG = kWgX * OB * 2;     // ... of a gradient row
+    constexpr int NL = (3 * NX + NG + 255) / 256;
+    __shared__ __align__(16) uint16_t xs[9][IB][XR][16];
+    __shared__ __align__(16) uint16_t gs[OB][kWgX][16];
+    const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, li = lane & 15, g = lane >> 4;
+    const int ib0 = ((int)blockIdx.y / nob) * IB, ob0 = ((int)blockIdx.y % nob) * OB;
+    const uint16_t* xb = x + cxo + ib0 * 16;
+    const uint16_t* gb = gz + cgo + ob0 * 16;
+    f4_t acc[7][IB][OB];
+#pragma unroll
+    for (int j = 0; j < 7; ++j)
+#pragma unroll
+        for (int a = 0; a < IB; ++a)
+#pragma unroll
+            for (int b = 0; b < OB; ++b) acc[j][a][b] = f4_t{0.f, 0.f, 0.f, 0.f};
+    const long long r0 = (long long)blockIdx.x * rows_per_slice;
+    const long long r1 = r0 + rows_per_slice < nrows ? r0 + rows_per_slice : nrows;
+    const bf8_t ones = __builtin_bit_cast(bf8_t, s8_t{0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80});
+
+    // piece q of input row (zz, yy) of sample row base, chunk x0: position q / (2 IB), then block and half
+    auto ldx = [&](long long row, bool ok, int q, int x0) -> u4_t {
+        const int pos = q / (2 * IB), xx = x0 + pos - 1;
+        if (!ok || (unsigned)xx >= (unsigned)W) return u4_t{0, 0, 0, 0};
+        return *reinterpret_cast<const u4_t*>(xb + (row * W + xx) * cxt + (q % (2 * IB)) * 8);
+    };
+    auto stx = [&](int slot, int q, u4_t v) {
+        const int pos = q / (2 * IB), c = q % (2 * IB);
+        *reinterpret_cast<u4_t*>(&xs[slot][c >> 1][pos][(c & 1) * 8]) = v;
+    };
+    for (int x0 = 0; x0 < W; x0 += kWgX) {
+        const int nk = W - x0 > 32 ? 2 : 1;
+        u4_t pre[NL];
+        // what row r adds to the staged rows: input rows (z + dz, y + 1) and the gradient row
+        auto fetch = [&](long long r) {
+            const int yy = (int)(r % H), zz = (int)((r / H) % D);
+#pragma unroll
+            for (int j = 0; j < NL; ++j) {
+                const int e = tid + 256 * j;
+                if (e < 3 * NX) {
+                    const int dz = e / NX - 1;
+                    pre[j] = ldx(r + (long long)dz * H + 1, (unsigned)(zz + dz) < (unsigned)D && yy + 1 < H, e % NX, x0);
+                } else if (e < 3 * NX + NG) {
+                    const int q = e - 3 * NX, pos = q / (2 * OB);
+                    pre[j] = x0 + pos < W ? *reinterpret_cast<const u4_t*>(gb + (r * W + x0 + pos) * cgt + (q % (2 * OB)) * 8)
+                                          : u4_t{0, 0, 0, 0};
+                }
+            }
+        };
+        fetch(r0);
+        for (long long r = r0; r < r1; ++r) {
+            const int yy = (int)(r % H), zz = (int)((r / H) % D);
+            // ring slot of input row y + dy: 3 ((y + dy + 3) % 3) + (dz + 1)
+            if (r == r0 || yy == 0) {  // rows y - 1 and y are not there yet
+                for (int e = tid; e < 6 * NX; e += 256) {
+                    const int w = e / NX, dz = w % 3 - 1, dy = w / 3 - 1;
+                    const bool ok = (unsigned)(zz + dz) < (unsigned)D && yy + dy >= 0;
+                    stx(3 * ((yy + dy + 3) % 3) + dz + 1, e % NX, ldx(r + (long long)dz * H + dy, ok, e % NX, x0));
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < NL; ++j) {
+                const int e = tid + 256 * j;
+                if (e < 3 * NX) {
+                    stx(3 * ((yy + 1) % 3) + e / NX, e % NX, pre[j]);
+                } else if (e < 3 * NX + NG) {
+                    const int q = e - 3 * NX, c = q % (2 * OB);
+                    *reinterpret_cast<u4_t*>(&gs[c >> 1][q / (2 * OB)][(c & 1) * 8]) = pre[j];
+                }
+            }
+            __syncthreads();
+            if (r + 1 < r1) fetch(r + 1);
+            for (int kb = 0; kb < nk; ++kb) {
+                const int lrow = kb * 32 + 8 * g + (li >> 2), lch = 4 * (li & 3);
+                bf8_t bfr[OB];
+#pragma unroll
+                for (int b = 0; b < OB; ++b) bfr[b] = tr_frag(&gs[b][lrow][lch], 1);
+#pragma unroll
+                for (int j = 0; j < 7; ++j) {
+                    const int t = wv + 4 * j;
+                    const int dz = t / 9, dy = (t / 3) % 3 - 1, dx = t % 3;
+                    const int slot = t < 27 ? 3 * ((yy + dy + 3) % 3) + dz : 0;
+#pragma unroll
+                    for (int a = 0; a < IB; ++a) {
+                        bf8_t af = tr_frag(&xs[slot][a][lrow + (t < 27 ? dx : 0)][lch], 1);
+                        if (t == 27) af = ones;
+#pragma unroll
+                        for (int b = 0; b < OB; ++b)
+                            acc[j][a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bfr[b], acc[j][a][b], 0, 0, 0);
+                    }
+                }
+            }
+            __syncthreads();
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 7; ++j) {
+        const int t = wv + 4 * j;
+#pragma unroll
+        for (int a = 0; a < IB; ++a)
+#pragma unroll
+            for (int b = 0; b < OB; ++b) {
+                const int o = (ob0 + b) * 16 + li;
+                if (t == 27) {
+                    if (bpart && ib0 == 0 && a == 0 && g == 0) bpart[(long long)blockIdx.x * cout + o] = acc[j][a][b][0];
+                    continue;
+                }
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int i = (ib0 + a) * 16 + 4 * g + r;
+                    if (i < cin) part[(((long long)blockIdx.x * 27 + t) * cin + i) * cout + o] = acc[j][a][b][r];
+                }
+            }
+    }
+}
+
+// The same for the transposed up-sampling: per coarse row, the 4 child rows of
+// the gradient; wave w = 2a + b holds the children (a, b, 0) and (a, b, 1),
+// whose positions are every other row of the staged gradient.  bpart holds one
+// partial bias sum per slice and wave.  (The three of an 8 x 56^3 pass: 3.0 ms
+// as one thread per channel pair over its positions, 0.04 ms here.)
+template <int IB, int OB>
+__global__ __launch_bounds__(256) void k_up_wgrad_rows(const uint16_t* __restrict__ x, const uint16_t* __restrict__ gy,
+                                                       int D, int H, int W, long long nrows, int cin, int cout, int cgt,
+                                                       int cgo, long long rows_per_slice, int nob,
+                                                       float* __restrict__ part, float* __restrict__ bpart) {
+    constexpr int NX = kWgX * IB * 2, NG = 2 * kWgX * OB * 2;
+    constexpr int NL = (NX + 4 * NG + 255) / 256;
+    __shared__ __align__(16) uint16_t xs[IB][kWgX][16];
+    __shared__ __align__(16) uint16_t gs[4][OB][2 * kWgX][16];
+    const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, li = lane & 15, g = lane >> 4;
+    const int ib0 = ((int)blockIdx.y / nob) * IB, ob0 = ((int)blockIdx.y % nob) * OB;
+    const uint16_t* xb = x + ib0 * 16;
+    const uint16_t* gb = gy + cgo + ob0 * 16;
+    f4_t acc[2][IB][OB], accb[OB];
+#pragma unroll
+    for (int b = 0; b < OB; ++b) {
+        accb[b] = f4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int a = 0; a < IB; ++a) acc[c][a][b] = f4_t{0.f, 0.f, 0.f, 0.f};
+    }
+    const bf8_t ones = __builtin_bit_cast(bf8_t, s8_t{0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80});
+    const long long r0 = (long long)blockIdx.x * rows_per_slice;
+    const long long r1 = r0 + rows_per_slice < nrows ? r0 + rows_per_slice : nrows;
+    for (int x0 = 0; x0 < W; x0 += kWgX) {
+        const int nk = W - x0 > 32 ? 2 : 1;
+        u4_t pre[NL];
+        auto fetch = [&](long long r) {
+            const long long nz = r / H;  // n D + z
+            const int yy = (int)(r % H);
+#pragma unroll
+            for (int j = 0; j < NL; ++j) {
+                const int e = tid + 256 * j;
+                pre[j] = u4_t{0, 0, 0, 0};
+                if (e < NX) {
+                    const int pos = e / (2 * IB);
+                    if (x0 + pos < W) pre[j] = *reinterpret_cast<const u4_t*>(xb + (r * W + x0 + pos) * cin + (e % (2 * IB)) * 8);
+                } else if (e < NX + 4 * NG) {
+                    const int w = (e - NX) / NG, q = (e - NX) % NG, pos = q / (2 * OB);
+                    // fine row ((n 2D + 2z + a) 2H + 2y + b) = (2 nz + a) 2H + 2y + b
+                    const long long fr = (2 * nz + (w >> 1)) * 2 * H + 2 * yy + (w & 1);
+                    if (2 * x0 + pos < 2 * W)
+                        pre[j] = *reinterpret_cast<const u4_t*>(gb + (fr * 2 * W + 2 * x0 + pos) * cgt + (q % (2 * OB)) * 8);
+                }
+            }
+        };
+        fetch(r0);
+        for (long long r = r0; r < r1; ++r) {
+#pragma unroll
+            for (int j = 0; j < NL; ++j) {
+                const int e = tid + 256 * j;
+                if (e < NX) {
+                    const int c = e % (2 * IB);
+                    *reinterpret_cast<u4_t*>(&xs[c >> 1][e / (2 * IB)][(c & 1) * 8]) = pre[j];
+                } else if (e < NX + 4 * NG) {
+                    const int w = (e - NX) / NG, q = (e - NX) % NG, c = q % (2 * OB);
+                    *reinterpret_cast<u4_t*>(&gs[w][c >> 1][q / (2 * OB)][(c & 1) * 8]) = pre[j];
+                }
+            }
+            __syncthreads();
+            if (r + 1 < r1) fetch(r + 1);
+            for (int kb = 0; kb < nk; ++kb) {
+                const int lrow = kb * 32 + 8 * g + (li >> 2), lch = 4 * (li & 3);
+                bf8_t af[IB];
+#pragma unroll
+                for (int a = 0; a < IB; ++a) af[a] = tr_frag(&xs[a][lrow][lch], 1);
+#pragma unroll
+                for (int c = 0; c < 2; ++c)
+#pragma unroll
+                    for (int b = 0; b < OB; ++b) {
+                        const bf8_t bfr = tr_frag(&gs[wv][b][2 * lrow + c][lch], 2);
+                        accb[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, bfr, accb[b], 0, 0, 0);
+#pragma unroll
+                        for (int a = 0; a < IB; ++a)
+                            acc[c][a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[a], bfr, acc[c][a][b], 0, 0, 0);
+                    }
+            }
+            __syncthreads();
+        }
+    }
+#pragma unroll
+    for (int b = 0; b < OB; ++b) {
+        const int o = (ob0 + b) * 16 + li;
+        if (ib0 == 0 && g == 0) bpart[((long long)blockIdx.x * 4 + wv) * cout + o] = accb[b][0];
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int a = 0; a < IB; ++a)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    part[(((long long)blockIdx.x * 8 + 2 * wv + c) * cin + (ib0 + a) * 16 + 4 * g + r) * cout + o] = acc[c][a][b][r];
+    }
+}
+
+// out[j] = sum over slices of part[slice][j]: 16 groups of slices per output in
+// a block (slice q in group q % 16, ascending), combined in order.  A chain of
+// slices per output and thread, as a grid of one thread per output has it, took
+// 26 us at 128 slices whatever the width.
+constexpr int kSumCols = 64, kSumGroups = 16;
+__global__ __launch_bounds__(kSumCols * kSumGroups) void k_sum_slices(const float* __restrict__ part, long long nslices,
+                                                                      long long n, float* __restrict__ out) {
+    __shared__ float red[kSumGroups][kSumCols];
+    const int c = threadIdx.x % kSumCols, grp = threadIdx.x / kSumCols;
+    const long long j = (long long)blockIdx.x * kSumCols + c;
+    float s = 0.0f;
+    if (j < n) {
+#pragma unroll 4
+        for (long long q = grp; q < nslices; q += kSumGroups) s += part[q * n + j];
+    }
+    red[grp][c] = s;
+    __syncthreads();
+    if (grp == 0 && j < n) {
+        float t = red[0][c];
+#pragma unroll
+        for (int q = 1; q < kSumGroups; ++q) t += red[q][c];
+        out[j] = t;
     }
 }
 
@@ -680,13 +950,27 @@ int conv3_fwd(const uint16_t* x, int nbatch, int D, int H, int W, int cxt, int c
     return TT_OK;
 }
 
+// 512 slices give every CU two workgroups; a slice of fewer than 8 rows would
+// stage more halo rows than it works on
 long long wgrad_slices(long long nrows) {
     long long s = (nrows + 7) / 8;
-    return s < 1 ? 1 : (s > 128 ? 128 : s);
+    return s < 1 ? 1 : (s > 512 ? 512 : s);
 }
 
+// partial weight gradients, then partial bias gradients, of every slice
 size_t conv3_wgrad_floats(long long nrows, int cin, int cout) {
-    return (size_t)wgrad_slices(nrows) * 27 * cin * cout;
+    return (size_t)wgrad_slices(nrows) * (27 * (size_t)cin * cout + cout);
+}
+
+int sum_slices(const float* part, long long ns, long long n, float* out, hipStream_t st) {
+    hipLaunchKernelGGL(k_sum_slices, dim3(blocks_of(n, kSumCols)), dim3(kSumCols * kSumGroups), 0, st, part, ns, n, out);
+    NN_LAUNCHED();
+    return TT_OK;
+}
+
+// channel ranges that can be read in aligned 16-byte pieces
+bool pieces16(const uint16_t* p, int ct, int co) {
+    return reinterpret_cast<uintptr_t>(p) % 16 == 0 && ct % 8 == 0 && co % 8 == 0;
 }
 
 long long colsum_blocks(long long npos) {
@@ -699,9 +983,7 @@ int colsum(const uint16_t* g, long long npos, int ct, int co, int c, float* out,
     const long long chunk = (npos + nb - 1) / nb;
     hipLaunchKernelGGL(k_colsum_part, dim3((unsigned)nb), dim3(256), 0, st, g, npos, ct, co, c, chunk, work);
     NN_LAUNCHED();
-    hipLaunchKernelGGL(k_sum_slices, dim3(blocks_of(c, 64)), dim3(64), 0, st, work, nb, (long long)c, out);
-    NN_LAUNCHED();
-    return TT_OK;
+    return sum_slices(work, nb, c, out, st);
 }
 
 int conv3_wgrad(const uint16_t* x, int nbatch, int D, int H, int W, int cxt, int cxo, int cin, const uint16_t* gz,
@@ -709,12 +991,34 @@ int conv3_wgrad(const uint16_t* x, int nbatch, int D, int H, int W, int cxt, int
     const long long nrows = (long long)nbatch * D * H;
     const long long ns = wgrad_slices(nrows);
     const long long rps = (nrows + ns - 1) / ns;
+    const long long n = 27LL * cin * cout;
+    const int nib = (cin + 15) / 16, nob = cout / 16;
+    // staged rows take whole 16-byte pieces of whole 16-channel blocks (the last
+    // block's channels past cin are read and dropped); other layouts go per tap
+    if (pieces16(x, cxt, cxo) && pieces16(gz, cgt, cgo) && cxo + nib * 16 <= cxt) {
+        float* bpart = gb ? work + ns * n : nullptr;
+        const int ib = nib % 2 == 0 ? 2 : 1, ob = nob % 2 == 0 ? 2 : 1;
+        const dim3 grid((unsigned)ns, (unsigned)((nib / ib) * (nob / ob)));
+#define NN_WG(A, B)                                                                                                   \
+    hipLaunchKernelGGL((k_conv3_wgrad_rows<A, B>), grid, dim3(256), 0, st, x, D, H, W, nrows, cxt, cxo, cin, gz, cgt, cgo, \
+                       cout, rps, nob / B, work, bpart)
+        if (ib == 2 && ob == 2) NN_WG(2, 2);
+        else if (ib == 2) NN_WG(2, 1);
+        else if (ob == 2) NN_WG(1, 2);
+        else NN_WG(1, 1);
+#undef NN_WG
+        NN_LAUNCHED();
+        if (gb) {
+            const int rc = sum_slices(bpart, ns, cout, gb, st);
+            if (rc) return rc;
+        }
+        return sum_slices(work, ns, n, gW, st);
+    }
     hipLaunchKernelGGL(k_conv3_wgrad, dim3((unsigned)ns, 27), dim3(256), 0, st, x, D, H, W, nrows, cxt, cxo, cin, gz,
                        cgt, cgo, cout, rps, work);
     NN_LAUNCHED();
-    const long long n = 27LL * cin * cout;
-    hipLaunchKernelGGL(k_sum_slices, dim3(grid_stride_blocks(n)), dim3(256), 0, st, work, ns, n, gW);
-    NN_LAUNCHED();
+    const int rc = sum_slices(work, ns, n, gW, st);
+    if (rc) return rc;
     if (gb) return colsum(gz, nrows * W, cgt, cgo, cout, gb, work, st);
     return TT_OK;
 }
@@ -726,10 +1030,16 @@ long long up_slices(long long np) {
     return s < 1 ? 1 : (s > 256 ? 256 : s);
 }
 
-size_t up_work_floats(long long np, int cin, int cout) {
+long long up_row_slices(long long nrows) {
+    long long s = (nrows + 3) / 4;
+    return s < 1 ? 1 : (s > 512 ? 512 : s);
+}
+
+size_t up_work_floats(long long np, long long nrows, int cin, int cout) {
     const size_t a = (size_t)up_slices(np) * 8 * cin * cout;
     const size_t b = colsum_floats(np * 8, cout);
-    return a > b ? a : b;
+    const size_t c = (size_t)up_row_slices(nrows) * (8 * (size_t)cin * cout + 4 * (size_t)cout);
+    return a > b ? (a > c ? a : c) : (b > c ? b : c);
 }
 
 int up_bwd(const uint16_t* x, const uint16_t* gy, int nbatch, int D, int H, int W, int cin, int cout, int cgt, int cgo,
@@ -740,14 +1050,32 @@ int up_bwd(const uint16_t* x, const uint16_t* gy, int nbatch, int D, int H, int 
                            cout, cgt, cgo, Wu, gx);
         NN_LAUNCHED();
     }
+    if (cin % 16 == 0 && cout % 16 == 0 && pieces16(x, cin, 0) && pieces16(gy, cgt, cgo)) {
+        const long long nrows = (long long)nbatch * D * H;
+        const long long ns = up_row_slices(nrows), rps = (nrows + ns - 1) / ns, n = 8LL * cin * cout;
+        float* bpart = work + ns * n;
+        const int nib = cin / 16, nob = cout / 16, ib = nib % 2 == 0 ? 2 : 1, ob = nob % 2 == 0 ? 2 : 1;
+        const dim3 grid((unsigned)ns, (unsigned)((nib / ib) * (nob / ob)));
+#define NN_WG(A, B)                                                                                                \
+    hipLaunchKernelGGL((k_up_wgrad_rows<A, B>), grid, dim3(256), 0, st, x, gy, D, H, W, nrows, cin, cout, cgt, cgo, rps, \
+                       nob / B, work, bpart)
+        if (ib == 2 && ob == 2) NN_WG(2, 2);
+        else if (ib == 2) NN_WG(2, 1);
+        else if (ob == 2) NN_WG(1, 2);
+        else NN_WG(1, 1);
+#undef NN_WG
+        NN_LAUNCHED();
+        const int rc = sum_slices(work, ns, n, gW, st);
+        return rc ? rc : sum_slices(bpart, 4 * ns, cout, gb, st);
+    }
     const long long ns = up_slices(np);
     const long long chunk = (np + ns - 1) / ns;
     hipLaunchKernelGGL(k_up_wgrad_part, dim3((unsigned)ns, 8), dim3(256), 0, st, x, gy, np, D, H, W, cin, cout, cgt,
                        cgo, chunk, work);
     NN_LAUNCHED();
     const long long n = 8LL * cin * cout;
-    hipLaunchKernelGGL(k_sum_slices, dim3(grid_stride_blocks(n)), dim3(256), 0, st, work, ns, n, gW);
-    NN_LAUNCHED();
+    const int rc = sum_slices(work, ns, n, gW, st);
+    if (rc) return rc;
     return colsum(gy, np * 8, cgt, cgo, cout, gb, work, st);
 }
 
@@ -912,7 +1240,8 @@ void layout(const Net& N, int nbatch, int D, int H, int W, int train, char* base
             if (g > wf) wf = g;
         }
         for (int k = 0; k < NUP; ++k) {
-            const size_t f = up_work_floats(A.P[3 - k], N.up[k].ci, N.up[k].co);
+            const long long np = A.P[3 - k];
+            const size_t f = up_work_floats(np, np / (W >> (3 - k)), N.up[k].ci, N.up[k].co);
             if (f > wf) wf = f;
         }
         const size_t hf = head_work_floats(A.P[0], c1);
@@ -1210,7 +1539,7 @@ int nn_up_fwd(const uint16_t* x, int nbatch, int D, int H, int W, int cin, const
 
 size_t nn_up_wgrad_work(int nbatch, int D, int H, int W, int cin, int cout) {
     if (nbatch < 1 || D < 1 || H < 1 || W < 1 || cin < 1 || cout < 1) return 0;
-    return up_work_floats((long long)nbatch * D * H * W, cin, cout) * sizeof(float);
+    return up_work_floats((long long)nbatch * D * H * W, (long long)nbatch * D * H, cin, cout) * sizeof(float);
 }
 
 int nn_up_bwd(const uint16_t* x, const uint16_t* gy, int nbatch, int D, int H, int W, int cin, int cout, int cg_total,
