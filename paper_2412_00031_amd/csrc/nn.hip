@@ -165,6 +165,180 @@ __global__ __launch_bounds__(256) void k_conv3_fwd(const uint16_t* __restrict__ 
         }
 }
 
+// ------------------------------------------- conv forward from LDS planes
+// The same convolution, bit for bit, with the input staged: a workgroup of 4
+// waves takes R rows of a plane (R W <= 64 MB positions) and marches along z
+// with three planes of R + 2 rows in LDS, zero-padded, so that a tap is an
+// address offset without masks; plane z + 2 is fetched to registers while the
+// matrix cores work on plane z.  Products are v_mfma_f32_16x16x32_bf16, which
+// adds 32 terms in the order of two 16x16x16 ones (checked bit for bit), at
+// twice their rate: the 27 KB 16-channel steps of the kernel above are taken in
+// pairs, in its order; a lone last step is paired with zeros.  The weights are the
+// row operand, so a lane ends with 4 consecutive channels of one position (one
+// 8-byte store).  Weights stay in registers over the march when they fit.
+// 32 x 56^3:
+// 16 -> 16 from 781 to 214 us (its bytes take 80), 32 -> 16 432; the 14 convolutions
+// of a prediction from 5.4 to 1.73 ms.  Bound by the step from plane to plane: fetch,
+// store, barrier, 98 products of 18 cycles a wave.
+typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
+typedef short s8_t __attribute__((ext_vector_type(8)));
+typedef uint32_t u4_t __attribute__((ext_vector_type(4)));
+
+constexpr int kCvPieces = 8;  // 16-byte pieces a thread fetches per plane at most
+
+__host__ __device__ constexpr int cv_pixel(int KB) { return KB == 4 ? 72 : 16 * KB; }  // elements (64 channels: padded against bank conflicts)
+
+template <int KB, int NB, int MB>
+__global__ __launch_bounds__(256, 2) void k_conv3_planes(const uint16_t* __restrict__ x, int D, int H, int W, int cxt,
+                                                         int cxo, const uint16_t* __restrict__ frag,
+                                                         const float* __restrict__ bias, int relu,
+                                                         uint16_t* __restrict__ y, int cyt, int cyo, int R, int ntile,
+                                                         int zc) {
+    constexpr int PS = cv_pixel(KB);
+    extern __shared__ __align__(16) uint16_t xs[];  // [3][R + 2][W + 2][PS]
+    const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, li = lane & 15, g = lane >> 4;
+    const int tile = blockIdx.x % ntile, n = blockIdx.x / ntile;
+    const int y0 = tile * R, z0 = blockIdx.y * zc, z1 = min(D, z0 + zc);
+    const int rows = R + 2, pw = W + 2, plane = rows * pw * PS;
+    for (int e = tid; e < 3 * plane / 8; e += 256) reinterpret_cast<u4_t*>(xs)[e] = u4_t{0, 0, 0, 0};
+
+    // this lane's piece of the weights of 16-channel steps st, st + 1 (zeros past the last), block nb: k = 8g .. 8g + 7
+    auto wfrag = [&](int st, int nb) -> bf8_t {
+        const int s1 = st + (g >> 1);
+        s4_t lo = {0, 0, 0, 0}, hi = {0, 0, 0, 0};
+        if (s1 < 27 * KB) {
+            const s4_t* f = reinterpret_cast<const s4_t*>(frag) + (s1 * NB + nb) * 64 + 32 * (g & 1) + li;
+            lo = f[0];
+            hi = f[16];
+        }
+        return __builtin_bit_cast(bf8_t, s8_t{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w});
+    };
+    // positions of this wave's blocks wv, wv + 4, ...: LDS offset of the lane's 8
+    // terms (8g of 32 channels, or 8 (g & 1) of one tap's 16) and index in the plane
+    const int npos = min(R, H - y0) * W, nblk = (npos + 15) / 16;
+    int base[MB], pos[MB];
+#pragma unroll
+    for (int j = 0; j < MB; ++j) {
+        const int q = (wv + 4 * j) * 16 + li, qc = min(q, npos - 1);
+        const int yy = qc / W, xx = qc - yy * W;
+        base[j] = (yy * pw + xx) * PS + (KB == 1 ? 8 * (g & 1) : 8 * g);
+        pos[j] = q < npos ? (y0 + yy) * W + xx : -1;
+    }
+    // pieces this thread fetches: element offset in a plane of x (-1: none) and LDS offset in a staged plane
+    int go[kCvPieces], lo[kCvPieces];
+#pragma unroll
+    for (int j = 0; j < kCvPieces; ++j) {
+        const int e = tid + 256 * j, rowp = 2 * KB * W, r = e / rowp, q = e - r * rowp, yy = y0 + r - 1;
+        go[j] = r < rows && (unsigned)yy < (unsigned)H ? (yy * W + q / (2 * KB)) * cxt + (q % (2 * KB)) * 8 : -1;
+        lo[j] = (r * pw + q / (2 * KB) + 1) * PS + (q % (2 * KB)) * 8;
+    }
+    const long long hw = (long long)H * W;
+    u4_t pre[kCvPieces];
+    auto fetch = [&](int z) {
+        const uint16_t* xz = x + ((long long)n * D + z) * hw * cxt + cxo;
+        const bool zok = (unsigned)z < (unsigned)D;
+#pragma unroll
+        for (int j = 0; j < kCvPieces; ++j) {
+            pre[j] = u4_t{0, 0, 0, 0};
+            if (zok && go[j] >= 0) pre[j] = *reinterpret_cast<const u4_t*>(xz + go[j]);
+        }
+    };
+    auto put = [&](int z) {
+        uint16_t* d = xs + (z + 3) % 3 * plane;
+#pragma unroll
+        for (int j = 0; j < kCvPieces; ++j)
+            if (go[j] >= 0) *reinterpret_cast<u4_t*>(d + lo[j]) = pre[j];
+    };
+    constexpr int NP = (27 * KB + 1) / 2;            // pairs of steps
+    constexpr bool RES = KB <= 2 && NB == 1;  // all weights in 56 or 108 registers
+    bf8_t wr[RES ? NP : 1][NB];
+    if (RES) {
+#pragma unroll
+        for (int m = 0; m < NP; ++m) wr[m][0] = wfrag(2 * m, 0);
+    }
+    __syncthreads();
+    fetch(z0 - 1);
+    put(z0 - 1);
+    fetch(z0);
+    put(z0);
+    fetch(z0 + 1);
+    for (int z = z0; z < z1; ++z) {
+        put(z + 1);
+        __syncthreads();
+        if (z + 1 < z1) fetch(z + 2);
+        f4_t acc[MB][NB];
+#pragma unroll
+        for (int j = 0; j < MB; ++j)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) acc[j][nb] = f4_t{0.f, 0.f, 0.f, 0.f};
+        auto mac = [&](const bf8_t (&w)[NB], int off, bool half) {
+#pragma unroll
+            for (int j = 0; j < MB; ++j) {
+                if (wv + 4 * j < nblk) {
+                    u4_t v = *reinterpret_cast<const u4_t*>(xs + base[j] + off);
+                    if (half) v = g < 2 ? v : u4_t{0, 0, 0, 0};
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb)
+                        acc[j][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[nb], __builtin_bit_cast(bf8_t, v), acc[j][nb], 0, 0, 0);
+                }
+            }
+        };
+        // LDS offset of tap t: plane z + t / 9 - 1, row and column shifts t / 3 % 3, t % 3
+        auto tap = [&](int t) { return (z + t / 9 + 2) % 3 * plane + (t / 3 % 3 * pw + t % 3) * PS; };
+        // pair m: steps 2m, 2m + 1, i.e. 32 channels of a tap or 16 channels of two taps (the last one alone)
+        auto pair_off = [&](int m) {
+            if (KB > 1) return tap(2 * m / KB) + 2 * m % KB * 16;
+            const int oa = tap(2 * m), ob = tap(min(2 * m + 1, 26));
+            return g < 2 ? oa : ob;
+        };
+        if constexpr (RES) {
+#pragma unroll
+            for (int m = 0; m < NP; ++m) mac(wr[m], pair_off(m), KB == 1 && m == NP - 1);
+        } else {
+            // weights are fetched three pairs ahead (from L2: 600 cycles; a pair's products take 36 to 290)
+            bf8_t w[4][NB];
+            auto get = [&](int m) {
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) w[m & 3][nb] = wfrag(2 * m, nb);
+            };
+#pragma unroll
+            for (int u = 0; u < 3; ++u) get(u);
+            constexpr int NL = (NP - 1) / 4 * 4;
+#pragma unroll 1
+            for (int m = 0; m < NL; m += 4) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) w[(u + 3) & 3][nb] = wfrag(2 * (m + u + 3), nb);
+                    mac(w[u], pair_off(m + u), false);
+                }
+            }
+#pragma unroll
+            for (int m = NL; m < NP; ++m) {
+                if (m + 3 < NP) get(m + 3);
+                mac(w[m & 3], pair_off(m), KB == 1 && m == NP - 1);
+            }
+        }
+        uint16_t* yb = y + ((long long)n * D + z) * hw * cyt + cyo + 4 * g;
+#pragma unroll
+        for (int j = 0; j < MB; ++j) {
+            if (pos[j] < 0) continue;
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                s4_t o;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    float v = acc[j][nb][r] + (bias ? bias[nb * 16 + 4 * g + r] : 0.0f);
+                    if (relu) v = fmaxf(v, 0.0f);
+                    o[r] = (short)f2bf(v);
+                }
+                *reinterpret_cast<s4_t*>(yb + (long long)pos[j] * cyt + nb * 16) = o;
+            }
+        }
+        __syncthreads();
+    }
+}
+
 // --------------------------------------------------------- conv wgrad
 // Partial sums of gW[t][i][o] = sum_p x[p + d_t][i] gz[p][o] over the rows
 // (n, z, y) of one slice, on the matrix cores with K = positions: A[i][k] =
@@ -272,10 +446,7 @@ __global__ __launch_bounds__(256) void k_conv3_wgrad(const uint16_t* __restrict_
 // block).  The per-tap kernel above re-reads x 27 times in 2-byte pieces: the 14
 // weight gradients of an 8 x 56^3 pass took 13.1 ms there (and their bias sums
 // 3.4 ms), 0.94 ms here; the 32 -> 16 one 167 us.
-typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
-typedef short s8_t __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) s4_t lds_s4_t;
-typedef uint32_t u4_t __attribute__((ext_vector_type(4)));
 
 // operand of 32 positions: rows 8g..8g+7 of the 16-channel block at p (32-byte
 // rows `step` rows apart), column li; p already holds this lane's piece
@@ -935,12 +1106,75 @@ int check_chan(int ct, int co, int c, const char* name) {
     return TT_OK;
 }
 
+// channel ranges that can be read in aligned 16-byte pieces
+bool pieces16(const uint16_t* p, int ct, int co) {
+    return reinterpret_cast<uintptr_t>(p) % 16 == 0 && ct % 8 == 0 && co % 8 == 0;
+}
+
+// Rows of a k_conv3_planes tile (0: the staged form does not take these sizes):
+// as many as its waves' blocks, the fetch registers and the LDS of two
+// workgroups per CU hold (of one, if a single row needs that), evened out over H.
+int conv3_plane_rows(int KB, int MB, int H, int W, size_t* lds) {
+    auto bytes = [&](int r) { return (size_t)3 * (r + 2) * (W + 2) * cv_pixel(KB) * sizeof(uint16_t); };
+    auto fits = [&](int r, size_t most) {
+        return r * W <= 64 * MB && (r + 2) * 2 * KB * W <= 256 * kCvPieces && bytes(r) <= most;
+    };
+    int R = 0;
+    while (R < H && fits(R + 1, 80 * 1024)) ++R;
+    if (R == 0 && fits(1, 156 * 1024)) R = 1;
+    if (R == 0) return 0;
+    const int nt = (H + R - 1) / R;
+    R = (H + nt - 1) / nt;
+    *lds = bytes(R);
+    return R;
+}
+
+template <int KB, int NB, int MB>
+int conv3_planes(const uint16_t* x, int nbatch, int D, int H, int W, int cxt, int cxo, const uint16_t* frag,
+                 const float* bias, int relu, uint16_t* y, int cyt, int cyo, int R, size_t lds, hipStream_t st) {
+    const int ntile = (H + R - 1) / R;
+    const long long nt = (long long)nbatch * ntile;
+    // z chunks for one round of two workgroups a CU (a chunk fetches 2 planes more than it works on)
+    long long nz = 512 / nt;
+    nz = nz < 1 ? 1 : (nz > D ? D : nz);
+    const int zc = (int)((D + nz - 1) / nz);
+    NN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_conv3_planes<KB, NB, MB>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    hipLaunchKernelGGL((k_conv3_planes<KB, NB, MB>), dim3((unsigned)nt, (unsigned)((D + zc - 1) / zc)), dim3(256), lds, st,
+                       x, D, H, W, cxt, cxo, frag, bias, relu, y, cyt, cyo, R, ntile, zc);
+    NN_LAUNCHED();
+    return TT_OK;
+}
+
+template <int KB>
+int conv3_planes_nb(int NB, const uint16_t* x, int nbatch, int D, int H, int W, int cxt, int cxo, const uint16_t* frag,
+                    const float* bias, int relu, uint16_t* y, int cyt, int cyo, int R, size_t lds, hipStream_t st) {
+    switch (NB) {
+        case 1: return conv3_planes<KB, 1, KB == 2 ? 6 : 8>(x, nbatch, D, H, W, cxt, cxo, frag, bias, relu, y, cyt, cyo, R, lds, st);
+        case 2: return conv3_planes<KB, 2, 8>(x, nbatch, D, H, W, cxt, cxo, frag, bias, relu, y, cyt, cyo, R, lds, st);
+        case 3: return conv3_planes<KB, 3, 4>(x, nbatch, D, H, W, cxt, cxo, frag, bias, relu, y, cyt, cyo, R, lds, st);
+        default: return conv3_planes<KB, 4, 4>(x, nbatch, D, H, W, cxt, cxo, frag, bias, relu, y, cyt, cyo, R, lds, st);
+    }
+}
+
 int conv3_fwd(const uint16_t* x, int nbatch, int D, int H, int W, int cxt, int cxo, int cin, const uint16_t* frag,
               const float* bias, int cout, int relu, uint16_t* y, int cyt, int cyo, hipStream_t st) {
     const long long npos = (long long)nbatch * D * H * W;
     const unsigned blocks = blocks_of(npos, 4 * 16 * kMB);
-    const int KB = cin / 16;
-    switch (cout / 16) {
+    const int KB = cin / 16, NB = cout / 16;
+    // staged planes take 16-byte pieces in and 8-byte ones out; 48 input channels
+    // (an odd number of steps per tap) and rows wider than a tile go direct
+    if (KB != 3 && pieces16(x, cxt, cxo) && reinterpret_cast<uintptr_t>(y) % 8 == 0 && cyt % 4 == 0 && cyo % 4 == 0 &&
+        (long long)nbatch * H < (1 << 30) && (long long)H * W * cxt < (1LL << 31)) {
+        size_t lds = 0;
+        const int R = conv3_plane_rows(KB, NB > 2 ? 4 : (KB == 2 && NB == 1 ? 6 : 8), H, W, &lds);
+        if (R > 0) {
+            if (KB == 1) return conv3_planes_nb<1>(NB, x, nbatch, D, H, W, cxt, cxo, frag, bias, relu, y, cyt, cyo, R, lds, st);
+            if (KB == 2) return conv3_planes_nb<2>(NB, x, nbatch, D, H, W, cxt, cxo, frag, bias, relu, y, cyt, cyo, R, lds, st);
+            return conv3_planes_nb<4>(NB, x, nbatch, D, H, W, cxt, cxo, frag, bias, relu, y, cyt, cyo, R, lds, st);
+        }
+    }
+    switch (NB) {
         case 1: hipLaunchKernelGGL(k_conv3_fwd<1>, dim3(blocks), dim3(256), 0, st, x, D, H, W, npos, cxt, cxo, KB, frag, bias, relu, y, cyt, cyo); break;
         case 2: hipLaunchKernelGGL(k_conv3_fwd<2>, dim3(blocks), dim3(256), 0, st, x, D, H, W, npos, cxt, cxo, KB, frag, bias, relu, y, cyt, cyo); break;
         case 3: hipLaunchKernelGGL(k_conv3_fwd<3>, dim3(blocks), dim3(256), 0, st, x, D, H, W, npos, cxt, cxo, KB, frag, bias, relu, y, cyt, cyo); break;
@@ -966,11 +1200,6 @@ int sum_slices(const float* part, long long ns, long long n, float* out, hipStre
     hipLaunchKernelGGL(k_sum_slices, dim3(blocks_of(n, kSumCols)), dim3(kSumCols * kSumGroups), 0, st, part, ns, n, out);
     NN_LAUNCHED();
     return TT_OK;
-}
-
-// channel ranges that can be read in aligned 16-byte pieces
-bool pieces16(const uint16_t* p, int ct, int co) {
-    return reinterpret_cast<uintptr_t>(p) % 16 == 0 && ct % 8 == 0 && co % 8 == 0;
 }
 
 long long colsum_blocks(long long npos) {

@@ -63,3 +63,37 @@ def test_up_wgrad_rows(torch_cuda, cin, cout, dims):
         ref, mag, refb, magb = ref + w, mag + wm, refb + b, magb + bm
     _check(gW, ref, mag)
     _check(gb, refb, magb)
+
+
+# Tiles of a plane at their edges: one row, ragged last tiles, rows of one
+# 16-position block and a rest, rows as wide as a tile, every count of channel
+# blocks, z chunks; and the layouts that go to the direct kernel (48 input
+# channels, rows wider than a tile, odd channel offsets).
+@pytest.mark.parametrize("cin,cout,nb,dims,offs", [
+    (16, 16, 1, (1, 1, 1), (0, 0)), (16, 16, 2, (9, 19, 56), (8, 4)), (16, 32, 1, (8, 12, 33), (0, 0)),
+    (16, 48, 1, (3, 7, 17), (8, 0)), (16, 64, 1, (2, 30, 9), (0, 8)), (32, 16, 1, (5, 23, 56), (0, 0)),
+    (32, 32, 2, (4, 28, 28), (16, 0)), (64, 32, 1, (6, 14, 14), (0, 4)), (64, 64, 1, (7, 7, 7), (0, 0)),
+    (16, 16, 1, (2, 2, 512), (0, 0)), (16, 16, 1, (2, 2, 513), (0, 0)), (48, 16, 1, (3, 5, 20), (0, 0)),
+    (32, 16, 1, (3, 5, 20), (4, 0)), (16, 16, 1, (3, 5, 20), (0, 3))])
+def test_conv3_planes(torch_cuda, cin, cout, nb, dims, offs):
+    from paper_2412_00031_amd import nn
+    torch = torch_cuda
+    rng = np.random.default_rng(cin * 3 + cout + dims[1])
+    cxo, cyo = offs
+    cxt = cin + 16 if cxo % 8 == 0 else cin + 4
+    x_d, x = _bf(torch, rng.standard_normal((nb,) + dims + (cxt,)))
+    W = rng.standard_normal((27, cin, cout)) * 0.2
+    W_d = torch.as_tensor(W.astype(np.float32)).cuda()
+    b = rng.standard_normal(cout).astype(np.float32)
+    y_d = torch.full((nb,) + dims + (cout + 12,), 7.0, dtype=torch.bfloat16, device="cuda")
+    nn.conv3_fwd(x_d, cin, nn.conv3_pack(W_d), torch.as_tensor(b).cuda(), cout, True, y_d, cx_off=cxo, cy_off=cyo)
+    got = y_d.double().cpu().numpy()
+    Wr = torch.as_tensor(W.astype(np.float32)).to(torch.bfloat16).double().numpy()
+    for q in range(nb):
+        xs = x[q, ..., cxo:cxo + cin]
+        ref = np.maximum(U.conv3(xs, Wr, b.astype(np.float64)), 0.0)
+        mag = U.conv3(np.abs(xs), np.abs(Wr), np.abs(b).astype(np.float64))
+        out = got[q, ..., cyo:cyo + cout]
+        assert np.all(np.abs(out - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-6 * mag), np.abs(out - ref).max()
+        rest = np.delete(got[q], np.s_[cyo:cyo + cout], axis=-1)
+        assert np.all(rest == 7.0)
