@@ -97,3 +97,104 @@ def test_conv3_planes(torch_cuda, cin, cout, nb, dims, offs):
         assert np.all(np.abs(out - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-6 * mag), np.abs(out - ref).max()
         rest = np.delete(got[q], np.s_[cyo:cyo + cout], axis=-1)
         assert np.all(rest == 7.0)
+
+
+# channel counts and offsets that do not come in aligned pieces of 8, beside ones that do
+@pytest.mark.parametrize("cin,cout,off", [(16, 16, 8), (5, 3, 1), (24, 16, 4), (64, 32, 16), (8, 48, 0)])
+def test_up_head_pool_mask_forms(torch_cuda, cin, cout, off):
+    from paper_2412_00031_amd import nn
+    torch = torch_cuda
+    rng = np.random.default_rng(cin + 5 * cout + off)
+    nb, D, H, W = 2, 3, 2, 5
+    x_d, x = _bf(torch, rng.standard_normal((nb, D, H, W, cin)))
+    Wu = rng.standard_normal((8, cin, cout)).astype(np.float32)
+    b = rng.standard_normal(cout).astype(np.float32)
+    y_d = torch.full((nb, 2 * D, 2 * H, 2 * W, cout + off + 8), 3.0, dtype=torch.bfloat16, device="cuda")
+    W_d, b_d = torch.as_tensor(Wu).cuda(), torch.as_tensor(b).cuda()
+    nn.up_fwd(x_d, W_d, b_d, y_d, cy_off=off)
+    g_d, g = _bf(torch, rng.standard_normal(tuple(y_d.shape)))
+    gx_d, _, _ = nn.up_bwd(x_d, g_d, W_d, cg_off=off)
+    y = y_d.double().cpu().numpy()
+    for q in range(nb):
+        gq = g[q, ..., off:off + cout]
+        for got, ref, mag in ((y[q, ..., off:off + cout], U.up(x[q], Wu.astype(np.float64), b.astype(np.float64)),
+                               U.up(np.abs(x[q]), np.abs(Wu).astype(np.float64), np.abs(b).astype(np.float64))),
+                              (gx_d[q].double().cpu().numpy(), U.up_backward(x[q], Wu.astype(np.float64), gq)[0],
+                               U.up_backward(x[q], np.abs(Wu).astype(np.float64), np.abs(gq))[0])):
+            assert np.all(np.abs(got - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-5 * mag)
+    assert np.all(np.delete(y, np.s_[off:off + cout], axis=-1) == 3.0)
+    # head: forward, data and weight gradients
+    w = rng.standard_normal(cin).astype(np.float32)
+    w_d = torch.as_tensor(w).cuda()
+    yh = nn.head_fwd(x_d, w_d, torch.zeros(1, device="cuda"))
+    gh = rng.standard_normal((nb, D, H, W)).astype(np.float32)
+    gxh, gw, gb = nn.head_bwd(x_d, torch.as_tensor(gh).cuda(), w_d)
+    _check(yh, x @ w.astype(np.float64), np.abs(x) @ np.abs(w).astype(np.float64))
+    want = torch.as_tensor(gh[..., None] * w).to(torch.bfloat16)
+    assert torch.equal(gxh.cpu(), want)
+    _check(gw, np.einsum("nzyxi,nzyx->i", x, gh), np.einsum("nzyxi,nzyx->i", np.abs(x), np.abs(gh)))
+    _check(gb, np.array([gh.astype(np.float64).sum()]), np.abs(gh).sum())
+    # pooling and mask, exact, on channels [off, off + cin) of a wider array of small integers (ties)
+    t_d, t = _bf(torch, rng.integers(-2, 3, (nb, 4, 2, 6, cin + off + 8)).astype(np.float64))
+    p_d = nn.pool_fwd(t_d, cin, c_off=off)
+    gp_d, gp = _bf(torch, rng.standard_normal((nb, 2, 1, 3, cin)))
+    gt_d = torch.ones_like(t_d)
+    nn.pool_bwd(t_d, gp_d, cin, gt_d, c_off=off, accumulate=True)
+    m_d = torch.full((nb, 4, 2, 6, cin + off), 5.0, dtype=torch.bfloat16, device="cuda")
+    gm_d, gm = _bf(torch, rng.standard_normal(t.shape))
+    nn.relu_mask(gm_d, t_d, cin, m_d, c_off=off, co_off=off)
+    for q in range(nb):
+        ts = t[q, ..., off:off + cin]
+        assert np.array_equal(p_d[q].double().cpu().numpy(), U.pool(ts))
+        want = torch.as_tensor(1.0 + U.pool_backward(ts, gp[q])).float().to(torch.bfloat16)
+        assert torch.equal(gt_d[q, ..., off:off + cin].cpu(), want)
+    assert np.all(np.delete(gt_d.double().cpu().numpy(), np.s_[off:off + cin], axis=-1) == 1.0)
+    assert np.array_equal(m_d[..., off:].double().cpu().numpy(), np.where(t > 0, gm, 0.0)[..., off:off + cin])
+    assert np.all(m_d[..., :off].double().cpu().numpy() == 5.0)
+
+
+# rows of the grid longer than a wave, one-node axes of the coarse grid, strides that leave a rest
+@pytest.mark.parametrize("n,stride,coord", [((5, 6, 131), 2, 1), ((4, 70, 9), 3, 0), ((9, 8, 65), 1, 1), ((4, 4, 4), 7, 0)])
+def test_warm_rows(torch_cuda, n, stride, coord):
+    from paper_2412_00031_amd import nn
+    torch = torch_cuda
+    rng = np.random.default_rng(sum(n) + stride)
+    g = dict(n=n, coord=coord, o=(6300.0, -0.02, 0.3), h=(1.0, 3e-4, 4e-4)) if coord else dict(n=n, coord=0, o=(0.0, 1.0, 2.0), h=(1.0, 2.0, 0.5))
+    m = tuple((v - 1) // stride + 1 for v in n)
+    dims = tuple(v + 2 for v in m)
+    t = lambda a: torch.as_tensor(np.ascontiguousarray(a), dtype=torch.float64, device="cuda")
+    s, xi, eta = rng.uniform(0.1, 0.3, n), rng.uniform(-0.05, 0.05, n), rng.uniform(-0.05, 0.05, n)
+    lo = np.array(g["o"])
+    src = lo + rng.uniform(0.0, 1.0, (2, 3)) * np.array(g["h"]) * (np.array(n) - 1)
+    par = np.stack([[0.2, 0.0, 0.0], [0.15, 0.0, 0.0]])
+    f = nn.warm_features(g, t(s), t(xi), t(eta), t(src), t(par), stride, dims).double().cpu().numpy()
+    ax = [g["o"][a] + g["h"][a] * stride * np.arange(m[a]) for a in range(3)]
+
+    def emb(a, b, c):
+        if coord == 0:
+            return np.stack(np.broadcast_arrays(a, b, c), -1)
+        return np.stack([a * np.cos(b) * np.cos(c), a * np.cos(b) * np.sin(c), a * np.sin(b) + 0.0 * c], -1)
+
+    X = emb(ax[0][:, None, None], ax[1][None, :, None], ax[2][None, None, :])
+    cut = tuple(slice(None, None, stride) for _ in range(3))
+    for q in range(2):
+        d = np.linalg.norm(X - emb(*src[q]), axis=-1)
+        ref = np.stack([(s[cut] / par[q, 0] - 1) * 5, xi[cut] * 25, eta[cut] * 25, d * 0.01], -1)
+        got = f[q, :m[0], :m[1], :m[2], :4]
+        assert np.all(np.abs(got - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-7)
+    rest = f.copy()
+    rest[:, :m[0], :m[1], :m[2], :4] = 0.0
+    assert np.all(rest == 0.0)
+    pred = rng.standard_normal((2,) + dims).astype(np.float32)
+    pred[1, 0, 0, 0] = np.nan
+    tau = nn.warm_init(g, torch.as_tensor(pred).cuda(), stride).cpu().numpy().reshape((2,) + n)
+    ref = pred[:, :m[0], :m[1], :m[2]].astype(np.float64)
+    for a in range(3):
+        i = np.arange(n[a])
+        b = np.minimum(i // stride, m[a] - 1)
+        c = np.minimum(b + 1, m[a] - 1)
+        w = np.where(c == b, 0.0, (i - b * stride) / stride).reshape([-1 if e == a + 1 else 1 for e in range(4)])
+        lo_, hi_ = np.take(ref, b, a + 1), np.take(ref, c, a + 1)
+        ref = np.where(w == 0.0, lo_, (1 - w) * lo_ + w * hi_)
+    ref = np.where(np.isnan(ref), 1.0, np.clip(1 + ref / 10, 0.25, 4.0))
+    assert np.allclose(tau, ref, rtol=1e-12, atol=1e-12)
