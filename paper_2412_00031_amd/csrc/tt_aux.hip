@@ -12,48 +12,146 @@
 
 namespace tt {
 
-__global__ void __launch_bounds__(256) k_misfit(int nsrc, int nrec, const double* __restrict__ T,
-                                                const double* __restrict__ Tobs, const double* __restrict__ w,
-                                                int npair, const int32_t* __restrict__ pairs,
-                                                const double* __restrict__ wpair, double alpha, double beta,
-                                                double* __restrict__ R, double* __restrict__ chi) {
+// Misfit and adjoint sources, one block per source.  The call has no workspace,
+// so each source's chi travels through the first element of its row of R:
+// k_misfit_chi leaves it there, k_misfit_sum adds them up in order, k_misfit_R
+// then writes R.  (All sources in one block, a thread per source walking its
+// receivers and pairs: 128 x 500 with 2000 pairs 1499 us; the three 34.)
+__global__ void __launch_bounds__(256) k_misfit_chi(int nrec, const double* __restrict__ T,
+                                                    const double* __restrict__ Tobs, const double* __restrict__ w,
+                                                    int npair, const int32_t* __restrict__ pairs,
+                                                    const double* __restrict__ wpair, double alpha, double beta,
+                                                    double* __restrict__ R) {
     __shared__ double sh[4];
-    __shared__ int bad;
-    if (threadIdx.x == 0) bad = 0;
-    __syncthreads();
+    const int q = blockIdx.x;
+    const long long base = (long long)q * nrec;
     double part = 0.0;
-    for (int q = threadIdx.x; q < nsrc; q += blockDim.x) {
-        const long long base = (long long)q * nrec;
-        for (int m = 0; m < nrec; ++m) {
-            const double ww = w ? w[base + m] : 1.0;
-            const double r = T[base + m] - Tobs[base + m];
-            part += alpha * 0.5 * ww * r * r;
-            R[base + m] = alpha * ww * r;
+    for (int m = threadIdx.x; m < nrec; m += 256) {
+        const double ww = w ? w[base + m] : 1.0;
+        const double r = T[base + m] - Tobs[base + m];
+        part += alpha * 0.5 * ww * r * r;
+    }
+    for (int p = threadIdx.x; p < npair; p += 256) {
+        const int m = pairs[2 * p], i = pairs[2 * p + 1];
+        if (m < 0 || m >= nrec || i < 0 || i >= nrec) {
+            part = __builtin_nan("");
+            continue;
         }
-        for (int p = 0; p < npair; ++p) {
-            const int m = pairs[2 * p], i = pairs[2 * p + 1];
-            if (m < 0 || m >= nrec || i < 0 || i >= nrec) {
-                bad = 1;
-                continue;
-            }
-            const double ww = wpair ? wpair[(long long)q * npair + p] : 1.0;
-            const double r = (T[base + m] - T[base + i]) - (Tobs[base + m] - Tobs[base + i]);
-            part += beta * 0.5 * ww * r * r;
-            R[base + m] += beta * ww * r;
-            R[base + i] -= beta * ww * r;
-        }
+        const double ww = wpair ? wpair[(long long)q * npair + p] : 1.0;
+        const double r = (T[base + m] - T[base + i]) - (Tobs[base + m] - Tobs[base + i]);
+        part += beta * 0.5 * ww * r * r;
     }
     const double tot = block_sum256(part, sh);
-    if (threadIdx.x == 0) *chi = bad ? __builtin_nan("") : tot;
+    if (threadIdx.x == 0) R[base] = tot;
+}
+
+__global__ void __launch_bounds__(256) k_misfit_sum(int nsrc, int nrec, const double* __restrict__ R,
+                                                    double* __restrict__ chi) {
+    __shared__ double sh[4];
+    double v = 0.0;
+    for (int q = threadIdx.x; q < nsrc; q += 256) v += R[(long long)q * nrec];
+    const double tot = block_sum256(v, sh);
+    if (threadIdx.x == 0) *chi = tot;
+}
+
+// R: each receiver starts from its own term and takes its pairs' contributions
+// in list order.  Pairs are taken in chunks; a chunk's contributions are listed
+// by receiver in LDS (counted, offsets by a scan, filled in any order and then
+// put in list order by the thread that owns the receiver).  A receiver with more
+// than kMisSort contributions of the chunk walks the chunk's pairs instead: a
+// star of pairs around one receiver costs a walk, not a quadratic sort.
+constexpr int kMisPairs = 1024;  // pairs of a chunk
+constexpr int kMisRecs = 4096;   // receivers listed at a time
+constexpr int kMisSort = 32;
+
+__global__ void __launch_bounds__(256) k_misfit_R(int nrec, const double* __restrict__ T,
+                                                  const double* __restrict__ Tobs, const double* __restrict__ w,
+                                                  int npair, const int32_t* __restrict__ pairs,
+                                                  const double* __restrict__ wpair, double alpha, double beta,
+                                                  double* __restrict__ R) {
+    __shared__ int cnt[kMisRecs], off[kMisRecs], ent[2 * kMisPairs], pm[kMisPairs], pi[kMisPairs], wsum[4];
+    __shared__ double sg[kMisPairs];
+    const int q = blockIdx.x, tid = threadIdx.x;
+    const long long base = (long long)q * nrec;
+    for (int m = tid; m < nrec; m += 256) {
+        const double ww = w ? w[base + m] : 1.0;
+        R[base + m] = alpha * ww * (T[base + m] - Tobs[base + m]);
+    }
+    for (int m0 = 0; m0 < nrec && npair > 0; m0 += kMisRecs) {
+        const int nm = min(kMisRecs, nrec - m0);
+        for (int pc = 0; pc < npair; pc += kMisPairs) {
+            for (int m = tid; m < nm; m += 256) cnt[m] = 0;
+            __syncthreads();
+            const int np = min(kMisPairs, npair - pc);
+            for (int p = tid; p < np; p += 256) {
+                const int m = pairs[2 * (pc + p)], i = pairs[2 * (pc + p) + 1];
+                pm[p] = pi[p] = -1;
+                if (m < 0 || m >= nrec || i < 0 || i >= nrec) continue;
+                pm[p] = m - m0;
+                pi[p] = i - m0;
+                const double ww = wpair ? wpair[(long long)q * npair + pc + p] : 1.0;
+                sg[p] = beta * ww * ((T[base + m] - T[base + i]) - (Tobs[base + m] - Tobs[base + i]));
+                if ((unsigned)(m - m0) < (unsigned)nm) atomicAdd(&cnt[m - m0], 1);
+                if ((unsigned)(i - m0) < (unsigned)nm) atomicAdd(&cnt[i - m0], 1);
+            }
+            __syncthreads();
+            // exclusive scan of cnt: runs of per receivers a thread, then over the threads
+            const int per = (nm + 255) / 256, f0 = min(tid * per, nm), f1 = min(f0 + per, nm);
+            int run = 0;
+            for (int m = f0; m < f1; ++m) run += cnt[m];
+            int inc = run;
+            for (int d = 1; d < 64; d <<= 1) {
+                const int o = __shfl_up(inc, d, 64);
+                if ((tid & 63) >= d) inc += o;
+            }
+            if ((tid & 63) == 63) wsum[tid >> 6] = inc;
+            __syncthreads();
+            int at = inc - run;
+            for (int v = 0; v < (tid >> 6); ++v) at += wsum[v];
+            for (int m = f0; m < f1; ++m) {
+                off[m] = at;
+                at += cnt[m];
+            }
+            __syncthreads();
+            for (int p = tid; p < np; p += 256) {
+                if ((unsigned)pm[p] < (unsigned)nm) ent[atomicAdd(&off[pm[p]], 1)] = 2 * p;
+                if ((unsigned)pi[p] < (unsigned)nm) ent[atomicAdd(&off[pi[p]], 1)] = 2 * p + 1;
+            }
+            __syncthreads();
+            for (int m = tid; m < nm; m += 256) {
+                const int n = cnt[m];
+                if (n == 0) continue;
+                double acc = R[base + m0 + m];
+                if (n > kMisSort) {
+                    for (int p = 0; p < np; ++p) {
+                        if (pm[p] == m) acc += sg[p];
+                        if (pi[p] == m) acc -= sg[p];
+                    }
+                    R[base + m0 + m] = acc;
+                    continue;
+                }
+                int* e = ent + off[m] - n;
+                for (int a = 1; a < n; ++a) {
+                    const int v = e[a];
+                    int c = a;
+                    for (; c > 0 && e[c - 1] > v; --c) e[c] = e[c - 1];
+                    e[c] = v;
+                }
+                for (int a = 0; a < n; ++a) acc += e[a] & 1 ? -sg[e[a] >> 1] : sg[e[a] >> 1];
+                R[base + m0 + m] = acc;
+            }
+            __syncthreads();
+        }
+    }
 }
 
 // Common-receiver differential misfit (Eq. (4), third misfit) and its adjoint
 // sources (Eq. (A4)), added to R and chi.
 //
 // Adjoint sources: one wave per receiver m.  The wave stages 64 of the
-// receiver's pairs at a time (indices and gamma w r in LDS); lane l owns source
-// n = base + l and adds the staged contributions that name it, in list order,
-// to its R[n][m] -- the additions each element receives come in the order of
+// receiver's pairs at a time (indices and gamma w r in LDS); for 64 sources after
+// 64, lane l owns source n = base + l and adds the staged contributions that name
+// it, in list order, to its R[n][m] -- the additions each element receives come in the order of
 // the pair list, as in the plain definition, and no two lanes write one
 // element.
 constexpr int kCrStage = 64;
@@ -67,31 +165,31 @@ __global__ void __launch_bounds__(64) k_misfit_cr_R(int nsrc, int nrec, const do
     const int m = blockIdx.x;
     const int p0 = off[m], p1 = off[m + 1];
     if (p0 < 0 || p1 <= p0 || !pair) return;  // nothing to add (malformed offsets: chi reports it)
-    for (int base = 0; base < nsrc; base += kCrStage) {
-        const int n = base + (int)threadIdx.x;
-        const long long cn = (long long)n * nrec + m;
-        double acc = n < nsrc ? R[cn] : 0.0;
-        bool touched = false;
-        for (int pc = p0; pc < p1; pc += kCrStage) {
-            const int p = pc + (int)threadIdx.x;
-            int a = -1, b = -1;
-            double g = 0.0;
-            if (p < p1) {
-                a = pair[2 * p];
-                b = pair[2 * p + 1];
-                if (a >= 0 && a < nsrc && b >= 0 && b < nsrc) {
-                    const long long ca = (long long)a * nrec + m, cb = (long long)b * nrec + m;
-                    const double ww = wcr ? wcr[p] : 1.0;
-                    g = gamma * ww * ((T[ca] - T[cb]) - (Tobs[ca] - Tobs[cb]));
-                } else {
-                    a = b = -1;
-                }
+    for (int pc = p0; pc < p1; pc += kCrStage) {
+        const int p = pc + (int)threadIdx.x;
+        int a = -1, b = -1;
+        double g = 0.0;
+        if (p < p1) {
+            a = pair[2 * p];
+            b = pair[2 * p + 1];
+            if (a >= 0 && a < nsrc && b >= 0 && b < nsrc) {
+                const long long ca = (long long)a * nrec + m, cb = (long long)b * nrec + m;
+                const double ww = wcr ? wcr[p] : 1.0;
+                g = gamma * ww * ((T[ca] - T[cb]) - (Tobs[ca] - Tobs[cb]));
+            } else {
+                a = b = -1;
             }
-            sn[threadIdx.x] = a;
-            sj[threadIdx.x] = b;
-            sg[threadIdx.x] = g;
-            __syncthreads();
-            const int cnt = min(kCrStage, p1 - pc);
+        }
+        sn[threadIdx.x] = a;
+        sj[threadIdx.x] = b;
+        sg[threadIdx.x] = g;
+        __syncthreads();
+        const int cnt = min(kCrStage, p1 - pc);
+        for (int base = 0; base < nsrc; base += kCrStage) {
+            const int n = base + (int)threadIdx.x;
+            const long long cn = (long long)n * nrec + m;
+            double acc = n < nsrc ? R[cn] : 0.0;
+            bool touched = false;
             for (int q = 0; q < cnt; ++q) {
                 if (sn[q] == n) {
                     acc += sg[q];
@@ -102,56 +200,102 @@ __global__ void __launch_bounds__(64) k_misfit_cr_R(int nsrc, int nrec, const do
                     touched = true;
                 }
             }
-            __syncthreads();
+            if (n < nsrc && touched) R[cn] = acc;
         }
-        if (n < nsrc && touched) R[cn] = acc;
+        __syncthreads();
     }
 }
 
-// gamma chi_cr over all pairs: one block, pair p of the flat list taken by
-// thread p mod 1024 (its receiver found by binary search in the offsets, staged
-// in LDS when they fit), fixed-order block reduction; malformed offsets or
-// indices make chi NaN.
-constexpr int kCrOffLds = 8192;
+// gamma chi_cr over all pairs: one block (the call has no workspace for partial
+// sums of several).  Receivers are taken in runs whose residuals T - Tobs of all
+// sources fit in LDS (kCrRes values: rows of the run are read coalesced); pair p
+// of the run is taken by thread p mod 1024, its receiver found by binary search
+// in the run's offsets.  More sources than kCrRes read T and Tobs per pair.
+// Fixed-order block reduction; malformed offsets or indices make chi NaN.
+// (128 x 500, 32000 pairs: 72 us with four scattered 8-byte reads a pair, 55 from
+// LDS; what is left is one CU's staging of the rows, five times 112 receivers.)
+constexpr int kCrRes = 14336;
+constexpr int kCrRun = 512;  // receivers of a run at most
 
 __global__ void __launch_bounds__(1024) k_misfit_cr_chi(int nsrc, int nrec, const double* __restrict__ T,
                                                         const double* __restrict__ Tobs,
-                                                        const int32_t* __restrict__ off_g,
+                                                        const int32_t* __restrict__ off,
                                                         const int32_t* __restrict__ pair,
                                                         const double* __restrict__ wcr, double gamma,
                                                         double* __restrict__ chi) {
+    extern __shared__ double res[];  // [nsrc][mr]
     __shared__ double sh[16];
     __shared__ int bad;
-    __shared__ int offl[kCrOffLds];
-    const bool staged = nrec + 1 <= kCrOffLds;
-    if (staged)
-        for (int m = threadIdx.x; m <= nrec; m += blockDim.x) offl[m] = off_g[m];
-    if (threadIdx.x == 0) bad = (off_g[0] != 0);
+    __shared__ int offl[kCrRun + 1];
+    if (threadIdx.x == 0) bad = (off[0] != 0);
     __syncthreads();
-    const int32_t* off = staged ? offl : off_g;
     for (int m = threadIdx.x; m < nrec; m += blockDim.x)
         if (off[m + 1] < off[m]) bad = 1;
     __syncthreads();
     const int total = bad ? 0 : off[nrec];
-    if (total > 0 && !pair) bad = 1;
+    __syncthreads();
+    if (total > 0 && !pair && threadIdx.x == 0) bad = 1;
+    __syncthreads();
     double part = 0.0;
     if (!bad) {
-        for (int p = threadIdx.x; p < total; p += blockDim.x) {
-            int lo = 0, hi = nrec;  // off[lo] <= p < off[hi]
-            while (hi - lo > 1) {
-                const int mid = (lo + hi) >> 1;
-                if (off[mid] <= p) lo = mid;
-                else hi = mid;
+        const bool staged = nsrc <= kCrRes;
+        const int mr = staged && nsrc > 0 ? min(kCrRun, kCrRes / nsrc) : kCrRun;
+        for (int m0 = 0; m0 < nrec; m0 += mr) {
+            const int nm = min(mr, nrec - m0);
+            for (int e = threadIdx.x; e <= nm; e += blockDim.x) offl[e] = off[m0 + e];
+            if (staged) {  // a wave takes every 16th source's row, eight rows in flight
+                const int wv = threadIdx.x >> 6;
+                for (int l = threadIdx.x & 63; l < nm; l += 64)
+                    for (int n0 = wv; n0 < nsrc; n0 += 128) {
+                        double tv[8], ov[8];
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) {
+                            const long long c = (long long)min(n0 + 16 * u, nsrc - 1) * nrec + m0 + l;
+                            tv[u] = T[c];
+                            ov[u] = Tobs[c];
+                        }
+#pragma unroll
+                        for (int u = 0; u < 8; ++u)
+                            if (n0 + 16 * u < nsrc) res[(n0 + 16 * u) * nm + l] = tv[u] - ov[u];
+                    }
             }
-            const int n = pair[2 * p], j = pair[2 * p + 1];
-            if (n < 0 || n >= nsrc || j < 0 || j >= nsrc) {
-                bad = 1;
-                continue;
+            __syncthreads();
+            const int pe = offl[nm];
+            for (int pb = offl[0] + (int)threadIdx.x; pb < pe; pb += 4 * 1024) {
+                int pn[4], pj[4];
+                double pw[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int p = min(pb + 1024 * u, pe - 1);
+                    pn[u] = pair[2 * p];
+                    pj[u] = pair[2 * p + 1];
+                    pw[u] = wcr ? wcr[p] : 1.0;
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int p = pb + 1024 * u, n = pn[u], j = pj[u];
+                    if (p >= pe) break;
+                    int lo = 0, hi = nm;  // offl[lo] <= p < offl[hi]
+                    while (hi - lo > 1) {
+                        const int mid = (lo + hi) >> 1;
+                        if (offl[mid] <= p) lo = mid;
+                        else hi = mid;
+                    }
+                    if (n < 0 || n >= nsrc || j < 0 || j >= nsrc) {
+                        bad = 1;
+                        continue;
+                    }
+                    double r;
+                    if (staged) {
+                        r = res[n * nm + lo] - res[j * nm + lo];
+                    } else {
+                        const long long cn = (long long)n * nrec + m0 + lo, cj = (long long)j * nrec + m0 + lo;
+                        r = (T[cn] - Tobs[cn]) - (T[cj] - Tobs[cj]);
+                    }
+                    part += gamma * 0.5 * pw[u] * r * r;
+                }
             }
-            const long long cn = (long long)n * nrec + lo, cj = (long long)j * nrec + lo;
-            const double ww = wcr ? wcr[p] : 1.0;
-            const double r = (T[cn] - T[cj]) - (Tobs[cn] - Tobs[cj]);
-            part += gamma * 0.5 * ww * r * r;
+            __syncthreads();
         }
     }
     part = wave_sum(part);
@@ -270,14 +414,22 @@ void launch_reloc_kernel(const Plan& P, const double* tau, int nev, const double
 void launch_misfit(int nsrc, int nrec, const double* T, const double* Tobs, const double* w, int npair,
                    const int32_t* pairs, const double* wpair, double alpha, double beta, double* R, double* chi,
                    hipStream_t st) {
-    hipLaunchKernelGGL(k_misfit, dim3(1), dim3(256), 0, st, nsrc, nrec, T, Tobs, w, npair, pairs, wpair, alpha, beta,
-                       R, chi);
+    if (nsrc == 0 || nrec == 0) {  // no residual; a pair can only name a receiver that is not there
+        launch_fill(chi, 1, nsrc > 0 && npair > 0 ? __builtin_nan("") : 0.0, st);
+        return;
+    }
+    hipLaunchKernelGGL(k_misfit_chi, dim3(nsrc), dim3(256), 0, st, nrec, T, Tobs, w, npair, pairs, wpair, alpha, beta, R);
+    hipLaunchKernelGGL(k_misfit_sum, dim3(1), dim3(256), 0, st, nsrc, nrec, R, chi);
+    hipLaunchKernelGGL(k_misfit_R, dim3(nsrc), dim3(256), 0, st, nrec, T, Tobs, w, npair, pairs, wpair, alpha, beta, R);
 }
 
 void launch_misfit_cr(int nsrc, int nrec, const double* T, const double* Tobs, const int32_t* off, const int32_t* pair,
                       const double* wcr, double gamma, double* R, double* chi, hipStream_t st) {
     hipLaunchKernelGGL(k_misfit_cr_R, dim3(nrec), dim3(64), 0, st, nsrc, nrec, T, Tobs, off, pair, wcr, gamma, R);
-    hipLaunchKernelGGL(k_misfit_cr_chi, dim3(1), dim3(1024), 0, st, nsrc, nrec, T, Tobs, off, pair, wcr, gamma, chi);
+    const size_t lds = sizeof(double) * (nsrc <= kCrRes ? (size_t)kCrRes : 0);
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_misfit_cr_chi), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)(sizeof(double) * kCrRes));
+    hipLaunchKernelGGL(k_misfit_cr_chi, dim3(1), dim3(1024), lds, st, nsrc, nrec, T, Tobs, off, pair, wcr, gamma, chi);
 }
 
 // ------------------------------------------- multiple-grid parameterisation
