@@ -934,48 +934,96 @@ __global__ void __launch_bounds__(256) k_adj_coef(SweepArgs a, const double* __r
 
 // d chi / d tau = sum_m R_m w_c T0(c) (discrete adjoint), or the point sources
 // sum_m R_m w_c of Eq. (5) (continuous adjoint, with_t0 = 0), added in receiver
-// order (one thread per source: deterministic)
+// order, one wave per source.  64 receivers are taken at a time, one a lane: a
+// lane adds the contributions to those corners of its cell that no earlier lane's
+// cell has, its own and, in receiver order, those of the later lanes whose cells
+// share the corner, so every node sees the additions of the plain loop in its
+// order.  (That loop on one thread per source waited for four dependent reads per
+// corner: 64 sources of 101^3 4.3 ms for 500 receivers; a wave per source 0.27.)
 template <int COORD>
-__global__ void k_adj_rhs(SweepArgs a, const double* __restrict__ diag_all, double* __restrict__ rhs_all,
-                          int* __restrict__ box_all, int nrec, const double* __restrict__ rec,
-                          const double* __restrict__ R, int with_t0) {
-    const int src = blockIdx.x * blockDim.x + threadIdx.x;
-    if (src >= a.nsrc) return;
+__global__ void __launch_bounds__(64) k_adj_rhs(SweepArgs a, const double* __restrict__ diag_all,
+                                                double* __restrict__ rhs_all, int* __restrict__ box_all, int nrec,
+                                                const double* __restrict__ rec, const double* __restrict__ R,
+                                                int with_t0) {
+    __shared__ int cell[3][64];
+    __shared__ double fr[3][64], rm[64];
+    const int src = blockIdx.x, lane = threadIdx.x;
     const Geo& G = a.G;
     const Src S = a.src[src];
     const double* dg = diag_all + (long long)src * G.N;
     double* rh = rhs_all + (long long)src * G.N;
-    int lo[3] = {G.n[0], G.n[1], G.n[2]}, hi[3] = {-1, -1, -1};
     double* brhs = const_cast<double*>(a.bnd_rhs) + (long long)src * G.NB;
-    for (int m = 0; m < nrec; ++m) {
+    int lo[3] = {G.n[0], G.n[1], G.n[2]}, hi[3] = {-1, -1, -1};
+    for (int m0 = 0; m0 < nrec; m0 += 64) {
+        const int cnt = min(64, nrec - m0);
+        const int m = m0 + min(lane, cnt - 1);
+        const bool on = lane < cnt;
         const Tri t = tri_of(G, rec[3 * m], rec[3 * m + 1], rec[3 * m + 2]);
-        const double r = R[(long long)src * nrec + m];
-        for (int c0 = 0; c0 < 2; ++c0)
-            for (int c1 = 0; c1 < 2; ++c1)
-                for (int c2 = 0; c2 < 2; ++c2) {
-                    const int i = t.b[0] + c0, j = t.b[1] + c1, k = t.b[2] + c2;
-                    const Col c = make_col(G, a.T, i, j);
-                    const double2 t2 = a.T.t2[k];
-                    double T0, tt[3];
-                    factor<COORD>(S, c, t2.x, t2.y, T0, tt);
-                    const double v = with_t0 ? r * tri_w(t, c0, c1, c2) * T0 : r * tri_w(t, c0, c1, c2);
-                    // divided by the row's diagonal like the records (a row-less node's
-                    // value is never read by the sweeps)
-                    const long long xn = nidx(G, i, j, k);
-                    const double d = dg[xn];
-                    rh[xn] += d != 0.0 ? v / d : v;
+        for (int ax = 0; ax < 3; ++ax) {
+            cell[ax][lane] = t.b[ax];
+            fr[ax][lane] = t.f[ax];
+            lo[ax] = min(lo[ax], t.b[ax]);
+            hi[ax] = max(hi[ax], t.b[ax] + 1);
+        }
+        rm[lane] = R[(long long)src * nrec + m];
+        __syncthreads();
+        unsigned long long near = 0ull;  // receivers whose cells touch this lane's
+        for (int q = 0; q < cnt; ++q)
+            if ((unsigned)(cell[0][q] - t.b[0] + 1) <= 2u && (unsigned)(cell[1][q] - t.b[1] + 1) <= 2u &&
+                (unsigned)(cell[2][q] - t.b[2] + 1) <= 2u)
+                near |= 1ull << q;
+        if (on) {
+            for (int cc = 0; cc < 8; ++cc) {
+                const int i = t.b[0] + (cc >> 2), j = t.b[1] + ((cc >> 1) & 1), k = t.b[2] + (cc & 1);
+                const Col c = make_col(G, a.T, i, j);
+                const double2 t2 = a.T.t2[k];
+                double T0, tt[3];
+                factor<COORD>(S, c, t2.x, t2.y, T0, tt);
+                const long long xn = nidx(G, i, j, k);
+                // divided by the row's diagonal like the records (a row-less node's
+                // value is never read by the sweeps)
+                const double d = dg[xn];
+                const bool face = on_bnd(G, 0, i) || on_bnd(G, 1, j) || on_bnd(G, 2, k);
+                const long long bn = face ? bnd_encode(G, i, j, k) : 0;
+                double acc = rh[xn], bacc = face ? brhs[bn] : 0.0;
+                bool mine = true;
+                for (unsigned long long w = near; w; w &= w - 1) {
+                    const int q = __ffsll(w) - 1;
+                    Tri u;
+                    unsigned in = 1u;
                     const int id[3] = {i, j, k};
                     for (int ax = 0; ax < 3; ++ax) {
-                        lo[ax] = min(lo[ax], id[ax]);
-                        hi[ax] = max(hi[ax], id[ax]);
+                        u.b[ax] = id[ax] - cell[ax][q];  // the node's corner of cell q, if it is one
+                        u.f[ax] = fr[ax][q];
+                        in &= (unsigned)u.b[ax] <= 1u;
                     }
-                    if (on_bnd(G, 0, i) || on_bnd(G, 1, j) || on_bnd(G, 2, k))
-                        brhs[bnd_encode(G, i, j, k)] += v;
+                    if (!in) continue;
+                    if (q < lane) {
+                        mine = false;
+                        break;
+                    }
+                    const double v = with_t0 ? rm[q] * tri_w(u, u.b[0], u.b[1], u.b[2]) * T0
+                                             : rm[q] * tri_w(u, u.b[0], u.b[1], u.b[2]);
+                    acc += d != 0.0 ? v / d : v;
+                    bacc += v;
                 }
+                if (mine) {
+                    rh[xn] = acc;
+                    if (face) brhs[bn] = bacc;
+                }
+            }
+        }
+        __syncthreads();
     }
     for (int ax = 0; ax < 3; ++ax) {
-        box_all[src * 6 + 2 * ax] = lo[ax];
-        box_all[src * 6 + 2 * ax + 1] = hi[ax];
+        for (int w = 32; w > 0; w >>= 1) {
+            lo[ax] = min(lo[ax], __shfl_xor(lo[ax], w, 64));
+            hi[ax] = max(hi[ax], __shfl_xor(hi[ax], w, 64));
+        }
+        if (lane == 0) {
+            box_all[src * 6 + 2 * ax] = lo[ax];
+            box_all[src * 6 + 2 * ax + 1] = hi[ax];
+        }
     }
 }
 
@@ -1586,7 +1634,7 @@ void launch_adj_init(const Plan& P, const SweepArgs& a, const double* tau, int n
     hipLaunchKernelGGL(k_fill, dim3(fill_blocks(2 * P.G.NB * P.nsrc)), dim3(256), 0, st, P.bnd_in,
                        2 * P.G.NB * P.nsrc, 0.0);  // bnd_in and bnd_rhs
     const dim3 grid(blocks_for(P.G.N, 256), P.nsrc);
-    const dim3 rgrid(blocks_for(P.nsrc, 64));
+    const dim3 rgrid(P.nsrc);
     const int t0 = P.continuous ? 0 : 1;
     if (P.G.coord == 1) {
         if (P.continuous) hipLaunchKernelGGL(k_cadj_coef<1>, grid, dim3(256), 0, st, a, tau, P.coef, P.diag, P.rhs);
