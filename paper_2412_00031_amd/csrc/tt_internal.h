@@ -384,6 +384,7 @@ struct Plan {
     double* model = nullptr;  // forward: [4][Sa][4] = (s, 1 - 2 xi, 2 eta, 1 + 2 xi) (aligned row-coalesced layouts)
     double* bnd_in = nullptr; // adjoint: [nsrc][NB] (continuous adjoint: boundary pass scratch)
     double* bnd_rhs = nullptr; // adjoint: right-hand side of the boundary nodes, [nsrc][NB]
+    double2* bnd_rec = nullptr;  // continuous adjoint: the boundary nodes' records, [nsrc][3][NB]
     bool continuous = false;  // adjoint: upwind discretisation of Eq. (5) instead of the exact transpose
     bool compact = false;     // adjoint: one node-order copy of the coefficient records
     // optional timing of the sweep kernels: an event pair around the
@@ -417,6 +418,7 @@ struct SweepArgs {
     double* eps_hist;       // optional [nsrc][hist_stride]
     int nslots, nbblocks, nsrc, max_iter, hist_stride;
     int compact;            // adjoint records in node order (TT_FLAG_COMPACT_ADJOINT)
+    int kfaces;             // adjoint: the sweeps set the nodes on a k face only (not the continuous system's)
     double kappa, tol;
 };
 

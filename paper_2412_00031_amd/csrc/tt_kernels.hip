@@ -601,10 +601,7 @@ __device__ __forceinline__ void unstage_tile(const Geo& G, const TileCtx& c, dou
 // else in a sweep reads or writes it, so the tile that finalises the end node
 // sets it right after its walk, next to the column it has just written back;
 // the boundary pass skips those nodes (strided ones: each sits in a cache line
-// of its own) and the change joins the tile's convergence sum.  (The adjoint
-// keeps them in its boundary pass: its value also needs the node's right-hand
-// side and coupling, loaded after the walk, which cost the sweep more than the
-// pass saved.)
+// of its own) and the change joins the tile's convergence sum.
 template <int DIR>
 __device__ __forceinline__ void fwd_kface_nodes(const Geo& G, const Src& S, const TileCtx& c, double* __restrict__ fld,
                                                 const double* lds, int own, int Lp, double& eps) {
@@ -854,12 +851,17 @@ constexpr int kRec = 6;
 // (k_adj_rhs adds to it); a zero diagonal (no row) stores a zero record
 __device__ __forceinline__ void store_record(const Geo& G, double* __restrict__ coef_all, double* __restrict__ diag_all,
                                              double* __restrict__ rhs_all, int src, long long x, int i, int j, int k,
-                                             const double (&out)[8], int compact) {
+                                             const double (&out)[8], int compact, double2* __restrict__ bnd = nullptr) {
     const double d = out[6];
     double2 rec[3];
 #pragma unroll
     for (int q = 0; q < 3; ++q)
         rec[q] = d != 0.0 ? make_double2(out[2 * q] / d, out[2 * q + 1] / d) : make_double2(0.0, 0.0);
+    if (bnd && (on_bnd(G, 0, i) || on_bnd(G, 1, j) || on_bnd(G, 2, k))) {
+        double2* br = bnd + (long long)src * 3 * G.NB + bnd_encode(G, i, j, k);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) br[q * G.NB] = rec[q];
+    }
     diag_all[(long long)src * G.N + x] = d;
     rhs_all[(long long)src * G.N + x] = 0.0;
     if (compact) {
@@ -1065,6 +1067,54 @@ __device__ __forceinline__ bool tile_meets_box(const Geo& G, const TileCtx& c, c
     return ia <= bx[1] && ib >= bx[0] && ja <= bx[3] && jb >= bx[2] && ka <= bx[5] && kb >= bx[4] && kq0 <= kq1;
 }
 
+// A k-face node of an interior column (its row: lambda_b = rhs_b - J_{x, b}
+// lambda_x, x the column's end node, no other row refers to it): the tile that
+// updates x sets it after its walk, as fwd_kface_nodes does; coupling and
+// right-hand side are loaded before the wait for upstream.  (In the boundary
+// pass, a line of its own each: 64 sources of 101^3 193 us a pass beside another
+// group's sweep, now 161.)
+struct AdjFace {
+    double in[2], rhs[2];
+    bool on[2];
+};
+
+template <int DIR>
+__device__ __forceinline__ void adj_kface_load(const SweepArgs& a, const Geo& G, const Src& S, const TileCtx& c, int src,
+                                               AdjFace& f) {
+    using D = Dir<DIR>;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        const int t = (e == 0 ? 0 : G.m[2] - 1) - c.kp0;          // the step that updates the end node
+        const int kb = c.kbase + D::s2 * (e == 0 ? -1 : G.m[2]);  // absolute k of the boundary node
+        f.on[e] = c.colv && t >= c.t0 && t < c.t1 && !in_fixed(S, c.i, c.j, kb);
+        f.in[e] = f.rhs[e] = 0.0;
+        if (f.on[e]) {
+            const long long b = (long long)src * G.NB + bnd_encode(G, c.i, c.j, kb);
+            f.in[e] = a.bnd_in[b];
+            f.rhs[e] = a.bnd_rhs[b];
+        }
+    }
+}
+
+template <int DIR>
+__device__ __forceinline__ void adj_kface_nodes(const Geo& G, const TileCtx& c, double* __restrict__ fld,
+                                                const double* lds, int own, int Lp, const AdjFace& f, double& dsum,
+                                                double& asum) {
+    using D = Dir<DIR>;
+    constexpr int sg = D::s2;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        if (!f.on[e]) continue;
+        const int t = (e == 0 ? 0 : G.m[2] - 1) - c.kp0;
+        const int o = sg > 0 ? own + t : own + Lp - 1 - t;
+        const double old = lds[e == 0 ? o : o + 2 * sg];  // entry t or t + 2: the boundary node
+        const double nv = f.rhs[e] - f.in[e] * lds[o + sg];
+        fld[nidx(G, c.i, c.j, c.kbase + sg * (e == 0 ? -1 : G.m[2]))] = nv;
+        dsum += fabs(nv - old);
+        if (DIR == 7) asum += fabs(nv);
+    }
+}
+
 template <int DIR, bool RHS, bool COMPACT>
 __device__ __forceinline__ bool adj_tile(const SweepArgs& a, const Geo& G, const Src& S, const TileCtx& c, int src,
                                          double* lds, const unsigned long long* up, unsigned long long target,
@@ -1081,6 +1131,8 @@ __device__ __forceinline__ bool adj_tile(const SweepArgs& a, const Geo& G, const
     AdjSlot ring[kPreAdj];
 #pragma unroll
     for (int u = 0; u < kPreAdj; ++u) adj_fetch<DIR, RHS, COMPACT>(c, cf, rh, xb, c.t0 + u, ring[u]);
+    AdjFace face;
+    if (a.kfaces) adj_kface_load<DIR>(a, G, S, c, src, face);
     const bool waited = wait_upstream(up, target);
     stage_tile<DIR>(G, c, fld, -(long long)src * G.N, (long long)(a.nsrc - src) * G.N - 2, lds);
     __syncthreads();
@@ -1121,6 +1173,7 @@ __device__ __forceinline__ bool adj_tile(const SweepArgs& a, const Geo& G, const
     }
     __syncthreads();
     unstage_tile<DIR>(G, c, fld, lds, Lp);
+    if (a.kfaces) adj_kface_nodes<DIR>(G, c, fld, lds, own, Lp, face, dsum, asum);
     return waited;
 }
 
@@ -1201,7 +1254,7 @@ __global__ void __launch_bounds__(kBndThreads) k_adj_bnd(SweepArgs a, int dir) {
     if (b < G.NB) {
         int i, j, k;
         bnd_decode(G, b, i, j, k);
-        if (!in_fixed(S, i, j, k)) {
+        if (!in_fixed(S, i, j, k) && !kface_only(G, i, j)) {  // (the sweeps set the nodes on a k face only)
             const double nv = adj_bval<2>(G, S, lam, brhs, bin, i, j, k);
             const long long x = nidx(G, i, j, k);
             d = fabs(nv - lam[x]);
@@ -1295,7 +1348,7 @@ __device__ __forceinline__ double cadj_area(const Geo& G, int a, int i, int j, i
 template <int COORD>
 __global__ void __launch_bounds__(256) k_cadj_coef(SweepArgs a, const double* __restrict__ tau_all,
                                                    double* __restrict__ coef_all, double* __restrict__ diag_all,
-                                                   double* __restrict__ rhs_all) {
+                                                   double* __restrict__ rhs_all, double2* __restrict__ bnd_all) {
     const Geo& G = a.G;
     const int src = blockIdx.y;
     const long long x = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1335,12 +1388,17 @@ __global__ void __launch_bounds__(256) k_cadj_coef(SweepArgs a, const double* __
         }
         out[6] = diag > 0.0 ? diag : HUGE_VAL;
     }
-    store_record(G, coef_all, diag_all, rhs_all, src, x, i, j, k, out, a.compact);
+    store_record(G, coef_all, diag_all, rhs_all, src, x, i, j, k, out, a.compact, bnd_all);
 }
 
 // Boundary pass of the continuous system, Jacobi: every boundary node's new P
-// from the values present before the pass, into tmp [nsrc][NB] ...
-__global__ void __launch_bounds__(kBndThreads) k_cadj_bnd_calc(SweepArgs a, double* __restrict__ tmp_all) {
+// from the values present before the pass, into tmp [nsrc][NB].  Its row comes
+// from the boundary's own copy of the records, in planes by boundary node
+// (from the sweeps' layout a node of a k face takes lines of its own for its
+// record, its right-hand side and its neighbours: 128 sources of 61^3 162 us
+// beside another group's sweep, now 82); the right-hand side is read inside the box where it is not zero.
+__global__ void __launch_bounds__(kBndThreads) k_cadj_bnd_calc(SweepArgs a, const double2* __restrict__ rec_all,
+                                                               double* __restrict__ tmp_all) {
     const int src = blockIdx.y;
     if (blockIdx.x == 0) queue_reset(a, src);
     if (!a.active[src]) return;
@@ -1349,19 +1407,22 @@ __global__ void __launch_bounds__(kBndThreads) k_cadj_bnd_calc(SweepArgs a, doub
     if (b >= G.NB) return;
     const Src S = a.src[src];
     const double* P = a.field + (long long)src * G.N;
-    const double* cf = a.coef + (long long)src * (a.compact ? G.N : 4 * G.Sa) * kRec;  // compact, or layout 0
+    const double2* rc = rec_all + (long long)src * 3 * G.NB + b;
+    const int* bx = a.box + src * 6;
     int i, j, k;
     bnd_decode(G, b, i, j, k);
     double nv = 0.0;
     if (!in_fixed(S, i, j, k)) {
         const long long x = nidx(G, i, j, k);
-        const double* r = cf + (a.compact ? x : arec_idx(G, 0, i, j, k)) * kRec;  // the row divided by its diagonal
         const int id[3] = {i, j, k};
         const long long st[3] = {G.si, G.sj, 1};
-        double acc = a.rhs[(long long)src * G.N + nidx(G, i, j, k)];
+        const bool in = i >= bx[0] && i <= bx[1] && j >= bx[2] && j <= bx[3] && k >= bx[4] && k <= bx[5];
+        double acc = in ? a.rhs[(long long)src * G.N + x] : 0.0;
+#pragma unroll
         for (int ax = 0; ax < 3; ++ax) {
-            if (r[2 * ax] != 0.0 && id[ax] + 1 < G.n[ax]) acc -= r[2 * ax] * P[x + st[ax]];
-            if (r[2 * ax + 1] != 0.0 && id[ax] > 0) acc -= r[2 * ax + 1] * P[x - st[ax]];
+            const double2 r = rc[ax * G.NB];  // the row divided by its diagonal
+            if (r.x != 0.0 && id[ax] + 1 < G.n[ax]) acc -= r.x * P[x + st[ax]];
+            if (r.y != 0.0 && id[ax] > 0) acc -= r.y * P[x - st[ax]];
         }
         nv = acc;
     }
@@ -1495,6 +1556,7 @@ SweepArgs make_args(const Plan& P, const double* s, const double* xi, const doub
     a.nbblocks = P.nbblocks;
     a.nsrc = P.nsrc;
     a.compact = P.compact ? 1 : 0;
+    a.kfaces = P.continuous ? 0 : 1;
     a.max_iter = P.max_iter;
     a.hist_stride = P.hist_stride;
     a.kappa = P.kappa;
@@ -1637,11 +1699,11 @@ void launch_adj_init(const Plan& P, const SweepArgs& a, const double* tau, int n
     const dim3 rgrid(P.nsrc);
     const int t0 = P.continuous ? 0 : 1;
     if (P.G.coord == 1) {
-        if (P.continuous) hipLaunchKernelGGL(k_cadj_coef<1>, grid, dim3(256), 0, st, a, tau, P.coef, P.diag, P.rhs);
+        if (P.continuous) hipLaunchKernelGGL(k_cadj_coef<1>, grid, dim3(256), 0, st, a, tau, P.coef, P.diag, P.rhs, P.bnd_rec);
         else hipLaunchKernelGGL(k_adj_coef<1>, grid, dim3(256), 0, st, a, tau, P.coef, P.bnd_in, P.diag, P.rhs);
         hipLaunchKernelGGL(k_adj_rhs<1>, rgrid, dim3(64), 0, st, a, P.diag, P.rhs, P.box, nrec, rec, R, t0);
     } else {
-        if (P.continuous) hipLaunchKernelGGL(k_cadj_coef<0>, grid, dim3(256), 0, st, a, tau, P.coef, P.diag, P.rhs);
+        if (P.continuous) hipLaunchKernelGGL(k_cadj_coef<0>, grid, dim3(256), 0, st, a, tau, P.coef, P.diag, P.rhs, P.bnd_rec);
         else hipLaunchKernelGGL(k_adj_coef<0>, grid, dim3(256), 0, st, a, tau, P.coef, P.bnd_in, P.diag, P.rhs);
         hipLaunchKernelGGL(k_adj_rhs<0>, rgrid, dim3(64), 0, st, a, P.diag, P.rhs, P.box, nrec, rec, R, t0);
     }
@@ -1659,7 +1721,7 @@ void launch_adj_iteration(const Plan& P, const SweepArgs& a, hipStream_t st) {
         }
         }
         if (P.continuous) {
-            hipLaunchKernelGGL(k_cadj_bnd_calc, dim3(P.nbblocks, P.nsrc), dim3(kBndThreads), 0, st, a, P.bnd_in);
+            hipLaunchKernelGGL(k_cadj_bnd_calc, dim3(P.nbblocks, P.nsrc), dim3(kBndThreads), 0, st, a, P.bnd_rec, P.bnd_in);
             hipLaunchKernelGGL(k_cadj_bnd_store, dim3(P.nbblocks, P.nsrc), dim3(kBndThreads), 0, st, a, P.bnd_in, d);
         } else {
             hipLaunchKernelGGL(k_adj_bnd, dim3(P.nbblocks, P.nsrc), dim3(kBndThreads), 0, st, a, d);
