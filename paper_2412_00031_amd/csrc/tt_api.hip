@@ -52,12 +52,13 @@ __device__ __align__(256) unsigned char scratch[kScratchBytes];
 // finer; one that fills the chip several times over is bound by what its tiles
 // move, which deeper tiles move less of.  Measured at depths 16 and 28
 // (forward), 16 and 40 (adjoint):
-//   41^3 x 1 source (25 columns)   forward 12.0 / 15.5 ms   adjoint 13.3 / 15.4 ms
-//   61^3 x 32 (2048)                       38.0 / 50.1              57.7 / 60.6
-//   61^3 x 40 (2560)                       49.2 / 53.9
-//   61^3 x 64 (4096)                       59.1 / 56.3             100.1 / 76.8
-//   101^3 x 24 (4056)                     160.5 / 149.8            275.9 / 195.1
-//   101^3 x 128 (21632)                   488.8 / 348.9            828.1 / 589.2
+//   41^3 x 1 source (25 columns)   forward 8.9 / 15.4 ms    adjoint 10.7 / 14.1 ms
+//   61^3 x 16 (1024)                       28.2 / -                 38.6 / 51.0
+//   61^3 x 32 (2048)                       34.3 / 49.3              57.7 / 60.6
+//   61^3 x 64 (4096)                       54.5 / 56.0             100.1 / 76.8
+//   101^3 x 32 (5408)                     152.0 / 152.4
+//   101^3 x 128 (21632)                   421.0 / 353.3            828.1 / 589.2
+// (forward, in whole lines where lines_of says so: 61^3 x 64 49.5)
 constexpr int kDefaultTileK = 32;
 constexpr int kDefaultTileKFwd = 16;
 constexpr int kDefaultTileKAdj = 16;
@@ -109,22 +110,44 @@ long long batch_columns(const tt_grid* g, int nsrc) {
     return (long long)((g->n[0] + 5) / 8) * ((g->n[1] + 5) / 8) * nsrc;
 }
 
+// Does a forward solve keep its fields in the workspace, in rows padded to whole
+// lines (k_fwd_lines), at the default tile depth?  Lines 16 nodes deep against
+// slabs of 28 steps: 61^3 x 64 49.5 / 56.2 ms, x 128 66.0 / 70.3, x 256 107.1 /
+// 117.0; 81^3 x 64 106.2 / 107.2; 101^3 x 64 (0.6 GB of fields) 211.5 / 216.8,
+// x 128 (1.2 GB) 357.6 / 353.8: beyond a few times the 256 MB cache behind the
+// L2s the deeper slabs' fewer hand-overs win.  Below kDeepColumns slabs of 16 do
+// (61^3 x 32 34.3 / 44.9 ms in lines).
+constexpr long long kLinesBytes = 768LL << 20;
+
+bool lines_of(const tt_grid* g, int nsrc) {
+    const long long nf = (long long)g->n[0] * g->n[1] * ((g->n[2] + 15) / 16 * 16);
+    return batch_columns(g, nsrc) >= kDeepColumns && nf < (1LL << 31) - 16 && 8 * nf * nsrc <= kLinesBytes;
+}
+
 // Number of concurrently iterated source groups of a solve.  A sweep launch
 // leaves the chip partly idle at its first and last columns, where a second
-// group's launch can run; a batch of many columns hardly has such ends.
-// Forward with 1 and 2 groups, adjoint with 2 and 4: 61^3 x 32 43 / 38 ms and
-// 69 / 58 ms; 61^3 x 64 56.3 / 58.3 and 76.8 / 78.8; 61^3 x 128 70.6 / 73.4 and
-// 118.3 / 119.6; 101^3 x 128 352 / 349 and 589 / 598.
-int groups_of(const tt_opts* o, const tt_grid* grid, int nsrc, int which) {
+// group's launch can run; a batch of many columns hardly has such ends, and a
+// batch of few never fills the chip, so that groups only take turns.  Forward
+// with 1 and 2 groups: 256 columns (61^3 x 4) 24.3 / 25.9 ms, 1024 (x 16) 28.2 /
+// 28.3, 2048 (x 32) 41.7 / 34.3; slabs of 28 on 101^3 x 128 354 / 355, whole lines
+// on 61^3 x 256 113.2 / 107.1.  Adjoint with 1, 2 and 4: 408 columns (32 x 25 x 82,
+// 34 sources) 24.6 / 25.2 / 25.9, 512 (61^3 x 8) 30.0 / 32.9 / 35.2, 1024 43.8 / 38.6
+// / 42.7, 2048 - / 69 / 58; 61^3 x 128 with 2 and 4 118.3 / 119.6, 101^3 x 128 589 / 598.
+int groups_of(const tt_opts* o, const tt_grid* grid, int nsrc, int which, bool lines = false) {
+    const long long cols = batch_columns(grid, nsrc);
     int g;
     if (o && (o->flags & TT_FLAG_TIME_SWEEPS))
         g = 1;
     else if (o && o->groups > 0)
         g = o->groups;
+    else if (which == 0)
+        g = cols < 1024 || (cols >= kDeepColumns && !lines) ? 1 : 2;
     else
-        g = std::max(1, std::min(nsrc / 8, (which == 0 ? 1 : 2) * (batch_columns(grid, nsrc) < kDeepColumns ? 2 : 1)));
+        g = cols < 768 ? 1 : (cols < 1536 || cols >= kDeepColumns ? 2 : 4);
+    if (!(o && o->groups > 0)) g = std::max(1, std::min(g, nsrc / 8));
     return g > nsrc ? nsrc : g;
 }
+
 
 // first source of group q of G
 int group_begin(int nsrc, int G, int q) { return (int)(((long long)nsrc * q) / G); }
@@ -146,6 +169,7 @@ tt::Geo make_geo(const tt_grid* g, int tk) {
     G.nt[1] = (G.m[1] + tt::kBJ - 1) / tt::kBJ;
     G.ncols = G.nt[0] * G.nt[1];
     G.N = (long long)G.n[0] * G.n[1] * G.n[2];
+    G.Nf = G.N;
     G.si = (long long)G.n[1] * G.n[2];
     G.sj = G.n[2];
     G.NB = G.N - (long long)G.m[0] * G.m[1] * G.m[2];
@@ -159,14 +183,23 @@ tt::Geo make_geo(const tt_grid* g, int tk) {
     return G;
 }
 
+// a field with its rows padded to whole lines
+tt::Geo padded(tt::Geo G) {
+    G.sj = (G.n[2] + 15) / 16 * 16;
+    G.si = G.n[1] * G.sj;
+    G.Nf = G.n[0] * G.si;
+    if (G.Nf == G.N) G.Nf += 16;  // (Nf != N marks the layout)
+    return G;
+}
+
 // Workspace layout (each region 256-byte aligned):
 //   Src[nsrc] | tab0[n0] | tab1[n1] | tab2[n2] | active[nsrc] | iter[nsrc] | counter |
-//   part[nsrc*nslots] (sums, sweep progress, queues) | model[4*Sa*4] (forward) | part2[nsrc*nslots] (adjoint) |
+//   part[nsrc*nslots] (sums, sweep progress, queues) | model[4*Sa*4], pad[nsrc*Nf] if padded (forward) | part2[nsrc*nslots] (adjoint) |
 //   coef[nsrc*4*Sa*6] (or [nsrc*N*6] compact) | diag[nsrc*N] | rhs[nsrc*N] | box[nsrc*6] | bnd_in, bnd_rhs[nsrc*NB] |
 //   bnd_rec[nsrc*3*NB] (adjoint)
 struct Layout {
     size_t off_src, off_t0, off_t1, off_t2, off_active, off_iter, off_counter, off_part, off_part2, off_coef,
-        off_diag, off_rhs, off_box, off_bnd, off_bndrec, off_model, total;
+        off_diag, off_rhs, off_box, off_bnd, off_bndrec, off_model, off_pad, total;
 };
 
 Layout layout(const tt::Geo& G, int nsrc, int nslots, int which, bool compact = false) {
@@ -188,11 +221,14 @@ Layout layout(const tt::Geo& G, int nsrc, int nslots, int which, bool compact = 
     L.off_bnd = o;
     L.off_bndrec = o;
     L.off_model = o;
+    L.off_pad = o;
     if (which == 0 || which == 1) {
         L.off_part = o; o = align_up(o + sizeof(double) * (size_t)nsrc * nslots);
     }
     if (which == 0) {
         L.off_model = o; o = align_up(o + sizeof(double) * 4 * 4 * (size_t)G.Sa);
+        L.off_pad = o;
+        if (G.Nf != G.N) o = align_up(o + sizeof(double) * (size_t)nsrc * (size_t)G.Nf);
     }
     if (which == 1) {
         L.off_part2 = o; o = align_up(o + sizeof(double) * (size_t)nsrc * nslots);
@@ -234,6 +270,7 @@ void bind_workspace(tt::Plan& P, void* ws, const Layout& L) {
     P.bnd_rhs = P.bnd_in + (size_t)P.nsrc * (size_t)P.G.NB;
     P.bnd_rec = reinterpret_cast<double2*>(b + L.off_bndrec);
     P.model = reinterpret_cast<double*>(b + L.off_model);
+    P.pad = reinterpret_cast<double*>(b + L.off_pad);
     P.T.t0 = P.tab0;
     P.T.t1 = P.tab1;
     P.T.t2 = P.tab2;
@@ -509,6 +546,13 @@ size_t grouped_total(const tt::Geo& G, int nsrc, int groups, int which, bool com
 
 bool compact_of(const tt_opts* o) { return o && (o->flags & TT_FLAG_COMPACT_ADJOINT); }
 
+// the default number of groups, or as many as a workspace sized for another batch holds
+int fit_groups(const tt::Geo& G, int nsrc, int groups, int which, size_t ws_bytes, const tt_opts* o) {
+    while (groups > 1 && !(o->groups > 0) && ws_bytes < grouped_total(G, nsrc, groups, which, which == 1 && compact_of(o)))
+        --groups;
+    return groups;
+}
+
 // Plans of the groups of a solve, bound to consecutive workspace regions, with
 // their streams made to wait for the work already queued on the caller's stream.
 int make_groups(const tt::Geo& G, int nsrc, int groups, int which, void* ws, size_t ws_bytes, const tt_opts* opts,
@@ -586,7 +630,7 @@ int check_ptrs(std::initializer_list<const void*> ps) {
 // Forward solve on a workspace that the caller checked (tt_forward) or the
 // scratch array provides (tt_forward_noalloc, one source group); the plan
 // checks are done by the callers.
-int forward_run(const tt::Geo& G, const double* s, const double* xi, const double* eta, int32_t nsrc,
+int forward_run(const tt::Geo& G, bool lines, const double* s, const double* xi, const double* eta, int32_t nsrc,
                 const double* src_pos, const double* src_par, const double* tau_init, const tt_opts* opts, double* tau,
                 int32_t* status, void* ws, size_t ws_bytes, int groups, hipStream_t caller) {
     int rc = TT_OK;
@@ -600,7 +644,7 @@ int forward_run(const tt::Geo& G, const double* s, const double* xi, const doubl
         if (opts->flags & TT_FLAG_TIME_SWEEPS) g.P.timing = &ev;
         tt::launch_tables(g.P, g.st);
         tt::launch_src_setup(g.P, src_pos + 3LL * q0, src_par + 3LL * q0, g.st);
-        g.a = tt::make_args(g.P, s, xi, eta, tau + (long long)q0 * G.N, status + q0);
+        g.a = tt::make_args(g.P, s, xi, eta, lines ? g.P.pad : tau + (long long)q0 * G.N, status + q0);
         tt::launch_fwd_init(g.P, g.a, tau_init ? tau_init + (long long)q0 * G.N : nullptr, s, xi, eta, g.st);
     }
     TT_HIP(hipGetLastError());
@@ -609,6 +653,10 @@ int forward_run(const tt::Geo& G, const double* s, const double* xi, const doubl
     auto one = [&](Group& g, hipStream_t s_) { tt::launch_fwd_iteration(g.P, g.a, s_); };
     rc = polled ? run_polled(gs, graph, one) : run_async(gs, graph, one);
     collect_timing(ev, 0);
+    if (rc == TT_OK && lines) {
+        for (int q = 0; q < groups; ++q) tt::launch_unpad(gs[q].P, tau + (long long)group_begin(nsrc, groups, q) * G.N, gs[q].st);
+        TT_HIP(hipGetLastError());
+    }
     if (rc == TT_OK) rc = finish_groups(gs, caller, polled);
     return rc;
 }
@@ -671,6 +719,10 @@ size_t tt_workspace_size(const tt_grid* grid, int32_t nsrc, const tt_opts* opts,
     if (opts && (opts->groups < 0 || opts->groups > TT_MAX_GROUPS)) return 0;
     if (opts && (opts->tile_k < 0 || opts->tile_k > tt::kMaxTileK)) return 0;
     tt::Geo G = make_geo(grid, tile_k_of(opts, which, grid, nsrc));
+    // (at any tile depth: a workspace serves calls that differ in it)
+    if (which == 0 && lines_of(grid, nsrc))
+        return std::max(grouped_total(padded(G), nsrc, groups_of(opts, grid, nsrc, 0, true), 0),
+                        grouped_total(G, nsrc, groups_of(opts, grid, nsrc, 0), 0));
     return grouped_total(G, nsrc, which <= 1 ? groups_of(opts, grid, nsrc, which) : 1, which, which == 1 && compact_of(opts));
 }
 
@@ -695,8 +747,15 @@ int tt_forward(const tt_grid* grid, const double* s, const double* xi, const dou
     tt::Geo G;
     int rc = forward_checks(grid, nsrc, opts, {s, xi, eta, src_pos, src_par, tau, status, ws}, &G);
     if (rc || nsrc == 0) return rc;
-    return forward_run(G, s, xi, eta, nsrc, src_pos, src_par, tau_init, opts, tau, status, ws, ws_bytes,
-                       groups_of(opts, grid, nsrc, 0), (hipStream_t)stream);
+    bool lines = opts->tile_k == 0 && lines_of(grid, nsrc);
+    int groups = groups_of(opts, grid, nsrc, 0, lines);
+    if (lines && ws_bytes < grouped_total(padded(G), nsrc, groups, 0)) {  // (solves in place)
+        lines = false;
+        groups = groups_of(opts, grid, nsrc, 0);
+    }
+    if (!lines) groups = fit_groups(G, nsrc, groups, 0, ws_bytes, opts);
+    return forward_run(lines ? padded(G) : G, lines, s, xi, eta, nsrc, src_pos, src_par, tau_init, opts, tau, status, ws,
+                       ws_bytes, groups, (hipStream_t)stream);
 }
 
 int tt_forward_noalloc(const tt_grid* grid, const double* s, const double* xi, const double* eta, int32_t nsrc,
@@ -715,8 +774,9 @@ int tt_forward_noalloc(const tt_grid* grid, const double* s, const double* xi, c
                                "%zu-byte scratch; use tt_forward with a caller workspace", need, kScratchBytes);
     void* ws = nullptr;
     if ((rc = scratch_ptr(&ws))) return rc;
-    return forward_run(G, s, xi, eta, nsrc, src_pos, src_par, tau_init, opts, tau, status, ws, kScratchBytes, 1,
-                       (hipStream_t)stream);
+    const bool lines = opts->tile_k == 0 && lines_of(grid, nsrc) && grouped_total(padded(G), nsrc, 1, 0) <= kScratchBytes;
+    return forward_run(lines ? padded(G) : G, lines, s, xi, eta, nsrc, src_pos, src_par, tau_init, opts, tau, status, ws,
+                       kScratchBytes, 1, (hipStream_t)stream);
 }
 
 size_t tt_forward_noalloc_limit(void) { return kScratchBytes; }
@@ -843,7 +903,7 @@ int tt_adjoint(const tt_grid* grid, const double* s, const double* xi, const dou
     if ((rc = check_ptrs({s, xi, eta, src_pos, src_par, tau, lam, status, ws}))) return rc;
     if (nrec > 0 && (!rec_pos || !R)) return fail(TT_EINVAL, "rec_pos/R NULL with nrec > 0");
     tt::Geo G = make_geo(grid, tile_k_of(opts, 1, grid, nsrc));
-    const int groups = groups_of(opts, grid, nsrc, 1);
+    const int groups = fit_groups(G, nsrc, groups_of(opts, grid, nsrc, 1), 1, ws_bytes, opts);
     hipStream_t caller = (hipStream_t)stream;
     std::vector<Group> gs;
     if ((rc = make_groups(G, nsrc, groups, 1, ws, ws_bytes, opts, caller, gs))) return rc;

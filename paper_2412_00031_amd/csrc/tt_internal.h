@@ -35,7 +35,8 @@ struct Geo {
     int tk;            // hyperplane steps of a tile (its extent along u = i' + j' + k')
     int ncols;         // tile columns: nt0 * nt1
     long long N;       // n0 * n1 * n2
-    long long si, sj;  // strides of axes 0 and 1 (axis 2 has stride 1)
+    long long si, sj;  // strides of axes 0 and 1 of the solution fields (axis 2 has stride 1)
+    long long Nf;      // elements of a solution field: N, or more if its rows are padded to whole lines
     long long NB;      // boundary nodes
     int W;             // n1 + n2 - 1: width of the row-coalesced layouts
     int n1p;           // aligned layouts: row pitch (a multiple of 8 records, >= n1 + 7)
@@ -382,6 +383,7 @@ struct Plan {
     double* rhs = nullptr;    // adjoint: right-hand side divided by the diagonal [nsrc][N]
     int* box = nullptr;       // adjoint: index box of each source's nonzero rhs [nsrc][6]
     double* model = nullptr;  // forward: [4][Sa][4] = (s, 1 - 2 xi, 2 eta, 1 + 2 xi) (aligned row-coalesced layouts)
+    double* pad = nullptr;    // forward: the solution fields with padded rows, [nsrc][Nf], if Nf != N
     double* bnd_in = nullptr; // adjoint: [nsrc][NB] (continuous adjoint: boundary pass scratch)
     double* bnd_rhs = nullptr; // adjoint: right-hand side of the boundary nodes, [nsrc][NB]
     double2* bnd_rec = nullptr;  // continuous adjoint: the boundary nodes' records, [nsrc][3][NB]
@@ -434,6 +436,7 @@ void launch_fwd_iteration(const Plan& P, const SweepArgs& a, hipStream_t st);
 void launch_adj_init(const Plan& P, const SweepArgs& a, const double* tau, int nrec, const double* rec_pos,
                      const double* R, const double* init, hipStream_t st);
 void launch_adj_iteration(const Plan& P, const SweepArgs& a, hipStream_t st);
+void launch_unpad(const Plan& P, double* tau, hipStream_t st);
 void launch_cadj_scale(const Plan& P, const double* s, double* lam, hipStream_t st);
 void launch_sample(const Plan& P, const double* tau, int nrec, const double* rec_pos, double* out,
                    hipStream_t st);

@@ -171,14 +171,14 @@ __global__ void k_fill(double* __restrict__ p, long long n, double v) {
 __global__ void k_solve_init(SweepArgs a, const double* init, double v0, double vfix) {
     const int src = blockIdx.y;
     const Src S = a.src[src];
-    double* f = a.field + (long long)src * a.G.N;
+    double* f = a.field + (long long)src * a.G.Nf;
     const double* ti = init ? init + (long long)src * a.G.N : nullptr;
     for (long long x = (long long)blockIdx.x * blockDim.x + threadIdx.x; x < a.G.N;
          x += (long long)gridDim.x * blockDim.x) {
         const int k = (int)(x % a.G.n[2]);
         const long long q = x / a.G.n[2];
         const int j = (int)(q % a.G.n[1]), i = (int)(q / a.G.n[1]);
-        f[x] = in_fixed(S, i, j, k) ? vfix : (ti ? ti[x] : v0);
+        f[nidx(a.G, i, j, k)] = in_fixed(S, i, j, k) ? vfix : (ti ? ti[x] : v0);
     }
     // sums, sweep progress and queue words start at zero
     for (long long x = (long long)blockIdx.x * blockDim.x + threadIdx.x; x < a.nslots;
@@ -208,9 +208,9 @@ struct Dir {
 };
 
 struct TileCtx {
-    int TI, TJ, TK, lane, li, lj, ext_i, ext_j;
+    int TI, TJ, U0, lane, li, lj, ext_i, ext_j;
     int ip, jp;    // this lane's column (sweep-relative; the tile corner's if the lane owns none)
-    int t0, t1;    // wave-uniform walk: steps t0 <= t < t1 (u = TK tk + t)
+    int t0, t1;    // wave-uniform walk: steps t0 <= t < t1 (u = U0 + t)
     int kp0;       // this lane's k' at step 0 (k' = kp0 + t)
     int kplo, kphi;  // record fetch clamp: this lane's k' range in the tile (a valid k' if empty)
     int kq0;       // staged entry (ci, cj, kk) holds k' = kq0 - ci - cj + kk
@@ -254,21 +254,24 @@ __device__ __forceinline__ TileCtx col_ctx(const Geo& G, const Src& S, int TI, i
     return c;
 }
 
-// the slab's part
-template <int DIR>
-__device__ __forceinline__ void slab_ctx(const Geo& G, const Src& S, TileCtx& c, int TK) {
+// the slab's part; HELD: records are fetched past the slab's end, for the next one
+template <int DIR, bool HELD = false>
+__device__ __forceinline__ void slab_ctx(const Geo& G, const Src& S, TileCtx& c, int U0, int depth) {
     using D = Dir<DIR>;
-    c.TK = TK;
-    const int U0 = TK * G.tk;
+    c.U0 = U0;
     const int ucol = kBI * (c.TI + c.TJ);  // u of the column's first node (i', j' at the tile corner, k' = 0)
     c.t0 = max(0, ucol - U0);
-    c.t1 = min(G.tk, ucol + (c.ext_i - 1) + (c.ext_j - 1) + G.m[2] - U0);
+    c.t1 = min(depth, ucol + (c.ext_i - 1) + (c.ext_j - 1) + G.m[2] - U0);
     c.kp0 = U0 - c.ip - c.jp;
     // prefetches past the walk re-read the lane's last record of this tile
     // (a cache hit) instead of the next slab's
     c.kplo = max(0, c.kp0 + c.t0);
     c.kphi = min(G.m[2] - 1, c.kp0 + c.t1 - 1);
     if (c.kplo > c.kphi) c.kplo = c.kphi = min(max(c.kp0 + c.t0, 0), G.m[2] - 1);
+    if (HELD) {
+        c.kplo = 0;
+        c.kphi = G.m[2] - 1;
+    }
     c.kq0 = U0 - ucol + 1;
     c.rr0 = c.rbase + c.rstep * c.kp0;
     c.tt0 = c.kbase + D::s2 * c.kp0;
@@ -417,8 +420,17 @@ __device__ __forceinline__ void march(const SweepArgs& a, const Geo& G, int c0, 
     }
 }
 
+struct Handover {
+    const unsigned long long* up;  // this lane's upstream column's progress word or NULL
+    unsigned long long target;     // what it must have reached
+    unsigned long long* own;       // this column's word, and its value when the slab is done
+    unsigned long long done;
+    bool more;                     // another slab follows
+};
+
 // March one tile column: tile(TK) for every slab in order, each after its wait.
-template <int DIR, class F>
+// HELD: the tile publishes its slab itself.
+template <int DIR, bool HELD, class F>
 __device__ __forceinline__ bool march_column(const SweepArgs& a, const Geo& G, int src, int TI, int TJ, F tile) {
     unsigned long long* prog = progress_words(a, src);
     unsigned long long* own = prog + TI * G.nt[1] + TJ;
@@ -431,8 +443,9 @@ __device__ __forceinline__ bool march_column(const SweepArgs& a, const Geo& G, i
     const int hi = col_tile_hi(G, TI + TJ);
     bool ok = true;
     for (int TK = col_tile_lo(G, TI + TJ); TK <= hi; ++TK) {
-        ok = tile(TK, up, base + TK + 1) && ok;
-        publish(own, TK < hi ? base + TK + 1 : base + 0xffffu);
+        const unsigned long long done = TK < hi ? base + TK + 1 : base + 0xffffu;
+        ok = tile(TK, Handover{up, base + TK + 1, own, done, TK < hi}) && ok;
+        if (!HELD) publish(own, done);
     }
     return ok;
 }
@@ -623,6 +636,178 @@ __device__ __forceinline__ void fwd_kface_nodes(const Geo& G, const Src& S, cons
     }
 }
 
+// ------------------------------------------------ windows held across slabs
+// The forward sweeps at a depth of 16 steps keep their window between the slabs
+// of a column instead of staging it anew.  While slab TK is walked, the entries
+// that slab TK + 1 adds -- kk = 2 .. tk + 1 of the tile's own columns and of the
+// downstream halo, which no other wave touches before this one has passed TK --
+// are loaded into registers; the two entries that the slabs share are carried in
+// a register pair; and what is left to load after the wait is the upstream halo,
+// two loads.  A walked slab's downstream edges (li = 7, lj = 7) are stored first
+// and published when they have arrived; the rest of the tile follows without a
+// wait.  The record ring runs on from slab to slab.
+//
+// Why: a batch that does not fill the chip waits for the hand-over from column to
+// column, and staging and the wait for all stores were part of it.  Staged and
+// held: 41^3 x 1 source 10.5 / 8.9 ms, 61^3 x 1 23.1 / 19.7, x 4 28.6 / 24.3, x 16
+// 32.6 / 28.2, x 32 38.0 / 34.3.  (The adjoint, whose steps are a quarter as long,
+// lost by it: 41^3 x 1 11.0 / 11.7, 61^3 x 32 56.6 / 59.6.)
+typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));   // two doubles at any element of a field
+typedef double d2a __attribute__((ext_vector_type(2), aligned(16)));  // a slot pair in LDS
+
+template <int DIR, int TKC>
+struct Window {
+    static constexpr int sg = Dir<DIR>::s2;
+    static constexpr int Lp = TKC + 2;         // = tile_pitch(TKC)
+    static constexpr int pairs = TKC / 2;      // lanes of a column: one slot pair each
+    static constexpr int cpl = 64 / pairs;     // columns per load
+    static constexpr int nload = 80 / cpl;     // loads of the own columns (64) and the downstream halo (16)
+    static constexpr int nhalo = 16 / cpl;     // loads of the upstream halo
+    static_assert(cpl == 8, "a row of columns per load");
+    // column (ci, cj) of load r on this lane
+    static __device__ __forceinline__ void col(int r, int sub, int& ci, int& cj) {
+        ci = r < 9 ? r + 1 : sub + 1;
+        cj = r < 9 ? sub + 1 : kTC - 1;
+    }
+    static __device__ __forceinline__ void halo_col(int r, int sub, int& ci, int& cj) {
+        const int n = r * cpl + sub;
+        ci = n < 8 ? 0 : n - 7;
+        cj = n < 8 ? n + 1 : 0;
+    }
+};
+
+// (or what follows from the lane number alone is kept for the whole kernel, in scratch)
+__device__ __forceinline__ int opaque_lane(const TileCtx& c) {
+    int lane = c.lane;
+    asm volatile("" : "+v"(lane));
+    return lane;
+}
+
+// The element of fld that entry kk = 0 of column (ci, cj) = (0, 0) would have:
+// entry kk of (ci, cj) is at org + ci A + cj B + s2 kk, A = s0 si - s2, B = s1 sj - s2.
+template <int DIR>
+__device__ __forceinline__ unsigned win_org(const Geo& G, const TileCtx& c, int kq0) {
+    using D = Dir<DIR>;
+    return (unsigned)stage_origin<D::s0>(G, 0, c.TI) * (unsigned)(int)G.si +
+           (unsigned)stage_origin<D::s1>(G, 1, c.TJ) * (unsigned)(int)G.sj + (unsigned)(c.kbase + D::s2 * kq0);
+}
+
+// Addresses are clamped into the array and columns to the ragged tile's halo
+// instead of being skipped (what they then load is never read), so that no
+// branch encloses a load.
+template <int DIR, int TKC>
+__device__ __forceinline__ d2u win_pair(const Geo& G, const TileCtx& c, const double* __restrict__ fld, int lo, int hi,
+                                        unsigned org, int ci, int cj, int kk) {
+    using D = Dir<DIR>;
+    const unsigned A = (unsigned)(D::s0 * (int)G.si - D::s2), B = (unsigned)(D::s1 * (int)G.sj - D::s2);
+    const unsigned x = org + (unsigned)min(ci, c.ext_i + 1) * A + (unsigned)min(cj, c.ext_j + 1) * B +
+                       (unsigned)(D::s2 * kk);
+    return *reinterpret_cast<const d2u*>(fld + min(max((int)x, lo), hi));
+}
+
+// loads R0 .. R1 - 1 of the entries that the slab at kq0 adds
+template <int DIR, int TKC, int R0, int R1>
+__device__ __forceinline__ void win_load(const Geo& G, const TileCtx& c, const double* __restrict__ fld, int lo, int hi,
+                                         int kq0, d2u (&pf)[Window<DIR, TKC>::nload]) {
+    using W = Window<DIR, TKC>;
+    const int lane = opaque_lane(c);
+    const int sub = lane / W::pairs, q = 2 * (lane % W::pairs);
+    const unsigned org = win_org<DIR>(G, c, kq0);
+#pragma unroll
+    for (int r = R0; r < R1; ++r) {
+        int ci, cj;
+        W::col(r, sub, ci, cj);
+        // slots q + 2, q + 3 hold entries q + 2, q + 3; mirrored, slots q, q + 1 hold Lp - 1 - q and the one below
+        pf[r] = win_pair<DIR, TKC>(G, c, fld, lo, hi, org, ci, cj, W::sg > 0 ? q + 2 : W::Lp - 1 - q);
+    }
+}
+
+template <int DIR, int TKC>
+__device__ __forceinline__ void win_put(const TileCtx& c, double* lds, const d2u (&pf)[Window<DIR, TKC>::nload]) {
+    using W = Window<DIR, TKC>;
+    const int lane = opaque_lane(c);
+    const int sub = lane / W::pairs, q = 2 * (lane % W::pairs);
+#pragma unroll
+    for (int r = 0; r < W::nload; ++r) {
+        int ci, cj;
+        W::col(r, sub, ci, cj);
+        *reinterpret_cast<d2a*>(lds + (ci * kTC + cj) * W::Lp + (W::sg > 0 ? q + 2 : q)) = pf[r];
+    }
+}
+
+// the upstream halo's entries 0 .. tk - 1
+template <int DIR, int TKC>
+__device__ __forceinline__ void win_halo(const Geo& G, const TileCtx& c, const double* __restrict__ fld, int lo, int hi,
+                                         double* lds) {
+    using W = Window<DIR, TKC>;
+    const int lane = opaque_lane(c);
+    const int sub = lane / W::pairs, q = 2 * (lane % W::pairs);
+    const unsigned org = win_org<DIR>(G, c, c.kq0);
+    d2u v[W::nhalo];
+#pragma unroll
+    for (int r = 0; r < W::nhalo; ++r) {
+        int ci, cj;
+        W::halo_col(r, sub, ci, cj);
+        v[r] = win_pair<DIR, TKC>(G, c, fld, lo, hi, org, ci, cj, W::sg > 0 ? q : W::Lp - 3 - q);
+    }
+#pragma unroll
+    for (int r = 0; r < W::nhalo; ++r) {
+        int ci, cj;
+        W::halo_col(r, sub, ci, cj);
+        *reinterpret_cast<d2a*>(lds + (ci * kTC + cj) * W::Lp + (W::sg > 0 ? q : q + 2)) = v[r];
+    }
+}
+
+// entries 0 and 1 of this lane's own column, as its slot pair: slots 0, 1 or, mirrored, Lp - 2, Lp - 1
+template <int DIR, int TKC>
+__device__ __forceinline__ d2u win_first(const Geo& G, const TileCtx& c, const double* __restrict__ fld, int lo, int hi) {
+    return win_pair<DIR, TKC>(G, c, fld, lo, hi, win_org<DIR>(G, c, c.kq0), c.li + 1, c.lj + 1, Dir<DIR>::s2 > 0 ? 0 : 1);
+}
+
+// the slab's last two entries, which are the next one's entries 0 and 1
+template <int DIR, int TKC>
+__device__ __forceinline__ d2u win_carry(const double* lds, int own) {
+    return *reinterpret_cast<const d2a*>(lds + own + (Dir<DIR>::s2 > 0 ? TKC : 0));
+}
+template <int DIR, int TKC>
+__device__ __forceinline__ void win_put_first(double* lds, int own, d2u v) {
+    *reinterpret_cast<d2a*>(lds + own + (Dir<DIR>::s2 > 0 ? 0 : TKC)) = v;
+}
+
+// Stores nodes of the walked slab (entries 1 .. tk): EDGES, the columns li = 7
+// and lj = 7, or all others.  E entries of 64 / E columns go out per store.
+template <int DIR, int TKC, bool EDGES>
+__device__ __forceinline__ void win_store(const Geo& G, const TileCtx& c, double* __restrict__ fld, const double* lds) {
+    using D = Dir<DIR>;
+    using W = Window<DIR, TKC>;
+    constexpr int E = TKC < 16 ? TKC : 16, cps = 64 / E, per = 8 / cps;
+    const int lane = opaque_lane(c);
+    const int sub = lane / E, r = lane % E;
+    const unsigned A = (unsigned)(D::s0 * (int)G.si - D::s2), B = (unsigned)(D::s1 * (int)G.sj - D::s2);
+    const unsigned kmax = (unsigned)G.m[2];
+#pragma unroll
+    for (int ch = 0; ch < TKC; ch += E) {
+        const int kk = ch + r + 1;
+        const unsigned org = win_org<DIR>(G, c, c.kq0) + (unsigned)(W::sg * kk);
+        const int kp = c.kq0 + kk, slot = W::sg > 0 ? kk : W::Lp - 1 - kk;
+        constexpr int n = EDGES ? 2 * per : 7 * per;
+        double v[n];
+        int ci[n], cj[n];
+#pragma unroll
+        for (int u = 0; u < n; ++u) {
+            const int h = (u % per) * cps + sub + 1;
+            ci[u] = EDGES ? (u < per ? kBI : h) : u / per + 1;
+            cj[u] = EDGES ? (u < per ? h : kBJ) : h;
+            v[u] = lds[(ci[u] * kTC + cj[u]) * W::Lp + slot];
+        }
+#pragma unroll
+        for (int u = 0; u < n; ++u)
+            if (ci[u] <= c.ext_i && cj[u] <= c.ext_j && (EDGES || cj[u] < kBJ) && (!EDGES || u < per || ci[u] < kBI) &&
+                (unsigned)(kp - ci[u] - cj[u]) < kmax)
+                fld[(int)(org + (unsigned)ci[u] * A + (unsigned)cj[u] * B)] = v[u];
+    }
+}
+
 // The per-node records a step needs (model, table) are loaded kPre steps
 // ahead into a ring slot indexed by the wave-uniform step number.
 constexpr int kPre = 4;       // forward: steps are long (the full update)
@@ -651,74 +836,378 @@ __device__ __forceinline__ void fwd_fetch(const TileCtx& c, const double* __rest
     r.s2 = tv.y;
 }
 
-// TKC: the tile depth as a compile-time constant (0: read from the geometry),
-// so that LDS offsets become immediates and the staging and write-back index
-// arithmetic folds; the host picks an instance whose TKC equals the depth.
-template <int COORD, int DIR, int TKC>
-__global__ void __launch_bounds__(64, 3) k_fwd_sweep(SweepArgs a, int c0, int cn) {
+// One step of the forward walk at step t of the slab.  No step has a branch:
+// every lane forms an update, one that has none to make stores it into the
+// window's corner column, which nothing reads.  So the factor of one step fills
+// the waits of the step before: 553 cycles a step of a lone wave with a branch
+// around each update.
+// HELD: t is below the window's depth, so that the corner column has the slot.
+template <int COORD, int DIR, bool HELD>
+__device__ __forceinline__ void fwd_step(const Src& S, const LfCol& W, const TileCtx& c, double* lds, int own, int Lp,
+                                         int t, const FwdSlot& r, double& eps) {
     using D = Dir<DIR>;
-    extern __shared__ double lds[];
-    Geo G = a.G;
-    if (TKC > 0) G.tk = TKC;
+    // sweep-relative neighbours: "up" = already updated this sweep
+    // slot of entry t (mirrored columns when s2 < 0): entry t + 1 is at o + s2
+    constexpr int sg = D::s2;
+    const int o = sg > 0 ? own + t : own + Lp - 1 - t;
+    const double cur = lds[o + sg];
+    const double up_i = lds[o - kTC * Lp], dn_i = lds[o + kTC * Lp + 2 * sg];
+    const double up_j = lds[o - Lp], dn_j = lds[o + Lp + 2 * sg];
+    const double up_k = lds[o], dn_k = lds[o + 2 * sg];
+    const double m0 = D::s0 > 0 ? up_i : dn_i, p0 = D::s0 > 0 ? dn_i : up_i;
+    const double m1 = D::s1 > 0 ? up_j : dn_j, p1 = D::s1 > 0 ? dn_j : up_j;
+    const double m2 = D::s2 > 0 ? up_k : dn_k, p2 = D::s2 > 0 ? dn_k : up_k;
+    const double nv = lf_update<COORD>(S, W, r.c2, r.s2, r.sx, r.ma, r.mb, r.mc, cur, m0, p0, m1, p1, m2, p2);
+    const bool on = step_on(c, t);
+    lds[HELD ? (on ? own : 0) + (sg > 0 ? t + 1 : Lp - 2 - t) : (on ? o + sg : 0)] = nv;
+    eps += on ? fabs(nv - cur) : 0.0;
+}
+
+// One column with its window held across slabs, records in a register ring that
+// runs on from slab to slab.
+template <int COORD, int DIR, int TKC>
+__device__ __forceinline__ void fwd_column(const SweepArgs& a, const Geo& G, int src, int TI, int TJ, double* lds) {
+    using D = Dir<DIR>;
+    using Win = Window<DIR, TKC>;
+    constexpr int ng = TKC / kPre, nl = Win::nload;
     const double* __restrict__ mdl = a.model + (long long)D::lay * G.Sa * 4;
     const double2* __restrict__ t2 = a.T.t2;
-    const int Lp = tile_pitch(G.tk);
-    march(a, G, c0, cn, [&](int src, int TI, int TJ) {
-        const Src S = a.src[src];
-        TileCtx c = col_ctx<DIR>(G, S, TI, TJ);
-        const Col cl = make_col(G, a.T, c.i, c.j);
-        const LfCol W = lf_col<COORD>(G, S, cl, a.kappa);
-        double* __restrict__ fld = a.field + (long long)src * G.N;
-        const int own = ((c.li + 1) * kTC + c.lj + 1) * Lp;
-        double eps = 0.0;
-        const bool ok = march_column<DIR>(a, G, src, TI, TJ, [&](int TK, const unsigned long long* up, unsigned long long target) {
-            slab_ctx<DIR>(G, S, c, TK);
-            if (c.t1 <= c.t0) return true;  // a ragged column's slab with no nodes
-            FwdSlot ring[kPre];
+    const Src S = a.src[src];
+    TileCtx c = col_ctx<DIR>(G, S, TI, TJ);
+    const Col cl = make_col(G, a.T, c.i, c.j);
+    const LfCol W = lf_col<COORD>(G, S, cl, a.kappa);
+    double* __restrict__ fld = a.field + (long long)src * G.N;
+    const long long xlo = -(long long)src * G.N, xhi = (long long)(a.nsrc - src) * G.N - 2;
+    const int lo = (int)(xlo > -1 ? xlo : -1), hi = (int)(xhi < G.N ? xhi : G.N);
+    int own = ((c.li + 1) * kTC + c.lj + 1) * Win::Lp;
+    double eps = 0.0;
+    FwdSlot ring[kPre];
+    d2u pf[nl], first;
+    slab_ctx<DIR, true>(G, S, c, col_tile_lo(G, TI + TJ) * TKC, TKC);
+    win_load<DIR, TKC, 0, nl>(G, c, fld, lo, hi, c.kq0, pf);
+    first = win_first<DIR, TKC>(G, c, fld, lo, hi);
 #pragma unroll
-            for (int u = 0; u < kPre; ++u) fwd_fetch<DIR>(c, mdl, t2, c.t0 + u, ring[u]);
-            const bool waited = wait_upstream(up, target);
-            stage_tile<DIR>(G, c, fld, -(long long)src * G.N, (long long)(a.nsrc - src) * G.N - 2, lds);
-            __syncthreads();
-
-            // The step count is padded to a multiple of kPre and no step has a branch:
-            // every lane forms an update, one that has none to make stores it into the
-            // window's corner column, which nothing reads.  (The LDS reads of a padded
-            // step stay inside the window: at most 3 entries past a column that others
-            // follow.)  So the factor of one step fills the waits of the step before:
-            // 553 cycles a step of a lone wave with a branch around each update.
-            for (int tb = c.t0; tb < c.t1; tb += kPre) {
+    for (int u = 0; u < kPre; ++u) fwd_fetch<DIR>(c, mdl, t2, c.t0 + u, ring[u]);
+    const bool ok = march_column<DIR, true>(a, G, src, TI, TJ, [&](int TK, const Handover& h) {
+        slab_ctx<DIR, true>(G, S, c, TK * TKC, TKC);
+        if (c.t1 <= c.t0) {  // a ragged column's slab with no nodes
+            publish(h.own, h.done);
+            return true;
+        }
+        win_put<DIR, TKC>(c, lds, pf);
+        win_put_first<DIR, TKC>(lds, own, first);
+        const bool waited = wait_upstream(h.up, h.target);
+        win_halo<DIR, TKC>(G, c, fld, lo, hi, lds);
+        __syncthreads();
+        // t0 is a multiple of 8, and so of a group's steps; steps past t1 are off
+        auto group = [&](auto gc) {
+            constexpr int g = decltype(gc)::value;
+            asm volatile("" : "+v"(c.rr0), "+v"(c.tt0), "+v"(own));  // (or the addresses of all groups are formed at once)
+            // loads return in order: the next window's, from memory, go out together in front of
+            // one group's record loads, so that the records wait for them once a slab
+            if (g == 0 && h.more) win_load<DIR, TKC, 0, nl>(G, c, fld, lo, hi, c.kq0 + TKC, pf);
+            if (g * kPre < c.t0 || g * kPre >= c.t1) return;
 #pragma unroll
-                for (int u = 0; u < kPre; ++u) {
-                    const int t = tb + u;
-                    FwdSlot& r = ring[u];
-                    // sweep-relative neighbours: "up" = already updated this sweep
-                    // slot of entry t (mirrored columns when s2 < 0): entry t + 1 is at o + s2
-                    constexpr int sg = D::s2;
-                    const int o = sg > 0 ? own + t : own + Lp - 1 - t;
-                    const double cur = lds[o + sg];
-                    const double up_i = lds[o - kTC * Lp], dn_i = lds[o + kTC * Lp + 2 * sg];
-                    const double up_j = lds[o - Lp], dn_j = lds[o + Lp + 2 * sg];
-                    const double up_k = lds[o], dn_k = lds[o + 2 * sg];
-                    const double m0 = D::s0 > 0 ? up_i : dn_i, p0 = D::s0 > 0 ? dn_i : up_i;
-                    const double m1 = D::s1 > 0 ? up_j : dn_j, p1 = D::s1 > 0 ? dn_j : up_j;
-                    const double m2 = D::s2 > 0 ? up_k : dn_k, p2 = D::s2 > 0 ? dn_k : up_k;
-                    const double nv = lf_update<COORD>(S, W, r.c2, r.s2, r.sx, r.ma, r.mb, r.mc, cur, m0, p0, m1, p1,
-                                                       m2, p2);
-                    const bool on = step_on(c, t);
-                    lds[on ? o + sg : 0] = nv;
-                    eps += on ? fabs(nv - cur) : 0.0;
-                    fwd_fetch<DIR>(c, mdl, t2, t + kPre, r);
-                }
+            for (int u = 0; u < kPre; ++u) {
+                fwd_step<COORD, DIR, true>(S, W, c, lds, own, Win::Lp, g * kPre + u, ring[u], eps);
+                fwd_fetch<DIR>(c, mdl, t2, g * kPre + u + kPre, ring[u]);
             }
-            __syncthreads();
-            unstage_tile<DIR>(G, c, fld, lds, Lp);
-            fwd_kface_nodes<DIR>(G, S, c, fld, lds, own, Lp, eps);
-            return waited;
-        });
-        eps = wave_sum(ok ? eps : HUGE_VAL);
-        if (c.lane == 0) part_add(a.part + (long long)src * a.nslots + TI * G.nt[1] + TJ, DIR, eps);
+        };
+        static_assert(ng == 4, "groups of a slab");
+        group(std::integral_constant<int, 0>{});
+        group(std::integral_constant<int, 1>{});
+        group(std::integral_constant<int, 2>{});
+        group(std::integral_constant<int, 3>{});
+        __syncthreads();
+        first = win_carry<DIR, TKC>(lds, own);
+        win_store<DIR, TKC, true>(G, c, fld, lds);
+        publish(h.own, h.done);
+        win_store<DIR, TKC, false>(G, c, fld, lds);
+        fwd_kface_nodes<DIR>(G, S, c, fld, lds, own, Win::Lp, eps);
+        __syncthreads();
+        return waited;
     });
+    eps = wave_sum(ok ? eps : HUGE_VAL);
+    if (c.lane == 0) part_add(a.part + (long long)src * a.nslots + TI * G.nt[1] + TJ, DIR, eps);
+}
+
+// ------------------------------------------------------- windows of whole lines
+// What a batch that fills the chip waits for is lines: a column's segment of a
+// slab lies across two 128-byte lines or more, and the L2 has turned over before
+// the next slab wants the last one again (24 sweeps of 128 sources of 101^3 in
+// slabs of 28 steps read 5.6e8 lines from beyond the L2s, the fields have 2.0e8;
+// whole lines 3.6e8).  Here the field lives in the workspace with its rows padded
+// to whole lines (G.sj nodes a row), and a column's window is two of them.  Which
+// batches gain by it: lines_of.
+//
+// Let kappa be a node's place in its row, counted in the sweep's direction: the
+// element itself (s2 > 0) or G.sj - 1 minus it, kappa = k' + delta.  Line m of a
+// column holds kappa in [16 m, 16 m + 16).  Walk m takes lane (li, lj) over
+// kappa = 16 m - 1 - li - lj + t, t = 0 .. 15: with the neighbours at kappa - 1
+// and kappa + 1 all lanes stay in [16 m - 16, 16 m + 16), lines m - 1 and m.  After
+// it line m - 1 is final in all columns and goes out whole; line m + 1, loaded
+// during the walk, takes its place.  kappa is the same for a tile and its
+// neighbours: walk m needs line m of the upstream halo, final after walk m + 1
+// over there.
+//
+// In LDS column (ci, cj) has 32 slots at 324 ci + 32 cj, kappa in slot kappa % 32
+// (s2 < 0: 31 minus that, so that pairs keep the order of memory); 324 spreads
+// the lanes' slots over the banks.  A lane's own value at kappa and the one
+// below stay in registers from step to step.
+constexpr int kLine = 16;
+constexpr int kLineRow = 324;
+constexpr int kLinesLds = kTC * kLineRow * 8;
+
+template <int DIR>
+__device__ __forceinline__ int line_slot(int kap) {
+    return Dir<DIR>::s2 > 0 ? kap & 31 : (31 - kap) & 31;
+}
+// first slot of line m, and its first element in a row
+template <int DIR>
+__device__ __forceinline__ int line_base(int m) {
+    return Dir<DIR>::s2 > 0 ? (m & 1) * kLine : (1 - (m & 1)) * kLine;
+}
+template <int DIR>
+__device__ __forceinline__ int line_elem(const Geo& G, int m) {
+    return Dir<DIR>::s2 > 0 ? m * kLine : (int)G.sj - kLine - m * kLine;
+}
+template <int DIR>
+__device__ __forceinline__ int line_addr(const Geo& G, const TileCtx& c, int ci, int cj) {
+    using D = Dir<DIR>;
+    return (stage_origin<D::s0>(G, 0, c.TI) + D::s0 * ci) * (int)G.si +
+           (stage_origin<D::s1>(G, 1, c.TJ) + D::s1 * cj) * (int)G.sj;
+}
+
+// loads R0 .. R1 - 1 of line m: eight columns of the tile and its downstream halo
+// each (columns past a ragged tile's halo re-read its last one)
+template <int DIR, int R0, int R1>
+__device__ __forceinline__ void line_load(const Geo& G, const TileCtx& c, const double* __restrict__ fld, int m,
+                                          d2a (&pf)[10]) {
+    const int lane = opaque_lane(c);
+    const int sub = lane >> 3, e = line_elem<DIR>(G, m) + 2 * (lane & 7);
+#pragma unroll
+    for (int r = R0; r < R1; ++r) {
+        int ci, cj;
+        Window<DIR, kLine>::col(r, sub, ci, cj);
+        pf[r] = *reinterpret_cast<const d2a*>(fld + line_addr<DIR>(G, c, min(ci, c.ext_i + 1), min(cj, c.ext_j + 1)) + e);
+    }
+}
+
+template <int DIR>
+__device__ __forceinline__ void line_put(const TileCtx& c, double* lds, int m, const d2a (&pf)[10]) {
+    const int lane = opaque_lane(c);
+    const int sub = lane >> 3, q = line_base<DIR>(m) + 2 * (lane & 7);
+#pragma unroll
+    for (int r = 0; r < 10; ++r) {
+        int ci, cj;
+        Window<DIR, kLine>::col(r, sub, ci, cj);
+        *reinterpret_cast<d2a*>(lds + ci * kLineRow + cj * 32 + q) = pf[r];
+    }
+}
+
+template <int DIR>
+__device__ __forceinline__ void line_halo(const Geo& G, const TileCtx& c, const double* __restrict__ fld, int m,
+                                          double* lds) {
+    const int lane = opaque_lane(c);
+    const int sub = lane >> 3, e = 2 * (lane & 7), h = sub + 1;
+    const d2a v0 = *reinterpret_cast<const d2a*>(fld + line_addr<DIR>(G, c, 0, min(h, c.ext_j + 1)) + line_elem<DIR>(G, m) + e);
+    const d2a v1 = *reinterpret_cast<const d2a*>(fld + line_addr<DIR>(G, c, min(h, c.ext_i + 1), 0) + line_elem<DIR>(G, m) + e);
+    const int q = line_base<DIR>(m) + e;
+    *reinterpret_cast<d2a*>(lds + h * 32 + q) = v0;
+    *reinterpret_cast<d2a*>(lds + h * kLineRow + q) = v1;
+}
+
+// line m of the own columns: EDGES, those with li = 7 or lj = 7, or all others
+template <int DIR, bool EDGES>
+__device__ __forceinline__ void line_store(const Geo& G, const TileCtx& c, double* __restrict__ fld, int m,
+                                           const double* lds) {
+    const int lane = opaque_lane(c);
+    const int h = (lane >> 3) + 1, e = 2 * (lane & 7), q = line_base<DIR>(m) + e;
+    constexpr int n = EDGES ? 2 : 7;
+    d2a v[n];
+#pragma unroll
+    for (int u = 0; u < n; ++u) {
+        const int ci = EDGES ? (u == 0 ? kBI : h) : u + 1, cj = EDGES ? (u == 0 ? h : kBJ) : h;
+        v[u] = *reinterpret_cast<const d2a*>(lds + ci * kLineRow + cj * 32 + q);
+    }
+#pragma unroll
+    for (int u = 0; u < n; ++u) {
+        const int ci = EDGES ? (u == 0 ? kBI : h) : u + 1, cj = EDGES ? (u == 0 ? h : kBJ) : h;
+        if (ci <= c.ext_i && cj <= c.ext_j && (EDGES ? u == 0 || ci < kBI : cj < kBJ))
+            *reinterpret_cast<d2a*>(fld + line_addr<DIR>(G, c, ci, cj) + line_elem<DIR>(G, m) + e) = v[u];
+    }
+}
+
+// the own columns' k-face nodes in line m copy their end nodes (fwd_kface_nodes)
+template <int DIR>
+__device__ __forceinline__ void line_kfaces(const Geo& G, const Src& S, const TileCtx& c, double* lds, int own, int m,
+                                            int delta, double& eps) {
+    using D = Dir<DIR>;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        const int kap = e == 0 ? delta - 1 : delta + G.m[2];
+        if (kap / kLine != m) continue;
+        const int kb = c.kbase + D::s2 * (e == 0 ? -1 : G.m[2]);  // absolute k of the boundary node
+        if (!c.colv || in_fixed(S, c.i, c.j, kb)) continue;
+        const double nv = lds[own + line_slot<DIR>(e == 0 ? kap + 1 : kap - 1)];
+        const double old = lds[own + line_slot<DIR>(kap)];
+        lds[own + line_slot<DIR>(kap)] = nv;
+        eps += fabs(nv - old);
+    }
+}
+
+template <int COORD, int DIR>
+__device__ __forceinline__ void fwd_line_column(const SweepArgs& a, const Geo& G, int src, int TI, int TJ, double* lds) {
+    using D = Dir<DIR>;
+    constexpr int ng = kLine / kPre;
+    const double* __restrict__ mdl = a.model + (long long)D::lay * G.Sa * 4;
+    const double2* __restrict__ t2 = a.T.t2;
+    const Src S = a.src[src];
+    TileCtx c = col_ctx<DIR>(G, S, TI, TJ);
+    const Col cl = make_col(G, a.T, c.i, c.j);
+    const LfCol W = lf_col<COORD>(G, S, cl, a.kappa);
+    double* __restrict__ fld = a.field + (long long)src * G.Nf;
+    const int delta = D::s2 > 0 ? 1 : (int)G.sj + 1 - G.n[2];
+    const int nlines = (int)G.sj / kLine, mhi = (G.m[2] + delta + c.ext_i + c.ext_j - 2) / kLine;
+    const int u0 = kBI * (TI + TJ) - 1 - delta;  // u of step t = 0 of walk 0
+    int own = (c.li + 1) * kLineRow + (c.lj + 1) * 32;
+    double eps = 0.0;
+    bool ok = true;
+    FwdSlot ring[kPre];
+    d2a pf[10];
+    slab_ctx<DIR, true>(G, S, c, u0, kLine);
+    line_load<DIR, 0, 10>(G, c, fld, 0, pf);
+    const int tf = (delta + 1) & ~(kPre - 1);  // the first group with a node, counted from walk 0
+#pragma unroll
+    for (int u = 0; u < kPre; ++u) fwd_fetch<DIR>(c, mdl, t2, tf + u, ring[u]);
+    unsigned long long* word = progress_words(a, src) + TI * G.nt[1] + TJ;
+    const unsigned long long* up = nullptr;
+    if (threadIdx.x == 0 && TI > 0) up = word - G.nt[1];
+    if (threadIdx.x == 1 && TJ > 0) up = word - 1;
+    // progress: (number of the sweep << 16) + lines that are final
+    const unsigned long long base = ((unsigned long long)a.iter[src] * 8 + DIR + 1) << 16;
+    for (int m = 0; m <= mhi; ++m) {
+        slab_ctx<DIR, true>(G, S, c, u0 + m * kLine, kLine);
+        if (m < nlines) {
+            line_put<DIR>(c, lds, m, pf);
+            ok = wait_upstream(up, base + m + 1) && ok;
+            line_halo<DIR>(G, c, fld, m, lds);
+        }
+        __syncthreads();
+        auto group = [&](auto gc) {
+            constexpr int g = decltype(gc)::value;
+            int kap = kLine * m - 1 - c.li - c.lj + g * kPre;
+            asm volatile("" : "+v"(c.rr0), "+v"(c.tt0), "+v"(own), "+v"(kap));  // (or the addresses of all groups are formed at once)
+            // together and ahead of a group's record loads, as in fwd_column
+            if (g == 0 && m + 1 < nlines) line_load<DIR, 0, 10>(G, c, fld, m + 1, pf);
+            if (g * kPre + kPre <= c.t0 || g * kPre >= c.t1) return;
+            double upk = lds[own + line_slot<DIR>(kap - 1)], cur = lds[own + line_slot<DIR>(kap)];
+            int at = own + line_slot<DIR>(kap);
+#pragma unroll
+            for (int u = 0; u < kPre; ++u) {
+                const int t = g * kPre + u;
+                FwdSlot& r = ring[u];
+                const int an = own + line_slot<DIR>(kap + u + 1);
+                const double dnk = lds[an];
+                const double up_i = lds[at - kLineRow], dn_i = lds[at + kLineRow];
+                const double up_j = lds[at - 32], dn_j = lds[at + 32];
+                const double m0 = D::s0 > 0 ? up_i : dn_i, p0 = D::s0 > 0 ? dn_i : up_i;
+                const double m1 = D::s1 > 0 ? up_j : dn_j, p1 = D::s1 > 0 ? dn_j : up_j;
+                const double m2 = D::s2 > 0 ? upk : dnk, p2 = D::s2 > 0 ? dnk : upk;
+                const double nv = lf_update<COORD>(S, W, r.c2, r.s2, r.sx, r.ma, r.mb, r.mc, cur, m0, p0, m1, p1, m2, p2);
+                const bool on = step_on(c, t);
+                lds[on ? at : 0] = nv;  // no branch in a step, as in fwd_step
+                eps += on ? fabs(nv - cur) : 0.0;
+                upk = on ? nv : cur;
+                cur = dnk;
+                at = an;
+                fwd_fetch<DIR>(c, mdl, t2, t + kPre, r);
+            }
+        };
+        static_assert(ng == 4, "groups of a walk");
+        group(std::integral_constant<int, 0>{});
+        group(std::integral_constant<int, 1>{});
+        group(std::integral_constant<int, 2>{});
+        group(std::integral_constant<int, 3>{});
+        const bool last = m == mhi, prev = m > 0, cur_too = last && m < nlines;
+        if (prev) line_kfaces<DIR>(G, S, c, lds, own, m - 1, delta, eps);
+        if (cur_too) line_kfaces<DIR>(G, S, c, lds, own, m, delta, eps);
+        __syncthreads();
+        if (prev) line_store<DIR, true>(G, c, fld, m - 1, lds);
+        if (cur_too) line_store<DIR, true>(G, c, fld, m, lds);
+        publish(word, last ? base + 0xffffu : base + m);
+        if (prev) line_store<DIR, false>(G, c, fld, m - 1, lds);
+        if (cur_too) line_store<DIR, false>(G, c, fld, m, lds);
+        __syncthreads();
+    }
+    eps = wave_sum(ok ? eps : HUGE_VAL);
+    if (c.lane == 0) part_add(a.part + (long long)src * a.nslots + TI * G.nt[1] + TJ, DIR, eps);
+}
+
+template <int COORD, int DIR>
+__global__ void __launch_bounds__(64, 2) k_fwd_lines(SweepArgs a, int c0, int cn) {
+    extern __shared__ __attribute__((aligned(16))) double lds[];
+    march(a, a.G, c0, cn, [&](int src, int TI, int TJ) { fwd_line_column<COORD, DIR>(a, a.G, src, TI, TJ, lds); });
+}
+
+// the solution out of its padded rows
+__global__ void __launch_bounds__(256) k_unpad(Geo G, const double* __restrict__ f, double* __restrict__ out) {
+    const long long x = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (x >= G.N) return;
+    const int k = (int)(x % G.n[2]);
+    const long long q = x / G.n[2];
+    out[(long long)blockIdx.y * G.N + x] = f[(long long)blockIdx.y * G.Nf + q * G.sj + k];
+}
+
+// TKC: the tile depth as a compile-time constant (0: read from the geometry); at
+// 16 the window is held across slabs.
+template <int COORD, int DIR, int TKC>
+__global__ void __launch_bounds__(64, TKC == 16 ? 2 : 3) k_fwd_sweep(SweepArgs a, int c0, int cn) {
+    using D = Dir<DIR>;
+    extern __shared__ __attribute__((aligned(16))) double lds[];
+    Geo G = a.G;
+    if (TKC > 0) G.tk = TKC;
+    if constexpr (TKC == 16) {
+        march(a, G, c0, cn, [&](int src, int TI, int TJ) { fwd_column<COORD, DIR, TKC>(a, G, src, TI, TJ, lds); });
+    } else {
+        const double* __restrict__ mdl = a.model + (long long)D::lay * G.Sa * 4;
+        const double2* __restrict__ t2 = a.T.t2;
+        const int Lp = tile_pitch(G.tk);
+        march(a, G, c0, cn, [&](int src, int TI, int TJ) {
+            const Src S = a.src[src];
+            TileCtx c = col_ctx<DIR>(G, S, TI, TJ);
+            const Col cl = make_col(G, a.T, c.i, c.j);
+            const LfCol W = lf_col<COORD>(G, S, cl, a.kappa);
+            double* __restrict__ fld = a.field + (long long)src * G.N;
+            const int own = ((c.li + 1) * kTC + c.lj + 1) * Lp;
+            double eps = 0.0;
+            const bool ok = march_column<DIR, false>(a, G, src, TI, TJ, [&](int TK, const Handover& h) {
+                slab_ctx<DIR>(G, S, c, TK * G.tk, G.tk);
+                if (c.t1 <= c.t0) return true;  // a ragged column's slab with no nodes
+                FwdSlot ring[kPre];
+#pragma unroll
+                for (int u = 0; u < kPre; ++u) fwd_fetch<DIR>(c, mdl, t2, c.t0 + u, ring[u]);
+                const bool waited = wait_upstream(h.up, h.target);
+                stage_tile<DIR>(G, c, fld, -(long long)src * G.N, (long long)(a.nsrc - src) * G.N - 2, lds);
+                __syncthreads();
+                // the step count is padded to a multiple of kPre (the LDS reads of a padded step
+                // stay inside the window: at most 3 entries past a column that others follow)
+                for (int tb = c.t0; tb < c.t1; tb += kPre) {
+#pragma unroll
+                    for (int u = 0; u < kPre; ++u) {
+                        fwd_step<COORD, DIR, false>(S, W, c, lds, own, Lp, tb + u, ring[u], eps);
+                        fwd_fetch<DIR>(c, mdl, t2, tb + u + kPre, ring[u]);
+                    }
+                }
+                __syncthreads();
+                unstage_tile<DIR>(G, c, fld, lds, Lp);
+                fwd_kface_nodes<DIR>(G, S, c, fld, lds, own, Lp, eps);
+                return waited;
+            });
+            eps = wave_sum(ok ? eps : HUGE_VAL);
+            if (c.lane == 0) part_add(a.part + (long long)src * a.nslots + TI * G.nt[1] + TJ, DIR, eps);
+        });
+    }
 }
 
 // model records (s, 1 - 2 xi, 2 eta, 1 + 2 xi) in the four aligned layouts
@@ -762,7 +1251,7 @@ __global__ void __launch_bounds__(kBndThreads) k_fwd_bnd(SweepArgs a, int dir) {
     if (!a.active[src]) return;
     const Geo& G = a.G;
     const Src S = a.src[src];
-    double* fld = a.field + (long long)src * G.N;
+    double* fld = a.field + (long long)src * G.Nf;
     const long long b = (long long)blockIdx.x * kBndThreads + threadIdx.x;
     double d = 0.0;
     if (b < G.NB) {
@@ -1060,7 +1549,7 @@ template <int DIR>
 __device__ __forceinline__ bool tile_meets_box(const Geo& G, const TileCtx& c, const int* bx) {
     using D = Dir<DIR>;
     const int i0 = 8 * c.TI, i1 = 8 * c.TI + c.ext_i - 1, j0 = 8 * c.TJ, j1 = 8 * c.TJ + c.ext_j - 1;
-    const int kq0 = max(0, c.TK * G.tk - i1 - j1), kq1 = min(G.m[2] - 1, c.TK * G.tk + G.tk - 1 - i0 - j0);
+    const int kq0 = max(0, c.U0 - i1 - j1), kq1 = min(G.m[2] - 1, c.U0 + G.tk - 1 - i0 - j0);
     const int ia = D::s0 > 0 ? 1 + i0 : G.n[0] - 2 - i1, ib = D::s0 > 0 ? 1 + i1 : G.n[0] - 2 - i0;
     const int ja = D::s1 > 0 ? 1 + j0 : G.n[1] - 2 - j1, jb = D::s1 > 0 ? 1 + j1 : G.n[1] - 2 - j0;
     const int ka = D::s2 > 0 ? 1 + kq0 : G.n[2] - 2 - kq1, kb = D::s2 > 0 ? 1 + kq1 : G.n[2] - 2 - kq0;
@@ -1187,13 +1676,13 @@ __global__ void __launch_bounds__(64, 3) k_adj_sweep(SweepArgs a, int c0, int cn
         const Src S = a.src[src];
         TileCtx c = col_ctx<DIR>(G, S, TI, TJ);
         double dsum = 0.0, asum = 0.0;
-        const bool ok = march_column<DIR>(a, G, src, TI, TJ, [&](int TK, const unsigned long long* up, unsigned long long target) {
-            slab_ctx<DIR>(G, S, c, TK);
+        const bool ok = march_column<DIR, false>(a, G, src, TI, TJ, [&](int TK, const Handover& h) {
+            slab_ctx<DIR>(G, S, c, TK * G.tk, G.tk);
             if (c.t1 <= c.t0) return true;  // a ragged column's slab with no nodes
             // wave-uniform: only tiles that meet the right-hand side read it
             if (tile_meets_box<DIR>(G, c, a.box + src * 6))
-                return adj_tile<DIR, true, COMPACT>(a, G, S, c, src, lds, up, target, dsum, asum);
-            return adj_tile<DIR, false, COMPACT>(a, G, S, c, src, lds, up, target, dsum, asum);
+                return adj_tile<DIR, true, COMPACT>(a, G, S, c, src, lds, h.up, h.target, dsum, asum);
+            return adj_tile<DIR, false, COMPACT>(a, G, S, c, src, lds, h.up, h.target, dsum, asum);
         });
         dsum = wave_sum(ok ? dsum : HUGE_VAL);
         asum = wave_sum(asum);
@@ -1662,7 +2151,7 @@ void launch_fwd_init(const Plan& P, const SweepArgs& a, const double* tau_init, 
     hipLaunchKernelGGL(k_solve_init, dim3(fill_blocks(P.G.N), P.nsrc), dim3(256), 0, st, a, tau_init, 1.0, 1.0);
 }
 
-static size_t tile_lds_bytes(const Geo& G) { return (size_t)stage_bytes(G.tk); }
+static size_t tile_lds_bytes(const Geo& G) { return (size_t)(G.Nf != G.N ? kLinesLds : stage_bytes(G.tk)); }
 
 // Workgroups (one wave each) of a sweep launch over cn sources: as many as the
 // chip's LDS holds, but no more than there are tile columns on each XCD.
@@ -1712,8 +2201,14 @@ constexpr SweepFn pick_adj(int d, std::integer_sequence<int, DS...>) {
     return t[d];
 }
 
-// forward sweep instances with a compile-time tile depth (the autotuner's
-// usual choices); other depths run the generic instance
+template <int COORD, int... DS>
+constexpr SweepFn pick_lines(int d, std::integer_sequence<int, DS...>) {
+    SweepFn t[] = {k_fwd_lines<COORD, DS>...};
+    return t[d];
+}
+
+// forward sweep instances with a compile-time tile depth (16: windows held across
+// slabs); other depths run the generic one
 template <int COORD>
 SweepFn fwd_sweep_fn_c(int tk, int d) {
     const auto seq = std::make_integer_sequence<int, 8>{};
@@ -1726,8 +2221,11 @@ SweepFn fwd_sweep_fn_c(int tk, int d) {
     }
 }
 
-SweepFn fwd_sweep_fn(int coord, int tk, int d) {
-    return coord == 1 ? fwd_sweep_fn_c<1>(tk, d) : fwd_sweep_fn_c<0>(tk, d);
+SweepFn fwd_sweep_fn(const Plan& P, int d) {
+    const auto seq = std::make_integer_sequence<int, 8>{};
+    const Geo& G = P.G;
+    if (G.Nf != G.N) return G.coord == 1 ? pick_lines<1>(d, seq) : pick_lines<0>(d, seq);
+    return G.coord == 1 ? fwd_sweep_fn_c<1>(G.tk, d) : fwd_sweep_fn_c<0>(G.tk, d);
 }
 
 // adjoint instances with a compile-time tile depth for the full record
@@ -1755,7 +2253,7 @@ void launch_fwd_iteration(const Plan& P, const SweepArgs& a, hipStream_t st) {
     for (int d = 0; d < 8; ++d) {
         {
         TimedLaunch tl(P, st, march_launches(P));
-        const SweepFn fn = fwd_sweep_fn(P.G.coord, P.G.tk, d);
+        const SweepFn fn = fwd_sweep_fn(P, d);
         for (int c0 = 0; c0 < P.nsrc; c0 += kMarchSources) {
             const int cn = std::min(kMarchSources, P.nsrc - c0);
             hipLaunchKernelGGL(fn, dim3(march_blocks(P, cn)), dim3(64), tile_lds_bytes(P.G), st, a, c0, cn);
@@ -1764,6 +2262,10 @@ void launch_fwd_iteration(const Plan& P, const SweepArgs& a, hipStream_t st) {
         hipLaunchKernelGGL(k_fwd_bnd, dim3(P.nbblocks, P.nsrc), dim3(kBndThreads), 0, st, a, d);
     }
     hipLaunchKernelGGL(k_fwd_finalize, dim3(P.nsrc), dim3(256), 0, st, a);
+}
+
+void launch_unpad(const Plan& P, double* tau, hipStream_t st) {
+    hipLaunchKernelGGL(k_unpad, dim3(blocks_for(P.G.N, 256), P.nsrc), dim3(256), 0, st, P.G, P.pad, tau);
 }
 
 void launch_adj_init(const Plan& P, const SweepArgs& a, const double* tau, int nrec, const double* rec,
