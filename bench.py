@@ -523,7 +523,7 @@ def main():
                                          lambda: step(False, poll=True, continuous=True))
     # roofline step: the same step once more with every directional sweep of the
     # sweep kernels timed by HIP events on the library's stream (one source
-    # group, so each launch carries a tile-plane of every active source)
+    # group, so each launch carries a sweep of every active source)
     rf = None
     if not args.no_sweep_timing:
         rf = run("roofline step", 1, 0 if runs else args.warmup,

@@ -153,7 +153,9 @@ typedef struct tt_opts {
 
 /* Bytes of device workspace needed by tt_forward (which = 0), tt_adjoint
  * (which = 1), tt_sample (which = 2) or tt_kernel (which = 3) for this grid,
- * source count and options (tile_k matters; opts may be NULL for defaults).
+ * source count and options (opts may be NULL for defaults).  A solve whose
+ * workspace was sized for another batch or other options runs if it holds at
+ * least the fields in place and one source group's tables.
  * Returns 0 for invalid arguments. */
 size_t tt_workspace_size(const tt_grid* grid, int32_t nsrc, const tt_opts* opts, int32_t which);
 
