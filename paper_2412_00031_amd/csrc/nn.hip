@@ -9,6 +9,7 @@
 // in a fixed order, so results are bitwise reproducible.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
@@ -524,7 +525,7 @@ __global__ __launch_bounds__(256) void k_conv3_wgrad_rows(const uint16_t* __rest
                 }
             }
         };
-        fetch(r0);
+        if (r0 < r1) fetch(r0);
         for (long long r = r0; r < r1; ++r) {
             const int yy = (int)(r % H), zz = (int)((r / H) % D);
             // ring slot of input row y + dy: 3 ((y + dy + 3) % 3) + (dz + 1)
@@ -643,7 +644,7 @@ __global__ __launch_bounds__(256) void k_up_wgrad_rows(const uint16_t* __restric
                 }
             }
         };
-        fetch(r0);
+        if (r0 < r1) fetch(r0);
         for (long long r = r0; r < r1; ++r) {
 #pragma unroll
             for (int j = 0; j < NL; ++j) {
@@ -1473,12 +1474,18 @@ int conv3_fwd(const uint16_t* x, int nbatch, int D, int H, int W, int cxt, int c
     return TT_OK;
 }
 
+// Slices of equal length that cover nrows rows, at most `most` of them.  The count
+// is taken again after the length has been rounded up, so that no slice starts
+// past the last row: the kernels read a slice's first rows unasked.
+long long even_slices(long long nrows, long long most) {
+    if (nrows < 1 || most < 1) return 1;
+    const long long rows = (nrows + most - 1) / most;
+    return (nrows + rows - 1) / rows;
+}
+
 // 512 slices give every CU two workgroups; a slice of fewer than 8 rows would
 // stage more halo rows than it works on
-long long wgrad_slices(long long nrows) {
-    long long s = (nrows + 7) / 8;
-    return s < 1 ? 1 : (s > 512 ? 512 : s);
-}
+long long wgrad_slices(long long nrows) { return even_slices(nrows, std::min((nrows + 7) / 8, 512LL)); }
 
 // partial weight gradients, then partial bias gradients, of every slice
 size_t conv3_wgrad_floats(long long nrows, int cin, int cout) {
@@ -1548,10 +1555,7 @@ long long up_slices(long long np) {
     return s < 1 ? 1 : (s > 256 ? 256 : s);
 }
 
-long long up_row_slices(long long nrows) {
-    long long s = (nrows + 3) / 4;
-    return s < 1 ? 1 : (s > 512 ? 512 : s);
-}
+long long up_row_slices(long long nrows) { return even_slices(nrows, std::min((nrows + 3) / 4, 512LL)); }
 
 size_t up_work_floats(long long np, long long nrows, int cin, int cout) {
     const size_t a = (size_t)up_slices(np) * 8 * cin * cout;
