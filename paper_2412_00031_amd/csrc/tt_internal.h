@@ -156,9 +156,10 @@ __device__ __forceinline__ void factor(const Src& S, const Col& c, double c2, do
                                        double& rq) {
     double d0, d1, d2;
     if (COORD == 1) {
-        double D0 = c.rct * c2 - S.Xs[0];
-        double D1 = c.rct * s2 - S.Xs[1];
-        double D2 = c.rst - S.Xs[2];
+        // (one rounding each, whichever of the products the caller keeps over a loop)
+        double D0 = fma(c.rct, c2, -S.Xs[0]);
+        double D1 = fma(c.rct, s2, -S.Xs[1]);
+        double D2 = fma(c.x0, c.st, -S.Xs[2]);
         d0 = D0 * S.E[0] + D1 * S.E[1] + D2 * S.E[2];
         d1 = D0 * S.E[3] + D1 * S.E[4] + D2 * S.E[5];
         d2 = D0 * S.E[6] + D1 * S.E[7] + D2 * S.E[8];
@@ -306,6 +307,14 @@ __device__ __forceinline__ LfCol lf_col(const Geo& G, const Src& S, const Col& c
 __device__ __forceinline__ double rsqrt_3(double x) {
     const double y = __builtin_amdgcn_rsq(x);
     const double e = fma(-(x * y), y, 1.0);
+    return fma(y, e * fma(0.375, e, 0.5), y);
+}
+// 1 / sqrt(x) correctly rounded but for a few cases in a thousand: as rsqrt_3, with
+// the residual e free of the rounding of x y
+__device__ __forceinline__ double rsqrt_c(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    const double t = x * y;
+    const double e = fma(-fma(x, y, -t), y, fma(-t, y, 1.0));
     return fma(y, e * fma(0.375, e, 0.5), y);
 }
 __device__ __forceinline__ double sqrt_3(double x) {
