@@ -134,7 +134,6 @@ __global__ void k_src_setup(Geo G, const double* __restrict__ pos, const double*
     const double det = b * c - f * f;
     S.mi11 = c / det; S.mi12 = -f / det; S.mi22 = b / det;
     S.s0 = par[3 * q];
-    S.rs = p0;
     S.fb[0] = cell_base(G, 0, p0);
     S.fb[1] = cell_base(G, 1, p1);
     S.fb[2] = cell_base(G, 2, p2);
@@ -843,7 +842,7 @@ __device__ __forceinline__ void fwd_fetch(const TileCtx& c, const double* __rest
 // around each update.
 // HELD: t is below the window's depth, so that the corner column has the slot.
 template <int COORD, int DIR, bool HELD>
-__device__ __forceinline__ void fwd_step(const Src& S, const LfCol& W, const TileCtx& c, double* lds, int own, int Lp,
+__device__ __forceinline__ void fwd_step(const Geo& G, const Src& S, const LfCol& W, const TileCtx& c, double* lds, int own, int Lp,
                                          int t, const FwdSlot& r, double& eps) {
     using D = Dir<DIR>;
     // sweep-relative neighbours: "up" = already updated this sweep
@@ -857,7 +856,7 @@ __device__ __forceinline__ void fwd_step(const Src& S, const LfCol& W, const Til
     const double m0 = D::s0 > 0 ? up_i : dn_i, p0 = D::s0 > 0 ? dn_i : up_i;
     const double m1 = D::s1 > 0 ? up_j : dn_j, p1 = D::s1 > 0 ? dn_j : up_j;
     const double m2 = D::s2 > 0 ? up_k : dn_k, p2 = D::s2 > 0 ? dn_k : up_k;
-    const double nv = lf_update<COORD>(S, W, r.c2, r.s2, r.sx, r.ma, r.mb, r.mc, cur, m0, p0, m1, p1, m2, p2);
+    const double nv = lf_update<COORD>(G, S, W, r.c2, r.s2, r.sx, r.ma, r.mb, r.mc, cur, m0, p0, m1, p1, m2, p2);
     const bool on = step_on(c, t);
     lds[HELD ? (on ? own : 0) + (sg > 0 ? t + 1 : Lp - 2 - t) : (on ? o + sg : 0)] = nv;
     eps += on ? fabs(nv - cur) : 0.0;
@@ -909,7 +908,7 @@ __device__ __forceinline__ void fwd_column(const SweepArgs& a, const Geo& G, int
             if (g * kPre < c.t0 || g * kPre >= c.t1) return;
 #pragma unroll
             for (int u = 0; u < kPre; ++u) {
-                fwd_step<COORD, DIR, true>(S, W, c, lds, own, Win::Lp, g * kPre + u, ring[u], eps);
+                fwd_step<COORD, DIR, true>(G, S, W, c, lds, own, Win::Lp, g * kPre + u, ring[u], eps);
                 fwd_fetch<DIR>(c, mdl, t2, g * kPre + u + kPre, ring[u]);
             }
         };
@@ -1114,7 +1113,7 @@ __device__ __forceinline__ void fwd_line_column(const SweepArgs& a, const Geo& G
                 const double m0 = D::s0 > 0 ? up_i : dn_i, p0 = D::s0 > 0 ? dn_i : up_i;
                 const double m1 = D::s1 > 0 ? up_j : dn_j, p1 = D::s1 > 0 ? dn_j : up_j;
                 const double m2 = D::s2 > 0 ? upk : dnk, p2 = D::s2 > 0 ? dnk : upk;
-                const double nv = lf_update<COORD>(S, W, r.c2, r.s2, r.sx, r.ma, r.mb, r.mc, cur, m0, p0, m1, p1, m2, p2);
+                const double nv = lf_update<COORD>(G, S, W, r.c2, r.s2, r.sx, r.ma, r.mb, r.mc, cur, m0, p0, m1, p1, m2, p2);
                 const bool on = step_on(c, t);
                 lds[on ? at : 0] = nv;  // no branch in a step, as in fwd_step
                 eps += on ? fabs(nv - cur) : 0.0;
@@ -1195,7 +1194,7 @@ __global__ void __launch_bounds__(64, TKC == 16 ? 2 : 3) k_fwd_sweep(SweepArgs a
                 for (int tb = c.t0; tb < c.t1; tb += kPre) {
 #pragma unroll
                     for (int u = 0; u < kPre; ++u) {
-                        fwd_step<COORD, DIR, false>(S, W, c, lds, own, Lp, tb + u, ring[u], eps);
+                        fwd_step<COORD, DIR, false>(G, S, W, c, lds, own, Lp, tb + u, ring[u], eps);
                         fwd_fetch<DIR>(c, mdl, t2, tb + u + kPre, ring[u]);
                     }
                 }
