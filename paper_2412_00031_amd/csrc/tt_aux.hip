@@ -207,14 +207,17 @@ __global__ void __launch_bounds__(64) k_misfit_cr_R(int nsrc, int nrec, const do
 }
 
 // gamma chi_cr over all pairs: one block (the call has no workspace for partial
-// sums of several).  Receivers are taken in runs whose residuals T - Tobs of all
-// sources fit in LDS (kCrRes values: rows of the run are read coalesced); pair p
+// sums of several).  Receivers are taken in runs whose T and Tobs of all sources
+// fit in LDS (kCrRes of each: rows of the run are read coalesced); pair p
 // of the run is taken by thread p mod 1024, its receiver found by binary search
 // in the run's offsets.  More sources than kCrRes read T and Tobs per pair.
+// Differences are taken source against source first, like the adjoint sources:
+// observed times may be clock times, whose differences are exact where T - Tobs
+// would be rounded to their own last place.
 // Fixed-order block reduction; malformed offsets or indices make chi NaN.
-// (128 x 500, 32000 pairs: 72 us with four scattered 8-byte reads a pair, 55 from
-// LDS; what is left is one CU's staging of the rows, five times 112 receivers.)
-constexpr int kCrRes = 14336;
+// (128 x 500, 32000 pairs: 72 us with four scattered 8-byte reads a pair, 60 from
+// LDS; what is left is one CU's staging of the rows, seven times 75 receivers.)
+constexpr int kCrRes = 9600;
 constexpr int kCrRun = 512;  // receivers of a run at most
 
 __global__ void __launch_bounds__(1024) k_misfit_cr_chi(int nsrc, int nrec, const double* __restrict__ T,
@@ -223,7 +226,8 @@ __global__ void __launch_bounds__(1024) k_misfit_cr_chi(int nsrc, int nrec, cons
                                                         const int32_t* __restrict__ pair,
                                                         const double* __restrict__ wcr, double gamma,
                                                         double* __restrict__ chi) {
-    extern __shared__ double res[];  // [nsrc][mr]
+    extern __shared__ double tl[];  // T [nsrc][mr], then Tobs
+    double* ol = tl + kCrRes;
     __shared__ double sh[16];
     __shared__ int bad;
     __shared__ int offl[kCrRun + 1];
@@ -256,7 +260,10 @@ __global__ void __launch_bounds__(1024) k_misfit_cr_chi(int nsrc, int nrec, cons
                         }
 #pragma unroll
                         for (int u = 0; u < 8; ++u)
-                            if (n0 + 16 * u < nsrc) res[(n0 + 16 * u) * nm + l] = tv[u] - ov[u];
+                            if (n0 + 16 * u < nsrc) {
+                                tl[(n0 + 16 * u) * nm + l] = tv[u];
+                                ol[(n0 + 16 * u) * nm + l] = ov[u];
+                            }
                     }
             }
             __syncthreads();
@@ -287,10 +294,10 @@ __global__ void __launch_bounds__(1024) k_misfit_cr_chi(int nsrc, int nrec, cons
                     }
                     double r;
                     if (staged) {
-                        r = res[n * nm + lo] - res[j * nm + lo];
+                        r = (tl[n * nm + lo] - tl[j * nm + lo]) - (ol[n * nm + lo] - ol[j * nm + lo]);
                     } else {
                         const long long cn = (long long)n * nrec + m0 + lo, cj = (long long)j * nrec + m0 + lo;
-                        r = (T[cn] - Tobs[cn]) - (T[cj] - Tobs[cj]);
+                        r = (T[cn] - T[cj]) - (Tobs[cn] - Tobs[cj]);
                     }
                     part += gamma * 0.5 * pw[u] * r * r;
                 }
@@ -426,9 +433,9 @@ void launch_misfit(int nsrc, int nrec, const double* T, const double* Tobs, cons
 void launch_misfit_cr(int nsrc, int nrec, const double* T, const double* Tobs, const int32_t* off, const int32_t* pair,
                       const double* wcr, double gamma, double* R, double* chi, hipStream_t st) {
     hipLaunchKernelGGL(k_misfit_cr_R, dim3(nrec), dim3(64), 0, st, nsrc, nrec, T, Tobs, off, pair, wcr, gamma, R);
-    const size_t lds = sizeof(double) * (nsrc <= kCrRes ? (size_t)kCrRes : 0);
+    const size_t lds = 2 * sizeof(double) * (nsrc <= kCrRes ? (size_t)kCrRes : 0);
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_misfit_cr_chi), hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)(sizeof(double) * kCrRes));
+                              (int)(2 * sizeof(double) * kCrRes));
     hipLaunchKernelGGL(k_misfit_cr_chi, dim3(1), dim3(1024), lds, st, nsrc, nrec, T, Tobs, off, pair, wcr, gamma, chi);
 }
 
