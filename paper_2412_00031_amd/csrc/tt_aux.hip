@@ -145,6 +145,54 @@ __global__ void __launch_bounds__(256) k_misfit_R(int nrec, const double* __rest
     }
 }
 
+// All of it in one block: chi first, in a fixed order, then R, whose pairs a
+// thread per source walks in list order.  Every input is read before R is written
+// (but for T and Tobs by pairs), so that R may be one of them.
+__global__ void __launch_bounds__(1024) k_misfit_one(int nsrc, int nrec, const double* T, const double* Tobs,
+                                                     const double* w, int npair, const int32_t* __restrict__ pairs,
+                                                     const double* __restrict__ wpair, double alpha, double beta,
+                                                     double* R, double* __restrict__ chi) {
+    __shared__ double sh[16];
+    const long long n = (long long)nsrc * nrec, np = (long long)nsrc * npair;
+    double part = 0.0;
+    for (long long e = threadIdx.x; e < n; e += 1024) {
+        const double ww = w ? w[e] : 1.0, r = T[e] - Tobs[e];
+        part += alpha * 0.5 * ww * r * r;
+    }
+    for (long long e = threadIdx.x; e < np; e += 1024) {
+        const long long base = e / npair * nrec;
+        const int p = (int)(e % npair), m = pairs[2 * p], i = pairs[2 * p + 1];
+        if (m < 0 || m >= nrec || i < 0 || i >= nrec) {
+            part = __builtin_nan("");
+            continue;
+        }
+        const double r = (T[base + m] - T[base + i]) - (Tobs[base + m] - Tobs[base + i]);
+        part += beta * 0.5 * (wpair ? wpair[e] : 1.0) * r * r;
+    }
+    part = wave_sum(part);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = part;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double tot = 0.0;
+        for (int v = 0; v < 16; ++v) tot += sh[v];
+        *chi = tot;
+    }
+    for (long long e = threadIdx.x; e < n; e += 1024) R[e] = alpha * (w ? w[e] : 1.0) * (T[e] - Tobs[e]);
+    if (npair == 0) return;
+    __syncthreads();
+    for (int q = threadIdx.x; q < nsrc; q += 1024) {
+        const long long base = (long long)q * nrec;
+        for (int p = 0; p < npair; ++p) {
+            const int m = pairs[2 * p], i = pairs[2 * p + 1];
+            if (m < 0 || m >= nrec || i < 0 || i >= nrec) continue;
+            const double g = beta * (wpair ? wpair[(long long)q * npair + p] : 1.0) *
+                             ((T[base + m] - T[base + i]) - (Tobs[base + m] - Tobs[base + i]));
+            R[base + m] += g;
+            R[base + i] -= g;
+        }
+    }
+}
+
 // Common-receiver differential misfit (Eq. (4), third misfit) and its adjoint
 // sources (Eq. (A4)), added to R and chi.
 //
@@ -423,6 +471,17 @@ void launch_misfit(int nsrc, int nrec, const double* T, const double* Tobs, cons
                    hipStream_t st) {
     if (nsrc == 0 || nrec == 0) {  // no residual; a pair can only name a receiver that is not there
         launch_fill(chi, 1, nsrc > 0 && npair > 0 ? __builtin_nan("") : 0.0, st);
+        return;
+    }
+    // the three launches' chi travels through R, which must then be none of the inputs
+    const size_t bytes = sizeof(double) * (size_t)nsrc * (size_t)nrec;
+    auto over = [&](const double* p) {
+        const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(R);
+        return p && a < b + bytes && b < a + bytes;
+    };
+    if (over(T) || over(Tobs) || over(w)) {
+        hipLaunchKernelGGL(k_misfit_one, dim3(1), dim3(1024), 0, st, nsrc, nrec, T, Tobs, w, npair, pairs, wpair, alpha,
+                           beta, R, chi);
         return;
     }
     hipLaunchKernelGGL(k_misfit_chi, dim3(nsrc), dim3(256), 0, st, nrec, T, Tobs, w, npair, pairs, wpair, alpha, beta, R);

@@ -1,0 +1,57 @@
+"""Misfits that one block computes: of any size, where the adjoint sources overwrite
+one of the inputs.  Bounds as for the other forms:
+three roundings a term and one per addition."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import oracle as O
+
+pytestmark = pytest.mark.gpu
+
+EPS = 2.0 ** -52
+
+
+def _call(torch, T, Tobs, w, pairs, R, chi):
+    from paper_2412_00031_amd import _lib
+    lib = _lib.load()
+    p = lambda a: ctypes.c_void_p(a.data_ptr() if a is not None else 0)
+    npair = 0 if pairs is None else pairs.shape[0]
+    _lib.check(lib.tt_misfit(T.shape[0], T.shape[1], p(T), p(Tobs), p(w), npair, p(pairs), p(None), 0.7, 1.3, p(R), p(chi),
+                             ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)))
+
+
+# R in place of T, of T_obs and of w, the last with pairs too
+@pytest.mark.parametrize("nsrc,nrec,npair,inplace", [
+    (5, 70, 0, "T"), (5, 70, 0, "Tobs"), (5, 70, 30, "w"), (300, 200, 0, "T"),
+    (300, 200, 0, "w")])
+def test_misfit_one_block(torch_cuda, nsrc, nrec, npair, inplace):
+    torch = torch_cuda
+    rng = np.random.default_rng(nsrc + 7 * nrec + npair)
+    T = rng.uniform(1, 20, (nsrc, nrec))
+    a = dict(T=T, Tobs=T + rng.normal(0, 0.2, T.shape), w=rng.uniform(0.5, 1.5, T.shape))
+    pairs = rng.integers(0, nrec, (npair, 2)).astype(np.int32)
+    chi_o, R_o = O.misfit(a["T"], a["Tobs"], a["w"], pairs, np.ones((nsrc, npair)), alpha=0.7, beta=1.3)
+    d = {k: torch.as_tensor(v, dtype=torch.float64, device="cuda") for k, v in a.items()}
+    pd = torch.as_tensor(pairs, device="cuda") if npair else None
+    R = d[inplace] if inplace else torch.empty((nsrc, nrec), dtype=torch.float64, device="cuda")
+    chi = torch.empty((), dtype=torch.float64, device="cuda")
+    _call(torch, d["T"], d["Tobs"], d["w"], pd, R, chi)
+    size, n = np.abs(0.7 * a["w"] * (T - a["Tobs"])), np.ones(T.shape)
+    for m, i in pairs:
+        t = np.abs(1.3 * ((T[:, m] - T[:, i]) - (a["Tobs"][:, m] - a["Tobs"][:, i])))
+        for q in (m, i):
+            size[:, q] += t
+            n[:, q] += 1
+    assert (np.abs(R.cpu().numpy() - R_o) <= (n + 3) * EPS * size).all()
+    assert abs(chi.item() - chi_o) <= (nsrc * (nrec + npair) + 4) * EPS * chi_o
+
+
+def test_misfit_one_block_bad_pair(torch_cuda):
+    torch = torch_cuda
+    d = lambda v: torch.as_tensor(v, dtype=torch.float64, device="cuda")
+    T, Tobs = d([[1.0, 2.0, 4.0]]), d([[1.5, 2.0, 3.0]])
+    R, chi = torch.empty_like(T), d(0.0)
+    _call(torch, T, Tobs, None, torch.tensor([[0, 3], [0, 1]], dtype=torch.int32, device="cuda"), R, chi)
+    assert torch.isnan(chi) and np.allclose(R.cpu().numpy(), [[0.7 * -0.5 + 1.3 * -0.5, 1.3 * 0.5, 0.7]], rtol=1e-15, atol=0)
