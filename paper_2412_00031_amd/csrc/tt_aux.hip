@@ -16,7 +16,9 @@ namespace tt {
 // so each source's chi travels through the first element of its row of R:
 // k_misfit_chi leaves it there, k_misfit_sum adds them up in order, k_misfit_R
 // then writes R.  (All sources in one block, a thread per source walking its
-// receivers and pairs: 128 x 500 with 2000 pairs 1499 us; the three 34.)
+// receivers and pairs: 128 x 500 with 2000 pairs 1499 us; the three 34.)  A few
+// residuals go to one block all the same (k_misfit_one): the two launches more
+// are a third of such a call.
 __global__ void __launch_bounds__(256) k_misfit_chi(int nrec, const double* __restrict__ T,
                                                     const double* __restrict__ Tobs, const double* __restrict__ w,
                                                     int npair, const int32_t* __restrict__ pairs,
@@ -466,6 +468,15 @@ void launch_reloc_kernel(const Plan& P, const double* tau, int nev, const double
         hipLaunchKernelGGL(k_reloc_kernel<0>, dim3(nev), dim3(64), 0, st, P.G, P.T, P.src, P.nsrc, tau, ev, R, K);
 }
 
+// Is one block the faster form?  Three launches take 15.5 to 16.5 us whatever the
+// size; one block 10.9 at 1 x 16, 10.6 at 64 x 64, 11.6 at 128 x 128, 38.8 at
+// 128 x 500, and with pairs, which a thread per source walks, 11.3 at 8 x 50 with
+// 20, 11.2 at 64 x 20 with 16, 11.6 at 300 x 10 with 8, but 21.7 there with 20 and
+// 16.8 at 8 x 500 with 32.
+static bool misfit_in_one(int nsrc, int nrec, int npair) {
+    return (long long)nsrc * (nrec + npair) <= 16384 && npair <= 24 && (long long)nsrc * npair <= 2560;
+}
+
 void launch_misfit(int nsrc, int nrec, const double* T, const double* Tobs, const double* w, int npair,
                    const int32_t* pairs, const double* wpair, double alpha, double beta, double* R, double* chi,
                    hipStream_t st) {
@@ -479,7 +490,7 @@ void launch_misfit(int nsrc, int nrec, const double* T, const double* Tobs, cons
         const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(R);
         return p && a < b + bytes && b < a + bytes;
     };
-    if (over(T) || over(Tobs) || over(w)) {
+    if (misfit_in_one(nsrc, nrec, npair) || over(T) || over(Tobs) || over(w)) {
         hipLaunchKernelGGL(k_misfit_one, dim3(1), dim3(1024), 0, st, nsrc, nrec, T, Tobs, w, npair, pairs, wpair, alpha,
                            beta, R, chi);
         return;

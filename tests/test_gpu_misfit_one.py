@@ -1,5 +1,5 @@
-"""Misfits that one block computes: of any size, where the adjoint sources overwrite
-one of the inputs.  Bounds as for the other forms:
+"""Misfits that one block computes: the form of a few residuals, and of any size where
+the adjoint sources overwrite one of the inputs.  Bounds as for the other forms:
 three roundings a term and one per addition."""
 import ctypes
 
@@ -22,9 +22,11 @@ def _call(torch, T, Tobs, w, pairs, R, chi):
                              ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)))
 
 
-# R in place of T, of T_obs and of w, the last with pairs too
+# one residual; around the limits on residuals (16384), pairs (24) and pairs of all
+# sources (2560); R in place of T, of T_obs and of w, the last with pairs too
 @pytest.mark.parametrize("nsrc,nrec,npair,inplace", [
-    (5, 70, 0, "T"), (5, 70, 0, "Tobs"), (5, 70, 30, "w"), (300, 200, 0, "T"),
+    (1, 1, 0, None), (1, 2, 1, None), (128, 128, 0, None), (128, 129, 0, None), (100, 9, 24, None), (100, 9, 25, None),
+    (106, 9, 24, None), (107, 9, 24, None), (5, 70, 0, "T"), (5, 70, 0, "Tobs"), (5, 70, 30, "w"), (300, 200, 0, "T"),
     (300, 200, 0, "w")])
 def test_misfit_one_block(torch_cuda, nsrc, nrec, npair, inplace):
     torch = torch_cuda
