@@ -468,6 +468,34 @@ __device__ __forceinline__ bf8_t tr_frag(const uint16_t* p, int step) {
 
 constexpr int kWgX = 64;  // positions of a row chunk
 
+// One tap of a slice's sums for one pair of 16-channel blocks, straight from memory,
+// with inputs outside the volume left out instead of multiplied by 0 (xb, gb: the
+// blocks' first channels; result as k_conv3_wgrad_rows has it).
+__device__ f4_t wgrad_tap(const uint16_t* __restrict__ xb, int D, int H, int W, int cxt, const uint16_t* __restrict__ gb,
+                          int cgt, long long r0, long long r1, int t, int lane) {
+    const int li = lane & 15, g = lane >> 4;
+    const int dz = t / 9 - 1, dy = t / 3 % 3 - 1, dx = t % 3 - 1;
+    f4_t acc = {0.f, 0.f, 0.f, 0.f};
+    for (long long r = r0; r < r1; ++r) {
+        const int yy = (int)(r % H), zz = (int)(r / H % D);
+        if ((unsigned)(zz + dz) >= (unsigned)D || (unsigned)(yy + dy) >= (unsigned)H) continue;
+        const long long nr = r + (long long)dz * H + dy;
+        for (int x0 = 0; x0 < W; x0 += 32) {
+            uint16_t a[8], b[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int xx = x0 + 8 * g + e;
+                const bool ok = xx < W;
+                a[e] = ok && (unsigned)(xx + dx) < (unsigned)W ? xb[(nr * W + xx + dx) * cxt + li] : (uint16_t)0;
+                b[e] = ok ? gb[(r * W + xx) * cgt + li] : (uint16_t)0;
+            }
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8_t, piece_of(a)),
+                                                          __builtin_bit_cast(bf8_t, piece_of(b)), acc, 0, 0, 0);
+        }
+    }
+    return acc;
+}
+
 // IB x OB: the 16-channel blocks of this workgroup (blockIdx.y: which of them)
 template <int IB, int OB>
 __global__ __launch_bounds__(256) void k_conv3_wgrad_rows(const uint16_t* __restrict__ x, int D, int H, int W,
@@ -571,6 +599,7 @@ __global__ __launch_bounds__(256) void k_conv3_wgrad_rows(const uint16_t* __rest
             __syncthreads();
         }
     }
+    unsigned over = 0;  // sums that overflowed
 #pragma unroll
     for (int j = 0; j < 7; ++j) {
         const int t = wv + 4 * j;
@@ -583,12 +612,25 @@ __global__ __launch_bounds__(256) void k_conv3_wgrad_rows(const uint16_t* __rest
                     if (bpart && ib0 == 0 && a == 0 && g == 0) bpart[(long long)blockIdx.x * cout + o] = acc[j][a][b][0];
                     continue;
                 }
+                const f4_t v = acc[j][a][b];
+                if (__any(!(fabsf(v[0]) + fabsf(v[1]) + fabsf(v[2]) + fabsf(v[3]) < HUGE_VALF)))
+                    over |= 1u << ((j * IB + a) * OB + b);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int i = (ib0 + a) * 16 + 4 * g + r;
-                    if (i < cin) part[(((long long)blockIdx.x * 27 + t) * cin + i) * cout + o] = acc[j][a][b][r];
+                    if (i < cin) part[(((long long)blockIdx.x * 27 + t) * cin + i) * cout + o] = v[r];
                 }
             }
+    }
+    // A row outside the volume, or a shift past a row's end, enters as products with 0,
+    // which an infinite value turns into no number: sums that overflowed are done again.
+    for (; over; over &= over - 1) {
+        const int q = __ffs((int)over) - 1, b = q % OB, a = q / OB % IB, t = wv + 4 * (q / (OB * IB));
+        const f4_t v = wgrad_tap(xb + a * 16, D, H, W, cxt, gb + b * 16, cgt, r0, r1, t, lane);
+        for (int r = 0; r < 4; ++r) {
+            const int i = (ib0 + a) * 16 + 4 * g + r;
+            if (i < cin) part[(((long long)blockIdx.x * 27 + t) * cin + i) * cout + (ob0 + b) * 16 + li] = v[r];
+        }
     }
 }
 
