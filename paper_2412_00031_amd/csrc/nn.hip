@@ -1526,8 +1526,12 @@ long long even_slices(long long nrows, long long most) {
 }
 
 // 512 slices give every CU two workgroups; a slice of fewer than 8 rows would
-// stage more halo rows than it works on
-long long wgrad_slices(long long nrows) { return even_slices(nrows, std::min((nrows + 7) / 8, 512LL)); }
+// stage more halo rows than it works on, which only pays while most of the chip is
+// idle (rows in 8s and in up to 32 slices: 4^3 of 64 -> 64 channels 31.0 and 21.9 us,
+// 8^3 31.5 and 27.4, 14^3 of 32 -> 32 30.6 and 28.0)
+long long wgrad_slices(long long nrows) {
+    return even_slices(nrows, std::min(std::max((nrows + 7) / 8, 32LL), std::min(nrows, 512LL)));
+}
 
 // partial weight gradients, then partial bias gradients, of every slice
 size_t conv3_wgrad_floats(long long nrows, int cin, int cout) {

@@ -1,0 +1,28 @@
+"""Edges of the rules that give small calls more waves: the weight gradient's slices
+(one row up to 32, then rows in eights).  Bounds as for the general forms."""
+import numpy as np
+import pytest
+
+from oracle import unet_ref as U
+
+pytestmark = pytest.mark.gpu
+
+
+def _bf(torch, a):
+    t = torch.as_tensor(np.asarray(a, dtype=np.float32)).to(torch.bfloat16)
+    return t.cuda(), t.double().numpy()
+
+
+@pytest.mark.parametrize("dims", [(1, 2, 3), (4, 8, 2), (3, 11, 2), (8, 32, 2), (257, 1, 2)])
+def test_wgrad_few_rows(torch_cuda, dims):
+    from paper_2412_00031_amd import nn
+    torch = torch_cuda
+    rng = np.random.default_rng(dims[1])
+    x_d, x = _bf(torch, rng.standard_normal((1,) + dims + (16,)))
+    g_d, g = _bf(torch, rng.standard_normal((1,) + dims + (16,)))
+    gW, gb = nn.conv3_wgrad(x_d, 16, g_d, 16)
+    Z = np.zeros((27, 16, 16))
+    _, w, b = U.conv3_backward(x[0], Z, g[0])
+    _, wm, bm = U.conv3_backward(np.abs(x[0]), Z, np.abs(g[0]))
+    for got, ref, mag in ((gW, w, wm), (gb, b, bm)):
+        assert np.all(np.abs(got.double().cpu().numpy() - ref) <= 1e-5 * mag + 1e-30)
