@@ -1,5 +1,6 @@
 """Edges of the rules that give small calls more waves: the weight gradient's slices
-(one row up to 32, then rows in eights).  Bounds as for the general forms."""
+(one row up to 32, then rows in eights) and the up-sampling's form below and above
+512 positions.  Bounds as for the general forms."""
 import numpy as np
 import pytest
 
@@ -26,3 +27,19 @@ def test_wgrad_few_rows(torch_cuda, dims):
     _, wm, bm = U.conv3_backward(np.abs(x[0]), Z, np.abs(g[0]))
     for got, ref, mag in ((gW, w, wm), (gb, b, bm)):
         assert np.all(np.abs(got.double().cpu().numpy() - ref) <= 1e-5 * mag + 1e-30)
+
+
+@pytest.mark.parametrize("nb,dims", [(1, (8, 8, 8)), (1, (27, 19, 1)), (2, (4, 8, 8))])
+def test_up_few_positions(torch_cuda, nb, dims):
+    from paper_2412_00031_amd import nn
+    torch = torch_cuda
+    rng = np.random.default_rng(dims[0])
+    x_d, x = _bf(torch, rng.standard_normal((nb,) + dims + (32,)))
+    Wu, b = rng.standard_normal((8, 32, 16)).astype(np.float32), rng.standard_normal(16).astype(np.float32)
+    y_d = torch.empty((nb,) + tuple(2 * d for d in dims) + (16,), dtype=torch.bfloat16, device="cuda")
+    nn.up_fwd(x_d, torch.as_tensor(Wu).cuda(), torch.as_tensor(b).cuda(), y_d)
+    y = y_d.double().cpu().numpy()
+    for q in range(nb):
+        ref = U.up(x[q], Wu.astype(np.float64), b.astype(np.float64))
+        mag = U.up(np.abs(x[q]), np.abs(Wu).astype(np.float64), np.abs(b).astype(np.float64))
+        assert np.all(np.abs(y[q] - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-5 * mag)
