@@ -1,6 +1,7 @@
 """Edges of the rules that give small calls more waves: the weight gradient's slices
-(one row up to 32, then rows in eights) and the up-sampling's form below and above
-512 positions.  Bounds as for the general forms."""
+(one row up to 32, then rows in eights), the up-sampling's form below and above 512
+positions, and the warm start's interpolation in pieces of 64 nodes for fewer than
+8 sources.  Bounds as for the general forms."""
 import numpy as np
 import pytest
 
@@ -43,3 +44,17 @@ def test_up_few_positions(torch_cuda, nb, dims):
         ref = U.up(x[q], Wu.astype(np.float64), b.astype(np.float64))
         mag = U.up(np.abs(x[q]), np.abs(Wu).astype(np.float64), np.abs(b).astype(np.float64))
         assert np.all(np.abs(y[q] - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-5 * mag)
+
+
+# 7 sources in pieces, 8 in runs, from the same predictions: bit for bit
+@pytest.mark.parametrize("n", [(5, 6, 64), (6, 5, 65), (12, 9, 200)])
+def test_warm_init_pieces(torch_cuda, n):
+    from paper_2412_00031_amd import nn
+    torch = torch_cuda
+    rng = np.random.default_rng(n[2])
+    g = dict(n=n, coord=0, o=(0.0, 0.0, 0.0), h=(1.0, 1.0, 1.0))
+    dims = tuple((v - 1) // 3 + 2 for v in n)
+    pred = torch.as_tensor(rng.standard_normal((8,) + dims).astype(np.float32)).cuda()
+    few, many = nn.warm_init(g, pred[:7].contiguous(), 3), nn.warm_init(g, pred, 3)
+    N = n[0] * n[1] * n[2]
+    assert torch.equal(few.reshape(7, N), many.reshape(8, N)[:7])
