@@ -1478,14 +1478,20 @@ int conv3_planes(const uint16_t* x, int nbatch, int D, int H, int W, int cxt, in
     return TT_OK;
 }
 
+// 16-position blocks a wave of k_conv3_planes holds, as its accumulators leave
+// registers for.  32 -> 16 channels, whose resident weights take 108 of them, has 6:
+// with 8 the plane's tiles are larger and fewer (8 x 56^3 105.5 us instead of 99.4,
+// 64^3 24.8 and 23.6, 24 x 100 x 100 31.1 and 29.4).
+constexpr int cv_blocks(int KB, int NB) { return NB > 2 ? 4 : (KB == 2 && NB == 1 ? 6 : 8); }
+
 template <int KB>
 int conv3_planes_nb(int NB, const uint16_t* x, int nbatch, int D, int H, int W, int cxt, int cxo, const uint16_t* frag,
                     const float* bias, int relu, uint16_t* y, int cyt, int cyo, int R, size_t lds, hipStream_t st) {
     switch (NB) {
-        case 1: return conv3_planes<KB, 1, KB == 2 ? 6 : 8>(x, nbatch, D, H, W, cxt, cxo, frag, bias, relu, y, cyt, cyo, R, lds, st);
-        case 2: return conv3_planes<KB, 2, 8>(x, nbatch, D, H, W, cxt, cxo, frag, bias, relu, y, cyt, cyo, R, lds, st);
-        case 3: return conv3_planes<KB, 3, 4>(x, nbatch, D, H, W, cxt, cxo, frag, bias, relu, y, cyt, cyo, R, lds, st);
-        default: return conv3_planes<KB, 4, 4>(x, nbatch, D, H, W, cxt, cxo, frag, bias, relu, y, cyt, cyo, R, lds, st);
+        case 1: return conv3_planes<KB, 1, cv_blocks(KB, 1)>(x, nbatch, D, H, W, cxt, cxo, frag, bias, relu, y, cyt, cyo, R, lds, st);
+        case 2: return conv3_planes<KB, 2, cv_blocks(KB, 2)>(x, nbatch, D, H, W, cxt, cxo, frag, bias, relu, y, cyt, cyo, R, lds, st);
+        case 3: return conv3_planes<KB, 3, cv_blocks(KB, 3)>(x, nbatch, D, H, W, cxt, cxo, frag, bias, relu, y, cyt, cyo, R, lds, st);
+        default: return conv3_planes<KB, 4, cv_blocks(KB, 4)>(x, nbatch, D, H, W, cxt, cxo, frag, bias, relu, y, cyt, cyo, R, lds, st);
     }
 }
 
@@ -1499,7 +1505,7 @@ int conv3_fwd(const uint16_t* x, int nbatch, int D, int H, int W, int cxt, int c
     if (KB != 3 && pieces16(x, cxt, cxo) && reinterpret_cast<uintptr_t>(y) % 8 == 0 && cyt % 4 == 0 && cyo % 4 == 0 &&
         (long long)nbatch * H < (1 << 30) && (long long)H * W * cxt < (1LL << 31)) {
         size_t lds = 0;
-        const int R = conv3_plane_rows(KB, NB > 2 ? 4 : (KB == 2 && NB == 1 ? 6 : 8), H, W, &lds);
+        const int R = conv3_plane_rows(KB, cv_blocks(KB, NB), H, W, &lds);
         if (R > 0) {
             if (KB == 1) return conv3_planes_nb<1>(NB, x, nbatch, D, H, W, cxt, cxo, frag, bias, relu, y, cyt, cyo, R, lds, st);
             if (KB == 2) return conv3_planes_nb<2>(NB, x, nbatch, D, H, W, cxt, cxo, frag, bias, relu, y, cyt, cyo, R, lds, st);
