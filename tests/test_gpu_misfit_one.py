@@ -57,3 +57,24 @@ def test_misfit_one_block_bad_pair(torch_cuda):
     R, chi = torch.empty_like(T), d(0.0)
     _call(torch, T, Tobs, None, torch.tensor([[0, 3], [0, 1]], dtype=torch.int32, device="cuda"), R, chi)
     assert torch.isnan(chi) and np.allclose(R.cpu().numpy(), [[0.7 * -0.5 + 1.3 * -0.5, 1.3 * 0.5, 0.7]], rtol=1e-15, atol=0)
+
+
+# a receiver of 64 pairs (sorted) and of 65 (walked), past the one-block form
+@pytest.mark.parametrize("npair", [64, 65])
+def test_misfit_star(torch_cuda, npair):
+    torch = torch_cuda
+    rng = np.random.default_rng(npair)
+    T = rng.uniform(1, 20, (3, 90))
+    Tobs = T + rng.normal(0, 0.2, T.shape)
+    pairs = np.stack([np.full(npair, 7), 8 + np.arange(npair)], 1)[rng.permutation(npair)].astype(np.int32)
+    chi_o, R_o = O.misfit(T, Tobs, np.ones(T.shape), pairs, np.ones((3, npair)), alpha=0.7, beta=1.3)
+    d = lambda v: torch.as_tensor(v, dtype=torch.float64, device="cuda")
+    R, chi = torch.empty((3, 90), dtype=torch.float64, device="cuda"), d(0.0)
+    _call(torch, d(T), d(Tobs), None, torch.as_tensor(pairs, device="cuda"), R, chi)
+    size = np.abs(0.7 * (T - Tobs))
+    for m, i in pairs:
+        t = np.abs(1.3 * ((T[:, m] - T[:, i]) - (Tobs[:, m] - Tobs[:, i])))
+        size[:, m] += t
+        size[:, i] += t
+    assert (np.abs(R.cpu().numpy() - R_o) <= (npair + 4) * EPS * size).all()
+    assert abs(chi.item() - chi_o) <= (3 * (90 + npair) + 4) * EPS * chi_o
