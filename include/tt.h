@@ -76,8 +76,11 @@ typedef struct tt_opts {
     double tol;        /* stop at the first iteration whose convergence measure is < tol */
     int32_t max_iter;  /* >= 1 */
     double kappa;      /* Lax-Friedrichs viscosity factor, >= max sqrt(1 + 2|xi|) */
-    int32_t tile_k;    /* k-extent of one sweep tile, 1..62; 0 = library default
-                          (tt_default_tile_k; deeper tiles for large batches).
+    int32_t tile_k;    /* k-extent of one sweep tile, 1..62; 0 = library default, by
+                          grid and batch size (tt_solve_form tells which).  A
+                          given depth is taken as it is: on batches of 3000 tile
+                          columns of 8 x 8 nodes or more, shallow ones are slower
+                          than the default by up to 2.5 times (depth 8: 1.8).
                           Results do not depend on it. */
     int32_t flags;     /* bit 0 (TT_FLAG_TIME_SWEEPS): time the sweep kernels with a HIP
                           event pair around the launches of every
@@ -153,11 +156,21 @@ typedef struct tt_opts {
 
 /* Bytes of device workspace needed by tt_forward (which = 0), tt_adjoint
  * (which = 1), tt_sample (which = 2) or tt_kernel (which = 3) for this grid,
- * source count and options (opts may be NULL for defaults).  A solve whose
- * workspace was sized for another batch or other options runs if it holds at
- * least the fields in place and one source group's tables.
+ * source count and options (opts may be NULL for defaults; tile_k, groups and
+ * the compact flag matter).  A solve whose workspace was sized for another
+ * batch, tile depth or group count runs as long as it holds one source group's
+ * tables and records: in fewer groups than asked for, and in place where it
+ * does not hold the padded fields of a large forward batch.  (Compact and full
+ * adjoint records need their own sizes.)
  * Returns 0 for invalid arguments. */
 size_t tt_workspace_size(const tt_grid* grid, int32_t nsrc, const tt_opts* opts, int32_t which);
+
+/* How tt_forward (which = 0) or tt_adjoint (which = 1) would run this batch on a
+ * workspace of ws_bytes: the depth of its sweeps' slabs, its source groups, and
+ * whether its fields are padded to whole lines (forward).  Pointers may be NULL.
+ * Returns an error for arguments that the solve would refuse. */
+int tt_solve_form(const tt_grid* grid, int32_t nsrc, const tt_opts* opts, int32_t which, size_t ws_bytes,
+                  int32_t* tile_k, int32_t* groups, int32_t* lines);
 
 /* Source constants s0, xi0, eta0 of the factorisation T = T0 * tau: the model
  * interpolated trilinearly at each source (factor of Sec. 3.1).
@@ -341,8 +354,8 @@ int tt_mg_expand(const tt_grid* grid, int32_t H, const int32_t* m, const double*
  * reading.  Pointers may be NULL. */
 int tt_sweep_timing(int32_t which, double* total_ms, int64_t* launches, int32_t reset);
 
-/* The tile depth (tt_opts.tile_k) that tile_k = 0 selects (large batches take
- * a deeper one): which = 0 tt_forward, 1 tt_adjoint; 0 for any other value. */
+/* The tile depth (tt_opts.tile_k) that tile_k = 0 selects for small batches
+ * (large ones take another: tt_solve_form): which = 0 tt_forward, 1 tt_adjoint; 0 for any other value. */
 int32_t tt_default_tile_k(int32_t which);
 
 /* Message for the last nonzero return of the calling thread ("" if none). */

@@ -23,7 +23,7 @@ class TTOpts(ctypes.Structure):
 
 EXPORTS = ["tt_workspace_size", "tt_source_params", "tt_forward", "tt_forward_noalloc", "tt_forward_noalloc_limit", "tt_sample", "tt_misfit", "tt_misfit_cr", "tt_reloc_times", "tt_reloc_kernel",
            "tt_adjoint", "tt_kernel", "tt_kernel_density", "tt_mg_workspace_size", "tt_mg_project", "tt_mg_expand",
-           "tt_sweep_timing", "tt_default_tile_k", "tt_last_error"]
+           "tt_sweep_timing", "tt_default_tile_k", "tt_solve_form", "tt_last_error"]
 
 NN_EXPORTS = ["nn_to_bf16", "nn_from_bf16", "nn_conv3_pack", "nn_conv3_fwd", "nn_conv3_wgrad_work", "nn_conv3_wgrad",
               "nn_relu_mask", "nn_pool_fwd", "nn_pool_bwd", "nn_up_fwd", "nn_up_wgrad_work", "nn_up_bwd",
@@ -113,6 +113,8 @@ def load(path=LIB_PATH):
     lib.tt_sweep_timing.restype = ctypes.c_int
     lib.tt_default_tile_k.argtypes = [i32]
     lib.tt_default_tile_k.restype = i32
+    lib.tt_solve_form.argtypes = [G, i32, O, i32, sz] + [ctypes.POINTER(i32)] * 3
+    lib.tt_solve_form.restype = ctypes.c_int
     lib.tt_last_error.argtypes = []
     lib.tt_last_error.restype = ctypes.c_char_p
     for name in ("tt_source_params", "tt_forward", "tt_forward_noalloc", "tt_sample", "tt_misfit", "tt_misfit_cr", "tt_reloc_times",

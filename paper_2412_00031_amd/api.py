@@ -108,6 +108,22 @@ def workspace(grid, nsrc, which, tile_k=0, device=None, groups=0, time_sweeps=Fa
     return torch.empty(int(nbytes), dtype=torch.uint8, device=device)
 
 
+def solve_form(grid, nsrc, which, tile_k=0, groups=0, ws_bytes=None, time_sweeps=False, compact=False):
+    """How a forward (which = 0) or adjoint (1) solve of nsrc sources would run on
+    a workspace of ws_bytes (None: one of the size that these options ask for):
+    dict of the slabs' depth ``tile_k``, the source ``groups`` and ``lines``
+    (forward fields padded to whole lines)."""
+    lib = _lib.load()
+    g = _grid(grid)
+    o = _opts(1e-6, 1, 1.0, tile_k, time_sweeps=time_sweeps, groups=groups, compact=compact)
+    if ws_bytes is None:
+        ws_bytes = lib.tt_workspace_size(ctypes.byref(g), int(nsrc), ctypes.byref(o), int(which))
+    out = [ctypes.c_int32(0) for _ in range(3)]
+    _lib.check(lib.tt_solve_form(ctypes.byref(g), int(nsrc), ctypes.byref(o), int(which), int(ws_bytes),
+                                 *(ctypes.byref(v) for v in out)))
+    return dict(tile_k=out[0].value, groups=out[1].value, lines=bool(out[2].value))
+
+
 def source_params(grid, s, xi, eta, src_pos):
     """s0, xi0, eta0 at each source (trilinear interpolation of the model)."""
     lib = _lib.load()

@@ -148,7 +148,6 @@ int groups_of(const tt_opts* o, const tt_grid* grid, int nsrc, int which, bool l
     return g > nsrc ? nsrc : g;
 }
 
-
 // first source of group q of G
 int group_begin(int nsrc, int G, int q) { return (int)(((long long)nsrc * q) / G); }
 
@@ -546,11 +545,46 @@ size_t grouped_total(const tt::Geo& G, int nsrc, int groups, int which, bool com
 
 bool compact_of(const tt_opts* o) { return o && (o->flags & TT_FLAG_COMPACT_ADJOINT); }
 
-// the default number of groups, or as many as a workspace sized for another batch holds
-int fit_groups(const tt::Geo& G, int nsrc, int groups, int which, size_t ws_bytes, const tt_opts* o) {
-    while (groups > 1 && !(o->groups > 0) && ws_bytes < grouped_total(G, nsrc, groups, which, which == 1 && compact_of(o)))
-        --groups;
+// as many of the wanted groups as the workspace holds (results do not depend on it)
+int fit_groups(const tt::Geo& G, int nsrc, int groups, int which, size_t ws_bytes, bool compact = false) {
+    while (groups > 1 && ws_bytes < grouped_total(G, nsrc, groups, which, compact)) --groups;
     return groups;
+}
+
+// How a solve runs on a workspace of ws_bytes: its geometry (tile depth, padded
+// rows or not) and source groups.
+struct Form {
+    tt::Geo G;
+    bool lines;
+    int groups;
+};
+
+// Whole lines at the default depth, where lines_of has them ahead and the workspace
+// holds the padded fields; else slabs in place.
+Form forward_form(const tt_grid* grid, int nsrc, const tt_opts* o, size_t ws_bytes) {
+    Form f;
+    f.G = make_geo(grid, tile_k_of(o, 0, grid, nsrc));
+    if (o->tile_k == 0 && lines_of(grid, nsrc)) {
+        const tt::Geo P = padded(f.G);
+        const int groups = fit_groups(P, nsrc, groups_of(o, grid, nsrc, 0, true), 0, ws_bytes);
+        if (ws_bytes >= grouped_total(P, nsrc, groups, 0)) {
+            f.G = P;
+            f.lines = true;
+            f.groups = groups;
+            return f;
+        }
+    }
+    f.lines = false;
+    f.groups = fit_groups(f.G, nsrc, groups_of(o, grid, nsrc, 0), 0, ws_bytes);
+    return f;
+}
+
+Form adjoint_form(const tt_grid* grid, int nsrc, const tt_opts* o, size_t ws_bytes) {
+    Form f;
+    f.G = make_geo(grid, tile_k_of(o, 1, grid, nsrc));
+    f.lines = false;
+    f.groups = fit_groups(f.G, nsrc, groups_of(o, grid, nsrc, 1), 1, ws_bytes, compact_of(o));
+    return f;
 }
 
 // Plans of the groups of a solve, bound to consecutive workspace regions, with
@@ -630,9 +664,12 @@ int check_ptrs(std::initializer_list<const void*> ps) {
 // Forward solve on a workspace that the caller checked (tt_forward) or the
 // scratch array provides (tt_forward_noalloc, one source group); the plan
 // checks are done by the callers.
-int forward_run(const tt::Geo& G, bool lines, const double* s, const double* xi, const double* eta, int32_t nsrc,
+int forward_run(const Form& form, const double* s, const double* xi, const double* eta, int32_t nsrc,
                 const double* src_pos, const double* src_par, const double* tau_init, const tt_opts* opts, double* tau,
-                int32_t* status, void* ws, size_t ws_bytes, int groups, hipStream_t caller) {
+                int32_t* status, void* ws, size_t ws_bytes, hipStream_t caller) {
+    const tt::Geo& G = form.G;
+    const bool lines = form.lines;
+    const int groups = form.groups;
     int rc = TT_OK;
     std::vector<Group> gs;
     if ((rc = make_groups(G, nsrc, groups, 0, ws, ws_bytes, opts, caller, gs))) return rc;
@@ -662,14 +699,12 @@ int forward_run(const tt::Geo& G, bool lines, const double* s, const double* xi,
 }
 
 // Argument checks shared by the forward entry points.
-int forward_checks(const tt_grid* grid, int32_t nsrc, const tt_opts* opts, std::initializer_list<const void*> ptrs,
-                   tt::Geo* G) {
+int forward_checks(const tt_grid* grid, int32_t nsrc, const tt_opts* opts, std::initializer_list<const void*> ptrs) {
     int rc = check_grid(grid);
     if (rc || (rc = check_opts(opts))) return rc;
     if (nsrc < 0) return fail(TT_EINVAL, "nsrc < 0");
     if (nsrc > 65535) return fail(TT_EINVAL, "nsrc > 65535");
     if (nsrc > 0 && (rc = check_ptrs(ptrs))) return rc;
-    *G = make_geo(grid, tile_k_of(opts, 0, grid, nsrc));
     return TT_OK;
 }
 
@@ -726,6 +761,20 @@ size_t tt_workspace_size(const tt_grid* grid, int32_t nsrc, const tt_opts* opts,
     return grouped_total(G, nsrc, which <= 1 ? groups_of(opts, grid, nsrc, which) : 1, which, which == 1 && compact_of(opts));
 }
 
+int tt_solve_form(const tt_grid* grid, int32_t nsrc, const tt_opts* opts, int32_t which, size_t ws_bytes, int32_t* tile_k,
+                  int32_t* groups, int32_t* lines) {
+    g_err.clear();
+    int rc = check_grid(grid);
+    if (rc || (rc = check_opts(opts))) return rc;
+    if (which < 0 || which > 1) return fail(TT_EINVAL, "which must be 0 or 1");
+    if (nsrc < 1 || nsrc > 65535) return fail(TT_EINVAL, "nsrc must be in [1, 65535]");
+    const Form f = which == 0 ? forward_form(grid, nsrc, opts, ws_bytes) : adjoint_form(grid, nsrc, opts, ws_bytes);
+    if (tile_k) *tile_k = f.lines ? tt::kLineDepth : f.G.tk;
+    if (groups) *groups = f.groups;
+    if (lines) *lines = f.lines ? 1 : 0;
+    return TT_OK;
+}
+
 int tt_source_params(const tt_grid* grid, const double* s, const double* xi, const double* eta, int32_t nsrc,
                      const double* src_pos, double* src_par, void* stream) {
     g_err.clear();
@@ -744,39 +793,31 @@ int tt_forward(const tt_grid* grid, const double* s, const double* xi, const dou
                const double* src_pos, const double* src_par, const double* tau_init, const tt_opts* opts, double* tau,
                int32_t* status, void* ws, size_t ws_bytes, void* stream) {
     g_err.clear();
-    tt::Geo G;
-    int rc = forward_checks(grid, nsrc, opts, {s, xi, eta, src_pos, src_par, tau, status, ws}, &G);
+    int rc = forward_checks(grid, nsrc, opts, {s, xi, eta, src_pos, src_par, tau, status, ws});
     if (rc || nsrc == 0) return rc;
-    bool lines = opts->tile_k == 0 && lines_of(grid, nsrc);
-    int groups = groups_of(opts, grid, nsrc, 0, lines);
-    if (lines && ws_bytes < grouped_total(padded(G), nsrc, groups, 0)) {  // (solves in place)
-        lines = false;
-        groups = groups_of(opts, grid, nsrc, 0);
-    }
-    if (!lines) groups = fit_groups(G, nsrc, groups, 0, ws_bytes, opts);
-    return forward_run(lines ? padded(G) : G, lines, s, xi, eta, nsrc, src_pos, src_par, tau_init, opts, tau, status, ws,
-                       ws_bytes, groups, (hipStream_t)stream);
+    return forward_run(forward_form(grid, nsrc, opts, ws_bytes), s, xi, eta, nsrc, src_pos, src_par, tau_init, opts, tau,
+                       status, ws, ws_bytes, (hipStream_t)stream);
 }
 
 int tt_forward_noalloc(const tt_grid* grid, const double* s, const double* xi, const double* eta, int32_t nsrc,
                        const double* src_pos, const double* src_par, const double* tau_init, const tt_opts* opts,
                        double* tau, int32_t* status, void* stream) {
     g_err.clear();
-    tt::Geo G;
-    int rc = forward_checks(grid, nsrc, opts, {s, xi, eta, src_pos, src_par, tau, status}, &G);
+    int rc = forward_checks(grid, nsrc, opts, {s, xi, eta, src_pos, src_par, tau, status});
     if (rc || nsrc == 0) return rc;
     if (opts->flags & (TT_FLAG_POLL | TT_FLAG_TIME_SWEEPS | TT_FLAG_GRAPH))
         return fail(TT_EINVAL, "tt_forward_noalloc: TT_FLAG_POLL, TT_FLAG_TIME_SWEEPS and TT_FLAG_GRAPH need "
                                "allocations (pinned memory, events, graphs) and are not available here");
-    const size_t need = grouped_total(G, nsrc, 1, 0);
+    const size_t need = grouped_total(make_geo(grid, tile_k_of(opts, 0, grid, nsrc)), nsrc, 1, 0);
     if (need > kScratchBytes)
         return fail(TT_EINVAL, "tt_forward_noalloc: this grid and batch need %zu bytes of workspace, more than the "
                                "%zu-byte scratch; use tt_forward with a caller workspace", need, kScratchBytes);
     void* ws = nullptr;
     if ((rc = scratch_ptr(&ws))) return rc;
-    const bool lines = opts->tile_k == 0 && lines_of(grid, nsrc) && grouped_total(padded(G), nsrc, 1, 0) <= kScratchBytes;
-    return forward_run(lines ? padded(G) : G, lines, s, xi, eta, nsrc, src_pos, src_par, tau_init, opts, tau, status, ws,
-                       kScratchBytes, 1, (hipStream_t)stream);
+    tt_opts one = *opts;
+    one.groups = 1;
+    return forward_run(forward_form(grid, nsrc, &one, kScratchBytes), s, xi, eta, nsrc, src_pos, src_par, tau_init, opts,
+                       tau, status, ws, kScratchBytes, (hipStream_t)stream);
 }
 
 size_t tt_forward_noalloc_limit(void) { return kScratchBytes; }
@@ -902,8 +943,9 @@ int tt_adjoint(const tt_grid* grid, const double* s, const double* xi, const dou
     if (nsrc > 65535) return fail(TT_EINVAL, "nsrc > 65535");
     if ((rc = check_ptrs({s, xi, eta, src_pos, src_par, tau, lam, status, ws}))) return rc;
     if (nrec > 0 && (!rec_pos || !R)) return fail(TT_EINVAL, "rec_pos/R NULL with nrec > 0");
-    tt::Geo G = make_geo(grid, tile_k_of(opts, 1, grid, nsrc));
-    const int groups = fit_groups(G, nsrc, groups_of(opts, grid, nsrc, 1), 1, ws_bytes, opts);
+    const Form form = adjoint_form(grid, nsrc, opts, ws_bytes);
+    const tt::Geo& G = form.G;
+    const int groups = form.groups;
     hipStream_t caller = (hipStream_t)stream;
     std::vector<Group> gs;
     if ((rc = make_groups(G, nsrc, groups, 1, ws, ws_bytes, opts, caller, gs))) return rc;

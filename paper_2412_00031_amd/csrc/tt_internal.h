@@ -25,6 +25,7 @@ constexpr int kBJ = 8;
 constexpr int kWave = 64;
 constexpr int kBndThreads = 256;
 constexpr int kMaxTileK = 62;  // k-extent of a forward sweep tile; the staged column (tk + 2) fits one wave
+constexpr int kLineDepth = 16;  // nodes of a line: the depth of the forward sweeps' slabs of whole lines
 
 // Kernel-argument copy of the grid.
 struct Geo {

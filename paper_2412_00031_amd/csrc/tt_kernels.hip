@@ -953,7 +953,7 @@ __device__ __forceinline__ void fwd_column(const SweepArgs& a, const Geo& G, int
 // (s2 < 0: 31 minus that, so that pairs keep the order of memory); 324 spreads
 // the lanes' slots over the banks.  A lane's own value at kappa and the one
 // below stay in registers from step to step.
-constexpr int kLine = 16;
+constexpr int kLine = kLineDepth;
 constexpr int kLineRow = 324;
 constexpr int kLinesLds = kTC * kLineRow * 8;
 

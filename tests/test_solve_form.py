@@ -1,0 +1,52 @@
+"""Host logic of how a solve runs: the default form of a batch, what explicit options
+make of it, and workspaces that were sized for other options."""
+import ctypes
+import os
+
+import pytest
+
+
+@pytest.fixture(scope="module")
+def api():
+    from paper_2412_00031_amd import _lib, api, build
+    if not os.path.exists(_lib.LIB_PATH):
+        build.build()
+    _lib.load(_lib.LIB_PATH)
+    return api
+
+
+def _size(api, g, nsrc, which, **kw):
+    from paper_2412_00031_amd import _lib
+    o = api._opts(1e-6, 1, 1.0, kw.get("tile_k", 0), groups=kw.get("groups", 0), compact=kw.get("compact", False))
+    return _lib.load().tt_workspace_size(ctypes.byref(api._grid(g)), nsrc, ctypes.byref(o), which)
+
+
+def _grid(n):
+    return dict(n=(n, n, n), coord=1, o=(6371.0 - (n - 1), -0.01, -0.01), h=(1.0, 0.02 / (n - 1), 0.02 / (n - 1)))
+
+
+def test_default_form_by_batch(api):
+    assert api.solve_form(_grid(41), 1, 0) == dict(tile_k=16, groups=1, lines=False)
+    assert api.solve_form(_grid(61), 64, 0) == dict(tile_k=16, groups=2, lines=True)
+    assert api.solve_form(_grid(101), 128, 0) == dict(tile_k=28, groups=1, lines=False)
+    assert api.solve_form(_grid(101), 128, 1) == dict(tile_k=40, groups=2, lines=False)
+    assert api.solve_form(_grid(61), 64, 0, tile_k=20) == dict(tile_k=20, groups=1, lines=False)
+    assert api.solve_form(_grid(61), 64, 0, time_sweeps=True)["groups"] == 1
+    with pytest.raises(RuntimeError):
+        api.solve_form(_grid(61), 64, 0, tile_k=63)
+
+
+@pytest.mark.parametrize("which", [0, 1])
+def test_workspace_sized_for_other_groups_serves(api, which):
+    for n, nsrc in ((61, 64), (41, 100), (101, 128), (21, 16)):
+        g = _grid(n)
+        for sized in (0, 1, 2):
+            have = _size(api, g, nsrc, which, groups=sized)
+            for asked in (1, 2, 4, 8):
+                f = api.solve_form(g, nsrc, which, groups=asked, ws_bytes=have)
+                assert 1 <= f["groups"] <= asked
+                # what it settles on fits, in place or padded
+                if not f["lines"]:
+                    assert _size(api, g, nsrc, which, groups=f["groups"], tile_k=f["tile_k"]) <= have
+        full = _size(api, g, nsrc, which, groups=4)
+        assert api.solve_form(g, nsrc, which, groups=4, ws_bytes=full)["groups"] == 4
