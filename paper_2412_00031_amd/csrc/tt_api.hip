@@ -754,8 +754,7 @@ size_t tt_workspace_size(const tt_grid* grid, int32_t nsrc, const tt_opts* opts,
     if (opts && (opts->groups < 0 || opts->groups > TT_MAX_GROUPS)) return 0;
     if (opts && (opts->tile_k < 0 || opts->tile_k > tt::kMaxTileK)) return 0;
     tt::Geo G = make_geo(grid, tile_k_of(opts, which, grid, nsrc));
-    // (at any tile depth: a workspace serves calls that differ in it)
-    if (which == 0 && lines_of(grid, nsrc))
+    if (which == 0 && (!opts || opts->tile_k == 0) && lines_of(grid, nsrc))  // (slabs of a given depth solve in place)
         return std::max(grouped_total(padded(G), nsrc, groups_of(opts, grid, nsrc, 0, true), 0),
                         grouped_total(G, nsrc, groups_of(opts, grid, nsrc, 0), 0));
     return grouped_total(G, nsrc, which <= 1 ? groups_of(opts, grid, nsrc, which) : 1, which, which == 1 && compact_of(opts));

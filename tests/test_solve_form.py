@@ -36,6 +36,15 @@ def test_default_form_by_batch(api):
         api.solve_form(_grid(61), 64, 0, tile_k=63)
 
 
+def test_workspace_of_an_explicit_depth_has_no_padded_fields(api):
+    g, nsrc = _grid(61), 64
+    fields = 8 * nsrc * 61 ** 3
+    assert _size(api, g, nsrc, 0) > fields
+    assert _size(api, g, nsrc, 0, tile_k=28) < _size(api, g, nsrc, 0) - fields
+    # the default then solves in place on it
+    assert not api.solve_form(g, nsrc, 0, ws_bytes=_size(api, g, nsrc, 0, tile_k=28))["lines"]
+
+
 @pytest.mark.parametrize("which", [0, 1])
 def test_workspace_sized_for_other_groups_serves(api, which):
     for n, nsrc in ((61, 64), (41, 100), (101, 128), (21, 16)):
