@@ -60,7 +60,7 @@ def parse():
     ap.add_argument("--tile-k", type=int, default=0, help="tile depth for both solves (0: autotune)")
     ap.add_argument("--tile-k-fwd", type=int, default=0, help="forward tile depth (overrides --tile-k/autotune)")
     ap.add_argument("--tile-k-adj", type=int, default=0, help="adjoint tile depth (overrides --tile-k/autotune)")
-    ap.add_argument("--no-autotune", action="store_true", help="use the library's default tile depths")
+    ap.add_argument("--no-autotune", action="store_true", help="use the library's default forms (tile depths and source groups)")
     ap.add_argument("--no-sweep-timing", action="store_true",
                     help="skip the per-launch sweep events (roofline then unmeasured)")
     ap.add_argument("--obs", choices=("true-model", "straight"), default="true-model",
@@ -406,11 +406,10 @@ def main():
         tk_f, tk_a = tk_f or tuned["fwd"], tk_a or tuned["adj"]
         if args.groups == 0:
             gr_f, gr_a = tuned["groups_fwd"], tuned["groups_adj"]
-    tk_f = tk_f or int(lib.tt_default_tile_k(0))
-    tk_a = tk_a or int(lib.tt_default_tile_k(1))
-    auto_groups = max(1, min(4, nsrc // 32))
-    gr_f, gr_a = gr_f or auto_groups, gr_a or auto_groups
-    log(f"tile depths: forward {tk_f}, adjoint {tk_a}; source groups: forward {gr_f}, adjoint {gr_a}")
+    # (0: the library's default for this grid and batch, as any caller gets it)
+    form_f = api.solve_form(g, nsrc, 0, tk_f, gr_f)
+    form_a = api.solve_form(g, nsrc, 1, tk_a, gr_a)
+    log(f"forward {form_f}, adjoint {form_a}")
     ws_f = api.workspace(g, nsrc, 0, tk_f, dev, groups=gr_f)
     ws_a = api.workspace(g, nsrc, 1, tk_a, dev, groups=gr_a)
     tau = torch.empty((nsrc,) + tuple(g["n"]), dtype=torch.float64, device=dev)
@@ -548,8 +547,9 @@ def main():
         bytes_f = upd_f * (16.0 + 24.0 / nsrc)
         bytes_a = upd_a * (16.0 + 32.0 + 24.0 / nsrc)
         kern = {
-            "k_fwd_sweep": dict(ms=ms_f, launches=n_f, bytes=bytes_f, updates=upd_f, tk=tk_f),
-            "k_adj_sweep": dict(ms=ms_a, launches=n_a, bytes=bytes_a, updates=upd_a, tk=tk_a),
+            "k_fwd_lines" if form_f["lines"] else "k_fwd_sweep":
+                dict(ms=ms_f, launches=n_f, bytes=bytes_f, updates=upd_f, tk=form_f["tile_k"]),
+            "k_adj_sweep": dict(ms=ms_a, launches=n_a, bytes=bytes_a, updates=upd_a, tk=form_a["tile_k"]),
         }
         for K in kern.values():
             K["achieved"] = K["bytes"] / (K["ms"] * 1e-3) / 1e9 if K["ms"] > 0 else 0.0
@@ -612,10 +612,10 @@ def main():
                                f"{len(wl['rec'])} receivers, tol {tol:g}, {start}",
                    "nsrc": nsrc, "grid": list(g["n"]), "tol": tol, "kappa": kappa,
                    "mean_iters_fwd": round(float(it_f.mean()), 2), "mean_iters_adj": round(float(it_a.mean()), 2),
-                   "tile_k": {"fwd": tk_f, "adj": tk_a,
+                   "tile_k": {"fwd": form_f["tile_k"], "adj": form_a["tile_k"], "fwd_lines": form_f["lines"],
                               "chosen_by": "autotune" if tuned else ("fixed" if (args.tile_k_fwd or args.tile_k_adj
                                                                                  or args.tile_k) else "default")},
-                   "source_groups": {"fwd": gr_f, "adj": gr_a},
+                   "source_groups": {"fwd": form_f["groups"], "adj": form_a["groups"]},
                    "source_order": ("by forward iterations of a host-polled solve before timing, most first"
                                     if args.order == "iterations" else "as generated"),
                    "solves": "asynchronous (iteration budget, no host polling)", "iteration_budgets": budgets,

@@ -1,6 +1,8 @@
 """Autotuner for the sweep launch shape of the forward and adjoint solves:
-the tile depth (tile_k, the hyperplane steps of one sweep tile) and the
-number of concurrently iterated source groups.
+the tile depth (tile_k, the hyperplane steps of one sweep tile; 0, the
+library's default form for the batch, which may be whole lines of padded
+fields, a form that no depth names) and the number of concurrently iterated
+source groups (0, the library's default number).
 
 For a grid and source count it times a few iterations of each solve for every
 candidate tile depth (the whole call, asynchronous as in production, with the
@@ -31,8 +33,8 @@ import torch
 
 from . import _lib, api
 
-CANDIDATES = (8, 12, 14, 16, 18, 20, 22, 24, 28, 32, 40, 48, 62)
-GROUP_CANDIDATES = (1, 2, 3, 4, 6, 8)
+CANDIDATES = (0, 8, 12, 14, 16, 18, 20, 22, 24, 28, 32, 40, 48, 62)
+GROUP_CANDIDATES = (0, 1, 2, 3, 4, 6, 8)
 
 
 def cache_path():

@@ -1,5 +1,6 @@
 """Host logic of how a solve runs: the default form of a batch, what explicit options
-make of it, and workspaces that were sized for other options."""
+make of it, workspaces that were sized for other options, and the tuner's choice
+between the default and explicit depths."""
 import ctypes
 import os
 
@@ -59,3 +60,21 @@ def test_workspace_sized_for_other_groups_serves(api, which):
                     assert _size(api, g, nsrc, which, groups=f["groups"], tile_k=f["tile_k"]) <= have
         full = _size(api, g, nsrc, which, groups=4)
         assert api.solve_form(g, nsrc, which, groups=4, ws_bytes=full)["groups"] == 4
+
+
+def test_tuner_can_choose_the_default_form(api, monkeypatch):
+    import torch
+    from paper_2412_00031_amd import autotune
+    g, nsrc = _grid(21), 8
+    asked = []
+
+    def timed(kind, grid, s, xi, eta, src, par, tau, rec, R, kappa, tk, groups, iters):
+        asked.append((kind, tk, groups))
+        return 1.0 if (tk, groups) == (0, 0) else 2.0
+
+    monkeypatch.setattr(autotune, "_time", timed)
+    monkeypatch.setattr(autotune.api, "forward", lambda *a, **k: (torch.zeros(nsrc, 1), None))
+    z = torch.zeros(1, dtype=torch.float64)
+    got = autotune.tune(g, z, z, z, torch.zeros(nsrc, 3), torch.zeros(nsrc, 3), 1.05, torch.zeros(2, 3), use_cache=False)
+    assert got == {"fwd": 0, "adj": 0, "groups_fwd": 0, "groups_adj": 0, "cached": False}
+    assert ("fwd", 16, 0) in asked and ("adj", 0, 2) in asked
