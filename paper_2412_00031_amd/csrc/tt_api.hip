@@ -194,11 +194,11 @@ tt::Geo padded(tt::Geo G) {
 // Workspace layout (each region 256-byte aligned):
 //   Src[nsrc] | tab0[n0] | tab1[n1] | tab2[n2] | active[nsrc] | iter[nsrc] | counter |
 //   part[nsrc*nslots] (sums, sweep progress, queues) | model[4*Sa*4], pad[nsrc*Nf] if padded (forward) | part2[nsrc*nslots] (adjoint) |
-//   coef[nsrc*4*Sa*6] (or [nsrc*N*6] compact) | diag[nsrc*N] | rhs[nsrc*N] | box[nsrc*6] | bnd_in, bnd_rhs[nsrc*NB] |
-//   bnd_rec[nsrc*3*NB] (adjoint)
+//   coef[nsrc*4*Sa*6] (or [nsrc*N*6] compact) | diag[nsrc*N] | rhs[nsrc*N] | box[nsrc*6] | bnd_in, bnd_rhs[nsrc*NB]
+//   (adjoint; diag is dead once the right-hand side is formed, and the continuous solve puts bnd_rec[nsrc*3*NB] there)
 struct Layout {
     size_t off_src, off_t0, off_t1, off_t2, off_active, off_iter, off_counter, off_part, off_part2, off_coef,
-        off_diag, off_rhs, off_box, off_bnd, off_bndrec, off_model, off_pad, total;
+        off_diag, off_rhs, off_box, off_bnd, off_model, off_pad, total;
 };
 
 Layout layout(const tt::Geo& G, int nsrc, int nslots, int which, bool compact = false) {
@@ -218,7 +218,6 @@ Layout layout(const tt::Geo& G, int nsrc, int nslots, int which, bool compact = 
     L.off_rhs = o;
     L.off_box = o;
     L.off_bnd = o;
-    L.off_bndrec = o;
     L.off_model = o;
     L.off_pad = o;
     if (which == 0 || which == 1) {
@@ -233,11 +232,10 @@ Layout layout(const tt::Geo& G, int nsrc, int nslots, int which, bool compact = 
         L.off_part2 = o; o = align_up(o + sizeof(double) * (size_t)nsrc * nslots);
         L.off_coef = o;
         o = align_up(o + sizeof(double) * 6 * (size_t)nsrc * (compact ? (size_t)G.N : 4 * (size_t)G.Sa));
-        L.off_diag = o; o = align_up(o + sizeof(double) * (size_t)nsrc * (size_t)G.N);
+        L.off_diag = o; o = align_up(o + sizeof(double) * (size_t)nsrc * (size_t)std::max(G.N, 6 * G.NB));
         L.off_rhs = o; o = align_up(o + sizeof(double) * (size_t)nsrc * (size_t)G.N);
         L.off_box = o; o = align_up(o + sizeof(int) * 6 * (size_t)nsrc);
         L.off_bnd = o; o = align_up(o + sizeof(double) * 2 * (size_t)nsrc * (size_t)G.NB);  // bnd_in, bnd_rhs
-        L.off_bndrec = o; o = align_up(o + sizeof(double) * 6 * (size_t)nsrc * (size_t)G.NB);
     }
     L.total = o;
     return L;
@@ -267,7 +265,7 @@ void bind_workspace(tt::Plan& P, void* ws, const Layout& L) {
     P.box = reinterpret_cast<int*>(b + L.off_box);
     P.bnd_in = reinterpret_cast<double*>(b + L.off_bnd);
     P.bnd_rhs = P.bnd_in + (size_t)P.nsrc * (size_t)P.G.NB;
-    P.bnd_rec = reinterpret_cast<double2*>(b + L.off_bndrec);
+    P.bnd_rec = reinterpret_cast<double2*>(P.diag);
     P.model = reinterpret_cast<double*>(b + L.off_model);
     P.pad = reinterpret_cast<double*>(b + L.off_pad);
     P.T.t0 = P.tab0;

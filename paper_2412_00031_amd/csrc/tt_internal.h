@@ -383,7 +383,7 @@ struct Plan {
     double* pad = nullptr;    // forward: the solution fields with padded rows, [nsrc][Nf], if Nf != N
     double* bnd_in = nullptr; // adjoint: [nsrc][NB] (continuous adjoint: boundary pass scratch)
     double* bnd_rhs = nullptr; // adjoint: right-hand side of the boundary nodes, [nsrc][NB]
-    double2* bnd_rec = nullptr;  // continuous adjoint: the boundary nodes' records, [nsrc][3][NB]
+    double2* bnd_rec = nullptr;  // continuous adjoint: the boundary nodes' records, [nsrc][3][NB], in place of diag
     bool continuous = false;  // adjoint: upwind discretisation of Eq. (5) instead of the exact transpose
     bool compact = false;     // adjoint: one node-order copy of the coefficient records
     // optional timing of the sweep kernels: an event pair around the

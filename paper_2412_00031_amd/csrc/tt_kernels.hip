@@ -1339,17 +1339,12 @@ constexpr int kRec = 6;
 // (k_adj_rhs adds to it); a zero diagonal (no row) stores a zero record
 __device__ __forceinline__ void store_record(const Geo& G, double* __restrict__ coef_all, double* __restrict__ diag_all,
                                              double* __restrict__ rhs_all, int src, long long x, int i, int j, int k,
-                                             const double (&out)[8], int compact, double2* __restrict__ bnd = nullptr) {
+                                             const double (&out)[8], int compact) {
     const double d = out[6];
     double2 rec[3];
 #pragma unroll
     for (int q = 0; q < 3; ++q)
         rec[q] = d != 0.0 ? make_double2(out[2 * q] / d, out[2 * q + 1] / d) : make_double2(0.0, 0.0);
-    if (bnd && (on_bnd(G, 0, i) || on_bnd(G, 1, j) || on_bnd(G, 2, k))) {
-        double2* br = bnd + (long long)src * 3 * G.NB + bnd_encode(G, i, j, k);
-#pragma unroll
-        for (int q = 0; q < 3; ++q) br[q * G.NB] = rec[q];
-    }
     diag_all[(long long)src * G.N + x] = d;
     rhs_all[(long long)src * G.N + x] = 0.0;
     if (compact) {
@@ -1836,7 +1831,7 @@ __device__ __forceinline__ double cadj_area(const Geo& G, int a, int i, int j, i
 template <int COORD>
 __global__ void __launch_bounds__(256) k_cadj_coef(SweepArgs a, const double* __restrict__ tau_all,
                                                    double* __restrict__ coef_all, double* __restrict__ diag_all,
-                                                   double* __restrict__ rhs_all, double2* __restrict__ bnd_all) {
+                                                   double* __restrict__ rhs_all) {
     const Geo& G = a.G;
     const int src = blockIdx.y;
     const long long x = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1876,15 +1871,30 @@ __global__ void __launch_bounds__(256) k_cadj_coef(SweepArgs a, const double* __
         }
         out[6] = diag > 0.0 ? diag : HUGE_VAL;
     }
-    store_record(G, coef_all, diag_all, rhs_all, src, x, i, j, k, out, a.compact, bnd_all);
+    store_record(G, coef_all, diag_all, rhs_all, src, x, i, j, k, out, a.compact);
+}
+
+// The boundary nodes' records, in planes by boundary node, for the boundary pass:
+// read in the sweeps' layout a node of a k face takes lines of its own for its
+// record every time (128 sources of 61^3 162 us a pass beside another group's
+// sweep, now 82).  Gathered once a solve, over the diagonals, which nothing reads
+// after the right-hand side.
+__global__ void __launch_bounds__(kBndThreads) k_cadj_bnd_records(SweepArgs a, double2* __restrict__ rec_all) {
+    const Geo& G = a.G;
+    const int src = blockIdx.y;
+    const long long b = (long long)blockIdx.x * kBndThreads + threadIdx.x;
+    if (b >= G.NB) return;
+    int i, j, k;
+    bnd_decode(G, b, i, j, k);
+    const double2* rc = reinterpret_cast<const double2*>(
+        a.coef + (a.compact ? (long long)src * G.N + nidx(G, i, j, k) : (long long)src * 4 * G.Sa + arec_idx(G, 0, i, j, k)) * kRec);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) rec_all[(long long)src * 3 * G.NB + q * G.NB + b] = rc[q];
 }
 
 // Boundary pass of the continuous system, Jacobi: every boundary node's new P
-// from the values present before the pass, into tmp [nsrc][NB].  Its row comes
-// from the boundary's own copy of the records, in planes by boundary node
-// (from the sweeps' layout a node of a k face takes lines of its own for its
-// record, its right-hand side and its neighbours: 128 sources of 61^3 162 us
-// beside another group's sweep, now 82); the right-hand side is read inside the box where it is not zero.
+// from the values present before the pass, into tmp [nsrc][NB].  The right-hand
+// side is read inside the box where it is not zero.
 __global__ void __launch_bounds__(kBndThreads) k_cadj_bnd_calc(SweepArgs a, const double2* __restrict__ rec_all,
                                                                double* __restrict__ tmp_all) {
     const int src = blockIdx.y;
@@ -2275,14 +2285,16 @@ void launch_adj_init(const Plan& P, const SweepArgs& a, const double* tau, int n
     const dim3 rgrid(P.nsrc);
     const int t0 = P.continuous ? 0 : 1;
     if (P.G.coord == 1) {
-        if (P.continuous) hipLaunchKernelGGL(k_cadj_coef<1>, grid, dim3(256), 0, st, a, tau, P.coef, P.diag, P.rhs, P.bnd_rec);
+        if (P.continuous) hipLaunchKernelGGL(k_cadj_coef<1>, grid, dim3(256), 0, st, a, tau, P.coef, P.diag, P.rhs);
         else hipLaunchKernelGGL(k_adj_coef<1>, grid, dim3(256), 0, st, a, tau, P.coef, P.bnd_in, P.diag, P.rhs);
         hipLaunchKernelGGL(k_adj_rhs<1>, rgrid, dim3(64), 0, st, a, P.diag, P.rhs, P.box, nrec, rec, R, t0);
     } else {
-        if (P.continuous) hipLaunchKernelGGL(k_cadj_coef<0>, grid, dim3(256), 0, st, a, tau, P.coef, P.diag, P.rhs, P.bnd_rec);
+        if (P.continuous) hipLaunchKernelGGL(k_cadj_coef<0>, grid, dim3(256), 0, st, a, tau, P.coef, P.diag, P.rhs);
         else hipLaunchKernelGGL(k_adj_coef<0>, grid, dim3(256), 0, st, a, tau, P.coef, P.bnd_in, P.diag, P.rhs);
         hipLaunchKernelGGL(k_adj_rhs<0>, rgrid, dim3(64), 0, st, a, P.diag, P.rhs, P.box, nrec, rec, R, t0);
     }
+    if (P.continuous)
+        hipLaunchKernelGGL(k_cadj_bnd_records, dim3(P.nbblocks, P.nsrc), dim3(kBndThreads), 0, st, a, P.bnd_rec);
     hipLaunchKernelGGL(k_solve_init, dim3(fill_blocks(P.G.N), P.nsrc), dim3(256), 0, st, a, init, 0.0, 0.0);
 }
 

@@ -78,3 +78,15 @@ def test_tuner_can_choose_the_default_form(api, monkeypatch):
     got = autotune.tune(g, z, z, z, torch.zeros(nsrc, 3), torch.zeros(nsrc, 3), 1.05, torch.zeros(2, 3), use_cache=False)
     assert got == {"fwd": 0, "adj": 0, "groups_fwd": 0, "groups_adj": 0, "cached": False}
     assert ("fwd", 16, 0) in asked and ("adj", 0, 2) in asked
+
+
+@pytest.mark.parametrize("n,nsrc", [(101, 3), (61, 20), (41, 8)])
+def test_adjoint_workspace_holds_what_both_systems_use(api, n, nsrc):
+    """Records, diagonal, right-hand side and two values per boundary node and source;
+    nothing that only the continuous system needs."""
+    N, NB = n ** 3, n ** 3 - (n - 2) ** 3
+    per_source = 8 * (2 * N + 2 * NB)
+    full = 4 * n * (2 * n - 1) * ((n + 14) // 8 * 8) * 48
+    slack = 64 * 1024 + nsrc * 8 * NB  # tables, sums and progress words
+    assert _size(api, _grid(n), nsrc, 1, groups=1) <= nsrc * (per_source + full) + slack
+    assert _size(api, _grid(n), nsrc, 1, groups=1, compact=True) <= nsrc * (per_source + 48 * N) + slack
