@@ -110,7 +110,7 @@ def parse():
     return ap.parse_args()
 
 
-SOLVER_SOURCES = ("tt_kernels.hip", "tt_device.h", "tt_internal.h")
+SOLVER_SOURCES = ("tt_kernels.hip", "tt_device.h", "tt_internal.h", "tt_wait.h")
 
 
 def solver_sha256():

@@ -190,7 +190,8 @@ int tt_source_params(const tt_grid* grid, const double* s, const double* xi, con
  *   status [nsrc]       out (device): iterations done if converged;
  *                       -iterations if max_iter was reached without
  *                       convergence (the TT_ENOCONV condition: outputs are
- *                       still written)
+ *                       still written).  A source whose sweep gave up a wait
+ *                       for a lost wave ends there, as not converged.
  * tau may alias tau_init.  Asynchronous on stream (see TT_FLAG_POLL). */
 int tt_forward(const tt_grid* grid, const double* s, const double* xi, const double* eta,
                int32_t nsrc, const double* src_pos, const double* src_par, const double* tau_init,

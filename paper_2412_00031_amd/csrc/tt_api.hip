@@ -245,7 +245,7 @@ void fill_plan(tt::Plan& P, const tt::Geo& G, int nsrc) {
     P.G = G;
     P.nsrc = nsrc;
     P.nbblocks = (int)((G.NB + tt::kBndThreads - 1) / tt::kBndThreads);
-    P.nslots = 2 * G.ncols + P.nbblocks + 1;
+    P.nslots = 2 * G.ncols + P.nbblocks + 2;
 }
 
 void bind_workspace(tt::Plan& P, void* ws, const Layout& L) {

@@ -397,7 +397,7 @@ struct SweepArgs {
     Tabs T;
     const double *s, *xi, *eta;
     const Src* src;
-    double* field;          // tau or lambda [nsrc][N]
+    double* field;          // tau or lambda [nsrc][Nf]
     const double* coef;     // adjoint coefficients [nsrc][4][Sa][6], or [nsrc][N][6] when compact
     const double* rhs;      // adjoint right-hand side / diagonal [nsrc][N]
     const int* box;         // [nsrc][6]: i, j, k ranges of the nonzero rhs (empty: lo > hi)
@@ -409,8 +409,8 @@ struct SweepArgs {
     int32_t* status;
     // per source nslots 8-byte slots: the convergence sums of the ncols tile
     // columns and nbblocks boundary blocks over the iteration's directions so
-    // far, the columns' sweep progress (ncols 64-bit words), and the ticket and
-    // owner words of the source's work queue (sweep_claim)
+    // far, the columns' sweep progress (ncols 64-bit words), the ticket and
+    // owner words of the source's work queue (sweep_claim), and its lost word
     double* part;
     double* part2;          // adjoint: sums of |lambda| in the last direction, same first two ranges
     int* counter;

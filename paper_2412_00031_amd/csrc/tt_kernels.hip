@@ -34,6 +34,7 @@
 
 #include "tt_device.h"
 #include "tt_internal.h"
+#include "tt_wait.h"
 
 namespace tt {
 
@@ -305,7 +306,8 @@ __device__ __forceinline__ bool step_on(const TileCtx& c, int t) {
 // columns are handed out by a ticket counter, ordered by TI + TJ, then TI,
 // then source.  A column's upstream neighbours have lower tickets, so whoever
 // holds them is already running, never waits for a later ticket, and finishes:
-// every wait ends, however many waves are resident.
+// every wait ends, however many waves are resident.  (Should a wave be lost all the
+// same, waits for it end after kWaitPolls polls and the source ends unconverged.)
 //
 // How a slab's values reach the next wave.  All waves of a batch share the
 // XCD's L2: a wave's stores are in that L2 once s_waitcnt vmcnt(0) has passed,
@@ -316,11 +318,13 @@ __device__ __forceinline__ bool step_on(const TileCtx& c, int t) {
 // an idle chip and 8.7 us with 256 such chains.
 constexpr int kMarchBatches = 8;                    // one per XCD
 constexpr int kMarchSources = 64 * kMarchBatches;   // sources of one launch: a batch's active mask is one wave ballot
-constexpr unsigned long long kWaitTicks = 400000000ull;  // 4 s of the 100 MHz clock: no wait lasts that long
 
 __device__ __forceinline__ unsigned* queue_words(const SweepArgs& a, int src) {
     return reinterpret_cast<unsigned*>(a.part + (long long)src * a.nslots + 2 * a.G.ncols + a.nbblocks);
 }
+
+// word 2 of the queue's: has a wave of this solve given up a wait for this source?
+__device__ __forceinline__ unsigned* lost_word(const SweepArgs& a, int src) { return queue_words(a, src) + 2; }
 
 // between two sweeps: every queue back to "no ticket taken, no owner"
 __device__ __forceinline__ void queue_reset(const SweepArgs& a, int src) {
@@ -361,26 +365,24 @@ __device__ __forceinline__ unsigned sweep_ticket(unsigned* q) {
 
 // Wait until both upstream columns have passed slab TK of this sweep (word >=
 // target), then drop stale L1 lines.  up: this lane's neighbour's word (lanes
-// 0 and 1) or NULL.  false if the wait was given up (never, unless a wave was
-// lost): the caller carries on, so that the launch ends, and poisons its
-// convergence sum, so that the source cannot be reported converged.
-__device__ __forceinline__ bool wait_upstream(const unsigned long long* up, unsigned long long target) {
-    unsigned long long start = 0;
-    bool ok = true;
-    for (;;) {
-        const unsigned long long v =
-            up ? __hip_atomic_load(up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : ~0ull;
-        if (__all(v >= target)) break;
-        __builtin_amdgcn_s_sleep(1);
-        const unsigned long long now = __builtin_amdgcn_s_memrealtime();
-        if (start == 0) start = now;
-        if (now - start > kWaitTicks) {
-            ok = false;
-            break;
-        }
+// 0 and 1) or NULL.  A wait that is given up (poll_until) marks the source as
+// lost; the caller carries on, so that the launch ends, and the source's
+// iteration ends as not converged (finish_iteration).
+__device__ __forceinline__ void wait_upstream(const unsigned long long* up, unsigned long long target, unsigned* lost) {
+    const bool ok = poll_until(
+        [&] {
+            const unsigned long long v =
+                up ? __hip_atomic_load(up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : ~0ull;
+            return (bool)__all(v >= target);
+        },
+        [&] { return (bool)__any(__hip_atomic_load(lost, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u); },
+        [] { __builtin_amdgcn_s_sleep(1); }, kWaitPolls);
+    if (!ok) {
+        __syncthreads();
+        if (threadIdx.x == 0) __hip_atomic_store(lost, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    return ok;
 }
 
 // this wave's stores are in the XCD's L2, then its column's progress says so
@@ -425,12 +427,13 @@ struct Handover {
     unsigned long long* own;       // this column's word, and its value when the slab is done
     unsigned long long done;
     bool more;                     // another slab follows
+    unsigned* lost;                // the source's lost word
 };
 
 // March one tile column: tile(TK) for every slab in order, each after its wait.
 // HELD: the tile publishes its slab itself.
 template <int DIR, bool HELD, class F>
-__device__ __forceinline__ bool march_column(const SweepArgs& a, const Geo& G, int src, int TI, int TJ, F tile) {
+__device__ __forceinline__ void march_column(const SweepArgs& a, const Geo& G, int src, int TI, int TJ, F tile) {
     unsigned long long* prog = progress_words(a, src);
     unsigned long long* own = prog + TI * G.nt[1] + TJ;
     const unsigned long long* up = nullptr;
@@ -440,13 +443,11 @@ __device__ __forceinline__ bool march_column(const SweepArgs& a, const Geo& G, i
     // that a finished earlier sweep's word is below every target of this one
     const unsigned long long base = ((unsigned long long)a.iter[src] * 8 + DIR + 1) << 16;
     const int hi = col_tile_hi(G, TI + TJ);
-    bool ok = true;
     for (int TK = col_tile_lo(G, TI + TJ); TK <= hi; ++TK) {
         const unsigned long long done = TK < hi ? base + TK + 1 : base + 0xffffu;
-        ok = tile(TK, Handover{up, base + TK + 1, own, done, TK < hi}) && ok;
+        tile(TK, Handover{up, base + TK + 1, own, done, TK < hi, lost_word(a, src)});
         if (!HELD) publish(own, done);
     }
-    return ok;
 }
 
 // Staged tile: the (8+2) x (8+2) columns of the tile and its i'/j' halo, each
@@ -887,15 +888,15 @@ __device__ __forceinline__ void fwd_column(const SweepArgs& a, const Geo& G, int
     first = win_first<DIR, TKC>(G, c, fld, lo, hi);
 #pragma unroll
     for (int u = 0; u < kPre; ++u) fwd_fetch<DIR>(c, mdl, t2, c.t0 + u, ring[u]);
-    const bool ok = march_column<DIR, true>(a, G, src, TI, TJ, [&](int TK, const Handover& h) {
+    march_column<DIR, true>(a, G, src, TI, TJ, [&](int TK, const Handover& h) {
         slab_ctx<DIR, true>(G, S, c, TK * TKC, TKC);
         if (c.t1 <= c.t0) {  // a ragged column's slab with no nodes
             publish(h.own, h.done);
-            return true;
+            return;
         }
         win_put<DIR, TKC>(c, lds, pf);
         win_put_first<DIR, TKC>(lds, own, first);
-        const bool waited = wait_upstream(h.up, h.target);
+        wait_upstream(h.up, h.target, h.lost);
         win_halo<DIR, TKC>(G, c, fld, lo, hi, lds);
         __syncthreads();
         // t0 is a multiple of 8, and so of a group's steps; steps past t1 are off
@@ -924,9 +925,8 @@ __device__ __forceinline__ void fwd_column(const SweepArgs& a, const Geo& G, int
         win_store<DIR, TKC, false>(G, c, fld, lds);
         fwd_kface_nodes<DIR>(G, S, c, fld, lds, own, Win::Lp, eps);
         __syncthreads();
-        return waited;
     });
-    eps = wave_sum(ok ? eps : HUGE_VAL);
+    eps = wave_sum(eps);
     if (c.lane == 0) part_add(a.part + (long long)src * a.nslots + TI * G.nt[1] + TJ, DIR, eps);
 }
 
@@ -1071,7 +1071,6 @@ __device__ __forceinline__ void fwd_line_column(const SweepArgs& a, const Geo& G
     const int u0 = kBI * (TI + TJ) - 1 - delta;  // u of step t = 0 of walk 0
     int own = (c.li + 1) * kLineRow + (c.lj + 1) * 32;
     double eps = 0.0;
-    bool ok = true;
     FwdSlot ring[kPre];
     d2a pf[10];
     slab_ctx<DIR, true>(G, S, c, u0, kLine);
@@ -1089,7 +1088,7 @@ __device__ __forceinline__ void fwd_line_column(const SweepArgs& a, const Geo& G
         slab_ctx<DIR, true>(G, S, c, u0 + m * kLine, kLine);
         if (m < nlines) {
             line_put<DIR>(c, lds, m, pf);
-            ok = wait_upstream(up, base + m + 1) && ok;
+            wait_upstream(up, base + m + 1, lost_word(a, src));
             line_halo<DIR>(G, c, fld, m, lds);
         }
         __syncthreads();
@@ -1139,7 +1138,7 @@ __device__ __forceinline__ void fwd_line_column(const SweepArgs& a, const Geo& G
         if (cur_too) line_store<DIR, false>(G, c, fld, m, lds);
         __syncthreads();
     }
-    eps = wave_sum(ok ? eps : HUGE_VAL);
+    eps = wave_sum(eps);
     if (c.lane == 0) part_add(a.part + (long long)src * a.nslots + TI * G.nt[1] + TJ, DIR, eps);
 }
 
@@ -1180,13 +1179,13 @@ __global__ void __launch_bounds__(64, TKC == 16 ? 2 : 3) k_fwd_sweep(SweepArgs a
             double* __restrict__ fld = a.field + (long long)src * G.N;
             const int own = ((c.li + 1) * kTC + c.lj + 1) * Lp;
             double eps = 0.0;
-            const bool ok = march_column<DIR, false>(a, G, src, TI, TJ, [&](int TK, const Handover& h) {
+            march_column<DIR, false>(a, G, src, TI, TJ, [&](int TK, const Handover& h) {
                 slab_ctx<DIR>(G, S, c, TK * G.tk, G.tk);
-                if (c.t1 <= c.t0) return true;  // a ragged column's slab with no nodes
+                if (c.t1 <= c.t0) return;  // a ragged column's slab with no nodes
                 FwdSlot ring[kPre];
 #pragma unroll
                 for (int u = 0; u < kPre; ++u) fwd_fetch<DIR>(c, mdl, t2, c.t0 + u, ring[u]);
-                const bool waited = wait_upstream(h.up, h.target);
+                wait_upstream(h.up, h.target, h.lost);
                 stage_tile<DIR>(G, c, fld, -(long long)src * G.N, (long long)(a.nsrc - src) * G.N - 2, lds);
                 __syncthreads();
                 // the step count is padded to a multiple of kPre (the LDS reads of a padded step
@@ -1201,9 +1200,8 @@ __global__ void __launch_bounds__(64, TKC == 16 ? 2 : 3) k_fwd_sweep(SweepArgs a
                 __syncthreads();
                 unstage_tile<DIR>(G, c, fld, lds, Lp);
                 fwd_kface_nodes<DIR>(G, S, c, fld, lds, own, Lp, eps);
-                return waited;
             });
-            eps = wave_sum(ok ? eps : HUGE_VAL);
+            eps = wave_sum(eps);
             if (c.lane == 0) part_add(a.part + (long long)src * a.nslots + TI * G.nt[1] + TJ, DIR, eps);
         });
     }
@@ -1278,16 +1276,11 @@ __device__ __forceinline__ void finish_iteration(const SweepArgs& a, int src, do
     const int it = a.iter[src] + 1;
     a.iter[src] = it;
     if (a.eps_hist) a.eps_hist[(long long)src * a.hist_stride + (it - 1)] = eps;
-    if (eps < a.tol) {
-        a.status[src] = it;
+    const Outcome o = iteration_outcome(eps, a.tol, it, a.max_iter, *lost_word(a, src) != 0u);
+    a.status[src] = o.status;
+    if (o.done) {
         a.active[src] = 0;
         atomicSub(a.counter, 1);
-    } else if (it >= a.max_iter) {
-        a.status[src] = -it;
-        a.active[src] = 0;
-        atomicSub(a.counter, 1);
-    } else {
-        a.status[src] = -it;
     }
 }
 
@@ -1599,9 +1592,8 @@ __device__ __forceinline__ void adj_kface_nodes(const Geo& G, const TileCtx& c, 
 }
 
 template <int DIR, bool RHS, bool COMPACT>
-__device__ __forceinline__ bool adj_tile(const SweepArgs& a, const Geo& G, const Src& S, const TileCtx& c, int src,
-                                         double* lds, const unsigned long long* up, unsigned long long target,
-                                         double& dsum, double& asum) {
+__device__ __forceinline__ void adj_tile(const SweepArgs& a, const Geo& G, const Src& S, const TileCtx& c, int src,
+                                         double* lds, const Handover& h, double& dsum, double& asum) {
     using D = Dir<DIR>;
     constexpr bool last = (DIR == 7);
     double* __restrict__ fld = a.field + (long long)src * G.N;
@@ -1616,7 +1608,7 @@ __device__ __forceinline__ bool adj_tile(const SweepArgs& a, const Geo& G, const
     for (int u = 0; u < kPreAdj; ++u) adj_fetch<DIR, RHS, COMPACT>(c, cf, rh, xb, c.t0 + u, ring[u]);
     AdjFace face;
     if (a.kfaces) adj_kface_load<DIR>(a, G, S, c, src, face);
-    const bool waited = wait_upstream(up, target);
+    wait_upstream(h.up, h.target, h.lost);
     stage_tile<DIR>(G, c, fld, -(long long)src * G.N, (long long)(a.nsrc - src) * G.N - 2, lds);
     __syncthreads();
 
@@ -1657,7 +1649,6 @@ __device__ __forceinline__ bool adj_tile(const SweepArgs& a, const Geo& G, const
     __syncthreads();
     unstage_tile<DIR>(G, c, fld, lds, Lp);
     if (a.kfaces) adj_kface_nodes<DIR>(G, c, fld, lds, own, Lp, face, dsum, asum);
-    return waited;
 }
 
 // TKC: compile-time tile depth as for k_fwd_sweep (0: from the geometry)
@@ -1670,15 +1661,16 @@ __global__ void __launch_bounds__(64, 3) k_adj_sweep(SweepArgs a, int c0, int cn
         const Src S = a.src[src];
         TileCtx c = col_ctx<DIR>(G, S, TI, TJ);
         double dsum = 0.0, asum = 0.0;
-        const bool ok = march_column<DIR, false>(a, G, src, TI, TJ, [&](int TK, const Handover& h) {
+        march_column<DIR, false>(a, G, src, TI, TJ, [&](int TK, const Handover& h) {
             slab_ctx<DIR>(G, S, c, TK * G.tk, G.tk);
-            if (c.t1 <= c.t0) return true;  // a ragged column's slab with no nodes
+            if (c.t1 <= c.t0) return;  // a ragged column's slab with no nodes
             // wave-uniform: only tiles that meet the right-hand side read it
             if (tile_meets_box<DIR>(G, c, a.box + src * 6))
-                return adj_tile<DIR, true, COMPACT>(a, G, S, c, src, lds, h.up, h.target, dsum, asum);
-            return adj_tile<DIR, false, COMPACT>(a, G, S, c, src, lds, h.up, h.target, dsum, asum);
+                adj_tile<DIR, true, COMPACT>(a, G, S, c, src, lds, h, dsum, asum);
+            else
+                adj_tile<DIR, false, COMPACT>(a, G, S, c, src, lds, h, dsum, asum);
         });
-        dsum = wave_sum(ok ? dsum : HUGE_VAL);
+        dsum = wave_sum(dsum);
         asum = wave_sum(asum);
         if (c.lane == 0) {
             part_add(a.part + (long long)src * a.nslots + TI * G.nt[1] + TJ, DIR, dsum);
