@@ -51,14 +51,16 @@ __device__ __align__(256) unsigned char scratch[kScratchBytes];
 // tiles from the sweep's first corner to its last, which shorter tiles cut
 // finer; one that fills the chip several times over is bound by what its tiles
 // move, which deeper tiles move less of.  Measured at depths 16 and 28
-// (forward), 16 and 40 (adjoint):
-//   41^3 x 1 source (25 columns)   forward 8.9 / 15.4 ms    adjoint 10.7 / 14.1 ms
+// (forward), 16 and 40 (adjoint), in place, ms:
+//   41^3 x 1 source (25 columns)   forward 8.9 / 15.4       adjoint 10.7 / 14.1
 //   61^3 x 16 (1024)                       28.2 / -                 38.6 / 51.0
 //   61^3 x 32 (2048)                       34.3 / 49.3              57.7 / 60.6
-//   61^3 x 64 (4096)                       54.5 / 56.0             100.1 / 76.8
-//   101^3 x 32 (5408)                     152.0 / 152.4
+//   33 x 25 x 82 x 300 (3600)              49.9 / 44.8             117.8 / 80.5
+//   61^3 x 64 (4096)                       53.5 / 54.1             103.7 / 74.9
+//   101^3 x 40 (6760)                     161.7 / 158.5            371.7 / 247.1
 //   101^3 x 128 (21632)                   421.0 / 353.3            828.1 / 589.2
-// (forward, in whole lines where lines_of says so: 61^3 x 64 49.5)
+// (forward, in whole lines where lines_of says so: 61^3 x 64 47.0, 33 x 25 x 82 x 300
+// 44.9, 101^3 x 40 160.1)
 constexpr int kDefaultTileK = 32;
 constexpr int kDefaultTileKFwd = 16;
 constexpr int kDefaultTileKAdj = 16;
@@ -127,12 +129,19 @@ bool lines_of(const tt_grid* g, int nsrc) {
 // Number of concurrently iterated source groups of a solve.  A sweep launch
 // leaves the chip partly idle at its first and last columns, where a second
 // group's launch can run; a batch of many columns hardly has such ends, and a
-// batch of few never fills the chip, so that groups only take turns.  Forward
-// with 1 and 2 groups: 256 columns (61^3 x 4) 24.3 / 25.9 ms, 1024 (x 16) 28.2 /
-// 28.3, 2048 (x 32) 41.7 / 34.3; slabs of 28 on 101^3 x 128 354 / 355, whole lines
-// on 61^3 x 256 113.2 / 107.1.  Adjoint with 1, 2 and 4: 408 columns (32 x 25 x 82,
-// 34 sources) 24.6 / 25.2 / 25.9, 512 (61^3 x 8) 30.0 / 32.9 / 35.2, 1024 43.8 / 38.6
-// / 42.7, 2048 - / 69 / 58; 61^3 x 128 with 2 and 4 118.3 / 119.6, 101^3 x 128 589 / 598.
+// batch of few never fills the chip, so that groups only take turns.
+// Forward, 1 and 2 groups (ms): 256 columns (61^3 x 4) 24.3 / 25.9; 512 (61^3 x 8)
+// 24.1 / 25.9; 768 to 845 27.5 / 26.9 (61^3 x 12), 21.6 / 20.3 (33 x 25 x 82 x 64), 83 / 93
+// (101^3 x 5); 1014 (101^3 x 6) 80 / 91, 1024 (61^3 x 16) 29.0 / 29.4; 1152 (33 x 25 x 82
+// x 96) 26.0 / 22.9; 1536 30.3 / 25.1; 2048 (61^3 x 32) 43.7 / 36.1; slabs of 28 on 101^3
+// x 128 354 / 355, whole lines on 61^3 x 256 113.2 / 107.1.
+// Adjoint, 1, 2 and 4 groups: 408 columns (32 x 25 x 82, 34 sources) 24.6 / 25.2 / 25.9;
+// 512 30.0 / 32.5 / 35.9; 768 to 800 41.6 / 37.7 / 39.8, 33.1 / 31.5 / 30.6, 18.7 / 17.6 /
+// 17.5 (41^3 x 32); 1024 42.1 / 37.6 / 41.2; 1536 (33 x 25 x 82 x 128) 60.2 / 51.7 / 49.5,
+// 1600 (41^3 x 64) 28.3 / 24.4 / 23.2; 2040 82.1 / 68.4 / 62.7, 2048 68.1 / 61.2 / 54.3; 2400
+// (41^3 x 96) 40.1 / 34.9 / 30.6, 2556 101.7 / 85.9 / 76.8; 3072 73.8 / 67.7 / 70.9 (61^3 x
+// 48) but 78.0 / 73.0 / 67.8 (33 x 25 x 82 x 256); 61^3 x 128 - / 118.3 / 119.6, 101^3 x 128
+// - / 589 / 598.  (At least 8 sources a group, one for each XCD.)
 int groups_of(const tt_opts* o, const tt_grid* grid, int nsrc, int which, bool lines = false) {
     const long long cols = batch_columns(grid, nsrc);
     int g;

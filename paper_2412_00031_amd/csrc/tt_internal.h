@@ -141,13 +141,10 @@ __device__ __forceinline__ double rsqrt_nr(double x) {
 }
 
 // T0 and its scaled gradient t at a node of column c with axis-2 table value
-// (c2, s2) = (cos phi, sin phi) or (x, 0); rq = 1/sqrt(Q) = s0 / T0 (0 at the
-// source itself, where the factor vanishes).  OFF_SOURCE: the caller never
-// asks at the source itself (Q > 0; the sweeps skip the fixed cell), so there
-// is no branch.
-template <int COORD, bool OFF_SOURCE = false>
-__device__ __forceinline__ void factor(const Src& S, const Col& c, double c2, double s2, double& T0, double t[3],
-                                       double& rq) {
+// (c2, s2) = (cos phi, sin phi) or (x, 0); zeros at the source itself, where the
+// factor vanishes.
+template <int COORD>
+__device__ __forceinline__ void factor(const Src& S, const Col& c, double c2, double s2, double& T0, double t[3]) {
     double d0, d1, d2;
     if (COORD == 1) {
         // (one rounding each, whichever of the products the caller keeps over a loop)
@@ -166,13 +163,12 @@ __device__ __forceinline__ void factor(const Src& S, const Col& c, double c2, do
     double m1 = S.mi11 * d1 + S.mi12 * d2;
     double m2 = S.mi12 * d1 + S.mi22 * d2;
     double Q = d0 * m0 + d1 * m1 + d2 * m2;
-    if (!OFF_SOURCE && !(Q > 0.0)) {
+    if (!(Q > 0.0)) {
         T0 = 0.0;
         t[0] = t[1] = t[2] = 0.0;
-        rq = 0.0;
         return;
     }
-    rq = rsqrt_nr(Q);
+    const double rq = rsqrt_nr(Q);
     T0 = S.s0 * (Q * rq);
     double f = S.s0 * rq;
     if (COORD == 1) {
@@ -190,12 +186,6 @@ __device__ __forceinline__ void factor(const Src& S, const Col& c, double c2, do
         t[1] = f * m1;
         t[2] = f * m2;
     }
-}
-
-template <int COORD>
-__device__ __forceinline__ void factor(const Src& S, const Col& c, double c2, double s2, double& T0, double t[3]) {
-    double rq;
-    factor<COORD, false>(S, c, c2, s2, T0, t, rq);
 }
 
 // Local state of the factored Hamiltonian at an interior node: P, M P, H.

@@ -705,8 +705,8 @@ __device__ __forceinline__ d2u win_pair(const Geo& G, const TileCtx& c, const do
     return *reinterpret_cast<const d2u*>(fld + min(max((int)x, lo), hi));
 }
 
-// loads R0 .. R1 - 1 of the entries that the slab at kq0 adds
-template <int DIR, int TKC, int R0, int R1>
+// the entries that the slab at kq0 adds
+template <int DIR, int TKC>
 __device__ __forceinline__ void win_load(const Geo& G, const TileCtx& c, const double* __restrict__ fld, int lo, int hi,
                                          int kq0, d2u (&pf)[Window<DIR, TKC>::nload]) {
     using W = Window<DIR, TKC>;
@@ -714,7 +714,7 @@ __device__ __forceinline__ void win_load(const Geo& G, const TileCtx& c, const d
     const int sub = lane / W::pairs, q = 2 * (lane % W::pairs);
     const unsigned org = win_org<DIR>(G, c, kq0);
 #pragma unroll
-    for (int r = R0; r < R1; ++r) {
+    for (int r = 0; r < W::nload; ++r) {
         int ci, cj;
         W::col(r, sub, ci, cj);
         // slots q + 2, q + 3 hold entries q + 2, q + 3; mirrored, slots q, q + 1 hold Lp - 1 - q and the one below
@@ -884,7 +884,7 @@ __device__ __forceinline__ void fwd_column(const SweepArgs& a, const Geo& G, int
     FwdSlot ring[kPre];
     d2u pf[nl], first;
     slab_ctx<DIR, true>(G, S, c, col_tile_lo(G, TI + TJ) * TKC, TKC);
-    win_load<DIR, TKC, 0, nl>(G, c, fld, lo, hi, c.kq0, pf);
+    win_load<DIR, TKC>(G, c, fld, lo, hi, c.kq0, pf);
     first = win_first<DIR, TKC>(G, c, fld, lo, hi);
 #pragma unroll
     for (int u = 0; u < kPre; ++u) fwd_fetch<DIR>(c, mdl, t2, c.t0 + u, ring[u]);
@@ -905,7 +905,7 @@ __device__ __forceinline__ void fwd_column(const SweepArgs& a, const Geo& G, int
             asm volatile("" : "+v"(c.rr0), "+v"(c.tt0), "+v"(own));  // (or the addresses of all groups are formed at once)
             // loads return in order: the next window's, from memory, go out together in front of
             // one group's record loads, so that the records wait for them once a slab
-            if (g == 0 && h.more) win_load<DIR, TKC, 0, nl>(G, c, fld, lo, hi, c.kq0 + TKC, pf);
+            if (g == 0 && h.more) win_load<DIR, TKC>(G, c, fld, lo, hi, c.kq0 + TKC, pf);
             if (g * kPre < c.t0 || g * kPre >= c.t1) return;
 #pragma unroll
             for (int u = 0; u < kPre; ++u) {
@@ -977,15 +977,15 @@ __device__ __forceinline__ int line_addr(const Geo& G, const TileCtx& c, int ci,
            (stage_origin<D::s1>(G, 1, c.TJ) + D::s1 * cj) * (int)G.sj;
 }
 
-// loads R0 .. R1 - 1 of line m: eight columns of the tile and its downstream halo
-// each (columns past a ragged tile's halo re-read its last one)
-template <int DIR, int R0, int R1>
+// line m of the tile's own columns and its downstream halo, eight columns a load
+// (columns past a ragged tile's halo re-read its last one)
+template <int DIR>
 __device__ __forceinline__ void line_load(const Geo& G, const TileCtx& c, const double* __restrict__ fld, int m,
                                           d2a (&pf)[10]) {
     const int lane = opaque_lane(c);
     const int sub = lane >> 3, e = line_elem<DIR>(G, m) + 2 * (lane & 7);
 #pragma unroll
-    for (int r = R0; r < R1; ++r) {
+    for (int r = 0; r < 10; ++r) {
         int ci, cj;
         Window<DIR, kLine>::col(r, sub, ci, cj);
         pf[r] = *reinterpret_cast<const d2a*>(fld + line_addr<DIR>(G, c, min(ci, c.ext_i + 1), min(cj, c.ext_j + 1)) + e);
@@ -1074,7 +1074,7 @@ __device__ __forceinline__ void fwd_line_column(const SweepArgs& a, const Geo& G
     FwdSlot ring[kPre];
     d2a pf[10];
     slab_ctx<DIR, true>(G, S, c, u0, kLine);
-    line_load<DIR, 0, 10>(G, c, fld, 0, pf);
+    line_load<DIR>(G, c, fld, 0, pf);
     const int tf = (delta + 1) & ~(kPre - 1);  // the first group with a node, counted from walk 0
 #pragma unroll
     for (int u = 0; u < kPre; ++u) fwd_fetch<DIR>(c, mdl, t2, tf + u, ring[u]);
@@ -1097,7 +1097,7 @@ __device__ __forceinline__ void fwd_line_column(const SweepArgs& a, const Geo& G
             int kap = kLine * m - 1 - c.li - c.lj + g * kPre;
             asm volatile("" : "+v"(c.rr0), "+v"(c.tt0), "+v"(own), "+v"(kap));  // (or the addresses of all groups are formed at once)
             // together and ahead of a group's record loads, as in fwd_column
-            if (g == 0 && m + 1 < nlines) line_load<DIR, 0, 10>(G, c, fld, m + 1, pf);
+            if (g == 0 && m + 1 < nlines) line_load<DIR>(G, c, fld, m + 1, pf);
             if (g * kPre + kPre <= c.t0 || g * kPre >= c.t1) return;
             double upk = lds[own + line_slot<DIR>(kap - 1)], cur = lds[own + line_slot<DIR>(kap)];
             int at = own + line_slot<DIR>(kap);
