@@ -80,7 +80,7 @@ typedef struct tt_opts {
                           grid and batch size (tt_solve_form tells which).  A
                           given depth is taken as it is: on batches of 3000 tile
                           columns of 8 x 8 nodes or more, shallow ones are slower
-                          than the default by up to 2.5 times (depth 8: 1.8).
+                          than the default (depth 4 up to 3 times, 8 twice).
                           Results do not depend on it. */
     int32_t flags;     /* bit 0 (TT_FLAG_TIME_SWEEPS): time the sweep kernels with a HIP
                           event pair around the launches of every
