@@ -283,14 +283,6 @@ __device__ __forceinline__ double rsqrt_3(double x) {
     const double e = fma(-(x * y), y, 1.0);
     return fma(y, e * fma(0.375, e, 0.5), y);
 }
-// 1 / sqrt(x) correctly rounded but for a few cases in a thousand: as rsqrt_3, with
-// the residual e free of the rounding of x y
-__device__ __forceinline__ double rsqrt_c(double x) {
-    const double y = __builtin_amdgcn_rsq(x);
-    const double t = x * y;
-    const double e = fma(-fma(x, y, -t), y, fma(-t, y, 1.0));
-    return fma(y, e * fma(0.375, e, 0.5), y);
-}
 __device__ __forceinline__ double sqrt_3(double x) {
     const double y = __builtin_amdgcn_rsq(x);
     const double t = x * y;

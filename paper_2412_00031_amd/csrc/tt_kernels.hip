@@ -26,7 +26,7 @@
 //     records side by side on every step.
 // Each sweep is followed by a boundary pass (one thread per boundary node), and
 // each iteration by a finalize kernel that forms the convergence measure from
-// per-tile partial sums in a fixed order (bitwise reproducible run to run).
+// the columns' partial sums in a fixed order (bitwise reproducible run to run).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -2069,7 +2069,7 @@ __global__ void __launch_bounds__(256) k_kernel_accum(Geo G, Tabs T, const Src* 
                 const double p1 = T0 * (c[u].g1 * (vp[u] - vm[u]) * G.inv2h[1]) + tx * t[1];
                 const double p2 = T0 * (c[u].g2 * d2 * G.inv2h[2]) + tx * t[2];
                 const double h2 = p0 * p0 + p1 * (ma[u] * p1 + mb[u] * p2) + p2 * (mb[u] * p1 + mc[u] * p2);
-                const double lh = l[u] * rsqrt_c(h2);  // lambda / H
+                const double lh = l[u] * rsqrt_3(h2);  // lambda / H
                 if (!in_fixed(S, i0 + u, j, k)) {
                     gs[u] += l[u];
                     gx[u] += lh * (p1 * p1 - p2 * p2);
