@@ -112,6 +112,27 @@ long long batch_columns(const tt_grid* g, int nsrc) {
     return (long long)((g->n[0] + 5) / 8) * ((g->n[1] + 5) / 8) * nsrc;
 }
 
+// Do an adjoint solve's sweeps walk deep slabs?  Where many columns fill the chip
+// (kDeepColumns); where each of the n0 + n1 + n2 levels that a sweep passes one after
+// the other holds enough nodes that moving them outlasts the hand-overs; and where the
+// batch's records (28 bytes a node and more) are beyond the 256 MB cache behind the
+// L2s.  Depths 16 and 40, each with its best number of groups, ms:
+//   by level:    41^3 x 49 (27e3 nodes a level) 20.5 / 22.2, x 65 (36e3) 23.8 / 23.8, x 100
+//     (56e3) 32.0 / 28.2; 61^3 x 23 (29e3) 46.4 / 56.8, x 32 (40e3) 56.3 / 62.3, x 33
+//     (41e3) 62.9 / 59.9, x 41 (51e3) 74.2 / 66.9; 33 x 25 x 82 x 97 (47e3) 39.8 / 40.5, x 170
+//     (82e3) 61.2 / 55.1; 25^3 x 200 (42e3) 13.0 / 12.7
+//   by nodes:    81^3 x 16 (8.5e6) 67.2 / 75.1, x 18 (9.6e6) 78.2 / 77.9, x 24 (12.8e6) 88.3 /
+//     83.3; 101^3 x 8 (8.2e6) 121.0 / 145.9, x 9 (9.3e6) 154.8 / 149.3, x 18 (18.5e6) 199.7 / 157.2
+//   by columns:  101 x 101 x 25 x 24 (4056 columns, 27e3 a level) 87.8 / 78.5
+constexpr double kDeepLevel = 40.2e3;
+constexpr double kDeepNodes = 9.0e6;
+
+bool adjoint_deep(const tt_grid* g, int nsrc) {
+    const double nodes = (double)g->n[0] * g->n[1] * g->n[2] * nsrc;
+    return batch_columns(g, nsrc) >= kDeepColumns || nodes >= kDeepLevel * (g->n[0] + g->n[1] + g->n[2]) ||
+           nodes >= kDeepNodes;
+}
+
 // Does a forward solve keep its fields in the workspace, in rows padded to whole
 // lines (k_fwd_lines), at the default tile depth?  Lines 16 nodes deep against
 // slabs of 28 steps: 61^3 x 64 49.5 / 56.2 ms, x 128 66.0 / 70.3, x 256 107.1 /
@@ -135,13 +156,16 @@ bool lines_of(const tt_grid* g, int nsrc) {
 // (101^3 x 5); 1014 (101^3 x 6) 80 / 91, 1024 (61^3 x 16) 29.0 / 29.4; 1152 (33 x 25 x 82
 // x 96) 26.0 / 22.9; 1536 30.3 / 25.1; 2048 (61^3 x 32) 43.7 / 36.1; slabs of 28 on 101^3
 // x 128 354 / 355, whole lines on 61^3 x 256 113.2 / 107.1.
-// Adjoint, 1, 2 and 4 groups: 408 columns (32 x 25 x 82, 34 sources) 24.6 / 25.2 / 25.9;
-// 512 30.0 / 32.5 / 35.9; 768 to 800 41.6 / 37.7 / 39.8, 33.1 / 31.5 / 30.6, 18.7 / 17.6 /
-// 17.5 (41^3 x 32); 1024 42.1 / 37.6 / 41.2; 1536 (33 x 25 x 82 x 128) 60.2 / 51.7 / 49.5,
-// 1600 (41^3 x 64) 28.3 / 24.4 / 23.2; 2040 82.1 / 68.4 / 62.7, 2048 68.1 / 61.2 / 54.3; 2400
-// (41^3 x 96) 40.1 / 34.9 / 30.6, 2556 101.7 / 85.9 / 76.8; 3072 73.8 / 67.7 / 70.9 (61^3 x
-// 48) but 78.0 / 73.0 / 67.8 (33 x 25 x 82 x 256); 61^3 x 128 - / 118.3 / 119.6, 101^3 x 128
-// - / 589 / 598.  (At least 8 sources a group, one for each XCD.)
+// Adjoint, 1, 2, 3 and 4 groups: 408 columns (33 x 25 x 82 x 34) 25.8 / 26.2 / 26.2 / 27.0;
+// 512 (61^3 x 8) 30.0 / 32.5 / - / 35.9; 576 (61^3 x 9) 40.6 / 35.2 / 37.4 / 38.5; 600
+// (41^3 x 24) 15.5 / 15.2 / 15.2 / 15.7; 1024 (61^3 x 16) 43.5 / 38.8 / 42.5 / 44.1; 1472 (61^3 x
+// 23) 58.9 / 52.7 / 46.4 / 50.7; 1536 (33 x 25 x 82 x 128) 61.6 / 51.6 / 50.2 / 49.9; 2048 (61^3
+// x 32) 73.6 / 63.4 / 63.4 / 56.3.  In deep slabs: 1521 (101^3 x 9) 153.5 / 150.2 / 150.4 / 149.4;
+// 3008 (61^3 x 47) 78.4 / 72.8 / 73.5 / 74.2; 3600 (33 x 25 x 82 x 300) 89.0 / 81.8 / 77.8 / 76.9;
+// 4096 (61^3 x 64) 79.8 / 75.4 / 77.9 / 76.4; 4225 (101^3 x 25) 200 / 199 / 190 / 188; 5577 (101 x
+// 101 x 25 x 33) 93.0 / 98.0 / 92.0 / 91.4; 6760 (101^3 x 40) 237 / 230 / 225 / 232; 8192
+// (61^3 x 128) 122 / 115 / 115 / 117; 16384 (61^3 x 256) - / 199 / 199 / 203; 21632 (101^3 x 128)
+// - / 584 / 585 / 593.
 int groups_of(const tt_opts* o, const tt_grid* grid, int nsrc, int which, bool lines = false) {
     const long long cols = batch_columns(grid, nsrc);
     int g;
@@ -152,13 +176,21 @@ int groups_of(const tt_opts* o, const tt_grid* grid, int nsrc, int which, bool l
     else if (which == 0)
         g = cols < 1024 || (cols >= kDeepColumns && !lines) ? 1 : 2;
     else
-        g = cols < 768 ? 1 : (cols < 1536 || cols >= kDeepColumns ? 2 : 4);
-    if (!(o && o->groups > 0)) g = std::max(1, std::min(g, nsrc / 8));
+        g = cols < 512 ? 1 : (!adjoint_deep(grid, nsrc) ? 4 : (cols < 8192 ? 3 : 2));
+    // a group of its own for every eight sources (forward: every full eight) at most
+    if (!(o && o->groups > 0)) g = std::max(1, std::min(g, (which == 0 ? nsrc : nsrc + 7) / 8));
     return g > nsrc ? nsrc : g;
 }
 
-// first source of group q of G
-int group_begin(int nsrc, int G, int q) { return (int)(((long long)nsrc * q) / G); }
+// First source of group q of G.  A launch deals its sources to the XCDs one by one,
+// so that eight to the group (and one rest) leave no XCD a source more than it need
+// have.  Adjoint, equal groups against these: 61^3 x 36 in four 79.1 / 65.7 ms, x 41
+// 85.0 / 74.2, 41^3 x 100 34.8 / 32.0, 101^3 x 18 in two 176.6 / 157.4.
+int group_begin(int nsrc, int G, int q) {
+    const long long eights = (nsrc + 7) / 8;
+    if (G > eights) return (int)(((long long)nsrc * q) / G);
+    return (int)std::min<long long>(nsrc, 8 * (eights * q / G));
+}
 
 tt::Geo make_geo(const tt_grid* g, int tk) {
     tt::Geo G;
@@ -286,8 +318,8 @@ void bind_workspace(tt::Plan& P, void* ws, const Layout& L) {
 int tile_k_of(const tt_opts* o, int which, const tt_grid* g, int nsrc) {
     if (o && o->tile_k > 0) return o->tile_k;
     if (which > 1) return kDefaultTileK;
-    if (batch_columns(g, nsrc) >= kDeepColumns) return which == 0 ? kDeepTileKFwd : kDeepTileKAdj;
-    return which == 0 ? kDefaultTileKFwd : kDefaultTileKAdj;
+    if (which == 0) return batch_columns(g, nsrc) >= kDeepColumns ? kDeepTileKFwd : kDefaultTileKFwd;
+    return adjoint_deep(g, nsrc) ? kDeepTileKAdj : kDefaultTileKAdj;
 }
 
 // pinned host words that receive the active-source count of each iteration
