@@ -234,12 +234,12 @@ tt::Geo padded(tt::Geo G) {
 
 // Workspace layout (each region 256-byte aligned):
 //   Src[nsrc] | tab0[n0] | tab1[n1] | tab2[n2] | active[nsrc] | iter[nsrc] | counter |
-//   part[nsrc*nslots] (sums, sweep progress, queues) | model[4*Sa*4], pad[nsrc*Nf] if padded (forward) | part2[nsrc*nslots] (adjoint) |
+//   part[nsrc*nslots] (sums, sweep progress, queues) | lon[nsrc*n2], model[4*Sa*4], pad[nsrc*Nf] if padded (forward) | part2[nsrc*nslots] (adjoint) |
 //   coef[nsrc*4*Sa*6] (or [nsrc*N*6] compact) | diag[nsrc*N] | rhs[nsrc*N] | box[nsrc*6] | bnd_in, bnd_rhs[nsrc*NB]
 //   (adjoint; diag is dead once the right-hand side is formed, and the continuous solve puts bnd_rec[nsrc*3*NB] there)
 struct Layout {
     size_t off_src, off_t0, off_t1, off_t2, off_active, off_iter, off_counter, off_part, off_part2, off_coef,
-        off_diag, off_rhs, off_box, off_bnd, off_model, off_pad, total;
+        off_diag, off_rhs, off_box, off_bnd, off_lon, off_model, off_pad, total;
 };
 
 Layout layout(const tt::Geo& G, int nsrc, int nslots, int which, bool compact = false) {
@@ -259,12 +259,14 @@ Layout layout(const tt::Geo& G, int nsrc, int nslots, int which, bool compact = 
     L.off_rhs = o;
     L.off_box = o;
     L.off_bnd = o;
+    L.off_lon = o;
     L.off_model = o;
     L.off_pad = o;
     if (which == 0 || which == 1) {
         L.off_part = o; o = align_up(o + sizeof(double) * (size_t)nsrc * nslots);
     }
     if (which == 0) {
+        L.off_lon = o; o = align_up(o + sizeof(double2) * (size_t)nsrc * (size_t)G.n[2]);
         L.off_model = o; o = align_up(o + sizeof(double) * 4 * 4 * (size_t)G.Sa);
         L.off_pad = o;
         if (G.Nf != G.N) o = align_up(o + sizeof(double) * (size_t)nsrc * (size_t)G.Nf);
@@ -307,6 +309,7 @@ void bind_workspace(tt::Plan& P, void* ws, const Layout& L) {
     P.bnd_in = reinterpret_cast<double*>(b + L.off_bnd);
     P.bnd_rhs = P.bnd_in + (size_t)P.nsrc * (size_t)P.G.NB;
     P.bnd_rec = reinterpret_cast<double2*>(P.diag);
+    P.lon = reinterpret_cast<double2*>(b + L.off_lon);
     P.model = reinterpret_cast<double*>(b + L.off_model);
     P.pad = reinterpret_cast<double*>(b + L.off_pad);
     P.T.t0 = P.tab0;

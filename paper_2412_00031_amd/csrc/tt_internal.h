@@ -87,6 +87,8 @@ struct Src {
     double E[9];       // rows: source-frame unit vectors r^_s, theta^_s, phi^_s
     double mi11, mi12, mi22;  // lower-right block of M0^{-1}
     double s0;
+    double rh;         // distance from the axis, r cos theta (spherical)
+    double rhl, zl;    // what rounding left out of rh and of Xs[2]
     int fb[3];         // base corner of the fixed cell
     int pad;
 };
@@ -221,21 +223,27 @@ __device__ __forceinline__ void local_state(const Geo& G, const Src& S, const Co
 // The factor enters through T0 = s0 Q rq and its scaled gradient t = s0 rq u
 // (rq = 1 / sqrt(Q), u = m on the node's unit vectors, m = M0^{-1} d), so
 // P_a = T0 q_a + tau t_a = s0 rq R_a with R_a = Q q_a + tau u_a and
-// H = s0 rq sqrt(R . M R): the update forms R, not T0 and t.  Along a spherical
-// column X = (rct c2, rct s2, r sin th), so d = E (X - Xs) is d_i = A_i c2 + B_i s2 + C_i
-// with column constants A, B, C.
+// H = s0 rq sqrt(R . M R): the update forms R, not T0 and t.
 //
-// u needs no projection through the embedding.  The horizontal direction of the
-// node is (cos ths F, -sin ths F, S) in the source frame, with ths the source's
-// latitude and F, S the cosine and sine of the longitude difference, and the axis
-// is (sin ths, cos ths, 0).  So m is turned by the source's latitude, by the
-// longitude difference and by the node's latitude th:
+// Neither d = E (X - Xs) nor u needs the embedding.  With ths the source's latitude
+// and F, S the cosine and sine of the longitude difference, the horizontal direction
+// of the node is (cos ths F, -sin ths F, S) in the source frame and the axis is
+// (sin ths, cos ths, 0).  So with the column's distances D_r, D_z from the source,
+// away from the axis and along it,
+//   d_0 = cos ths (D_r + rct (F - 1)) + sin ths D_z,
+//   d_1 = cos ths D_z - sin ths (D_r + rct (F - 1)),  d_2 = rct S,
+// one operation each with column constants, and m is turned by the source's
+// latitude, by the longitude difference and by the node's latitude th:
 //   w = cos ths d_0 - sin ths m_1,  z = sin ths d_0 + cos ths m_1,
 //   g = F w + S m_2,                u_2 = F m_2 - S w,
-//   u_0 = cos th g + sin th z,      u_1 = cos th z - sin th g:
-// 16 operations where the projection took 17, and as exact up to the poles (u_1
-// from u_0 by a division by cos th is two cheaper and has 4 times its error at 86
-// degrees).
+//   u_0 = cos th g + sin th z,      u_1 = cos th z - sin th g.
+// F - 1 and S come from a table per source (k_lon), rounded once: F - 1 is small where
+// d is, and what the source's own coordinates lose to rounding is kept beside them, so
+// that nothing in d rounds at the Earth's radius (rms error of 12 iterations on 25^3 nodes
+// at latitude 80 1.4e-16, 4.8e-16 with d from the rounded embedding, 6.4e-16 with one that
+// is projected back).  3 and 12 operations; 6 and 16 with F and S formed in every update
+// (101^3 x 7 forward 89.7 / 93.0 ms, 61^3 x 17 29.7 / 31.1); u_1 from u_0 by a division by
+// cos th is one operation cheaper still but has 4 times the error at 86 degrees.
 //
 // The average of the neighbours sum_a w_a p_a, p_a = up_a + dn_a, has weights of sum
 // 1/2 that add up to it in doubles only nearly; what they miss shifts every node the
@@ -246,7 +254,7 @@ struct LfCol {
     double w1, w2;      // averaging weights w_a
     double rho;
     double ct, st;      // the column's latitude (spherical)
-    double A[3], B[3], C[3];  // d_i along the column (spherical); Cartesian: C = (x0, y) - Xs
+    double rct, A[2], C[2];  // d along the column: d_i = A_i (F - 1) + C_i (spherical); Cartesian: C = (x0, y) - Xs
 };
 
 template <int COORD>
@@ -261,14 +269,15 @@ __device__ __forceinline__ LfCol lf_col(const Geo& G, const Src& S, const Col& c
     W.ct = c.ct;
     W.st = c.st;
     if (COORD == 1) {
-        const double D2 = fma(c.x0, c.st, -S.Xs[2]);
-        for (int i = 0; i < 3; ++i) {
-            W.A[i] = c.rct * S.E[3 * i];
-            W.B[i] = c.rct * S.E[3 * i + 1];
-            W.C[i] = D2 * S.E[3 * i + 2] - (S.Xs[0] * S.E[3 * i] + S.Xs[1] * S.E[3 * i + 1]);
-        }
+        const double sts = S.E[2], cts = S.E[5];
+        const double Dr = fma(c.x0, c.ct, -S.rh) - S.rhl, Dz = fma(c.x0, c.st, -S.Xs[2]) - S.zl;
+        W.rct = c.rct;
+        W.A[0] = c.rct * cts;
+        W.A[1] = -(c.rct * sts);
+        W.C[0] = fma(Dr, cts, Dz * sts);
+        W.C[1] = fma(Dz, cts, -(Dr * sts));
     } else {
-        W.A[0] = W.A[1] = W.A[2] = W.B[0] = W.B[1] = W.B[2] = W.C[2] = 0.0;
+        W.rct = W.A[0] = W.A[1] = 0.0;
         W.C[0] = c.x0 - S.Xs[0];
         W.C[1] = c.ct - S.Xs[1];
     }
@@ -290,20 +299,21 @@ __device__ __forceinline__ double sqrt_3(double x) {
     return fma(t, e * fma(0.375, e, 0.5), t);
 }
 
+// (f1, sn) = (F - 1, S), or (distance along axis 2, 0).
 // (every contraction is spelled out: all instances round alike)
 template <int COORD>
-__device__ __forceinline__ double lf_update(const Geo& G, const Src& S, const LfCol& W, double c2, double s2, double sx,
+__device__ __forceinline__ double lf_update(const Geo& G, const Src& S, const LfCol& W, double f1, double sn, double sx,
                                             double ma, double mb, double mc, double tx, double up0, double dn0,
                                             double up1, double dn1, double up2, double dn2) {
     double d0, d1, d2;
     if (COORD == 1) {
-        d0 = fma(c2, W.A[0], fma(s2, W.B[0], W.C[0]));
-        d1 = fma(c2, W.A[1], fma(s2, W.B[1], W.C[1]));
-        d2 = fma(c2, W.A[2], fma(s2, W.B[2], W.C[2]));
+        d0 = fma(f1, W.A[0], W.C[0]);
+        d1 = fma(f1, W.A[1], W.C[1]);
+        d2 = W.rct * sn;
     } else {
         d0 = W.C[0];
         d1 = W.C[1];
-        d2 = c2 - S.Xs[2];
+        d2 = f1;
     }
     const double m1 = fma(S.mi11, d1, S.mi12 * d2);
     const double m2 = fma(S.mi12, d1, S.mi22 * d2);
@@ -311,13 +321,12 @@ __device__ __forceinline__ double lf_update(const Geo& G, const Src& S, const Lf
     const double rq = rsqrt_3(Q);
     double u0, u1, u2;
     if (COORD == 1) {
-        const double sts = S.E[2], cts = S.E[5], sps = -S.E[6], cps = S.E[7];
-        const double F = fma(c2, cps, s2 * sps), D = fma(s2, cps, -c2 * sps);
+        const double sts = S.E[2], cts = S.E[5];
         const double w = fma(cts, d0, -sts * m1), z = fma(sts, d0, cts * m1);
-        const double g = fma(F, w, D * m2);
+        const double g = fma(f1, w, fma(sn, m2, w));
         u0 = fma(W.ct, g, W.st * z);
         u1 = fma(W.ct, z, -W.st * g);
-        u2 = fma(F, m2, -D * w);
+        u2 = fma(f1, m2, fma(-sn, w, m2));
     } else {
         u0 = d0;
         u1 = m1;
@@ -352,6 +361,7 @@ struct Plan {
     double* tab0 = nullptr;
     double2* tab1 = nullptr;
     double2* tab2 = nullptr;
+    double2* lon = nullptr;   // forward: longitude differences [nsrc][n2] (k_lon)
     int* active = nullptr;
     int* iter = nullptr;
     int* counter = nullptr;
@@ -379,6 +389,7 @@ struct SweepArgs {
     Tabs T;
     const double *s, *xi, *eta;
     const Src* src;
+    const double2* lon;     // forward: (cos - 1, sin) of the longitude difference or (x - x_s, 0), [nsrc][n2]
     double* field;          // tau or lambda [nsrc][Nf]
     const double* coef;     // adjoint coefficients [nsrc][4][Sa][6], or [nsrc][N][6] when compact
     const double* rhs;      // adjoint right-hand side / diagonal [nsrc][N]

@@ -114,6 +114,25 @@ __global__ void k_tables(Geo G, double* __restrict__ t0, double2* __restrict__ t
     }
 }
 
+// p + q = *hi + *lo exactly
+__device__ __forceinline__ void two_sum(double p, double q, double* hi, double* lo) {
+#pragma clang fp contract(off)
+    const double s = p + q, t = s - p;
+    *lo = (p - (s - t)) + (q - t);
+    *hi = s;
+}
+
+// a b + c d + e, rounded about once (the products' and sums' errors are carried along)
+__device__ __forceinline__ double dot_2(double a, double b, double c, double d, double e) {
+#pragma clang fp contract(off)
+    const double p = a * b, q = c * d;
+    const double pl = fma(a, b, -p), ql = fma(c, d, -q);
+    double s, sl, r, rl;
+    two_sum(p, e, &s, &sl);
+    two_sum(s, q, &r, &rl);
+    return r + ((sl + rl) + (pl + ql));
+}
+
 __global__ void k_src_setup(Geo G, const double* __restrict__ pos, const double* __restrict__ par,
                             Src* __restrict__ out, int nsrc) {
     const int q = blockIdx.x * blockDim.x + threadIdx.x;
@@ -125,10 +144,15 @@ __global__ void k_src_setup(Geo G, const double* __restrict__ pos, const double*
         S.E[0] = ct * cp; S.E[1] = ct * sp; S.E[2] = st;
         S.E[3] = -st * cp; S.E[4] = -st * sp; S.E[5] = ct;
         S.E[6] = -sp; S.E[7] = cp; S.E[8] = 0.0;
+        S.rh = p0 * ct;
+        // (cp and sp are rounded, and their squares add up to 1 only nearly)
+        S.rhl = fma(S.rh, dot_2(cp, cp, sp, sp, -1.0), fma(p0, ct, -S.rh));
+        S.zl = fma(p0, st, -(p0 * st));
         S.Xs[0] = p0 * S.E[0]; S.Xs[1] = p0 * S.E[1]; S.Xs[2] = p0 * S.E[2];
     } else {
         for (int a = 0; a < 9; ++a) S.E[a] = (a % 4 == 0) ? 1.0 : 0.0;
         S.Xs[0] = p0; S.Xs[1] = p1; S.Xs[2] = p2;
+        S.rh = S.rhl = S.zl = 0.0;
     }
     const double xi0 = par[3 * q + 1], eta0 = par[3 * q + 2];
     const double b = 1.0 - 2.0 * xi0, c = 1.0 + 2.0 * xi0, f = 2.0 * eta0;
@@ -140,6 +164,19 @@ __global__ void k_src_setup(Geo G, const double* __restrict__ pos, const double*
     S.fb[2] = cell_base(G, 2, p2);
     S.pad = 0;
     out[q] = S;
+}
+
+// Longitude difference of every axis-2 node from every source: (cos - 1, sin) of it
+// (Cartesian: (x - x_s, 0)), from the same rounded sines and cosines as elsewhere.
+__global__ void k_lon(Geo G, const double2* __restrict__ t2, const Src* __restrict__ src, double2* __restrict__ out,
+                      long long n) {
+    const long long x = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (x >= n) return;
+    const double2 t = t2[x % G.n[2]];
+    const Src& S = src[x / G.n[2]];
+    const double sp = -S.E[6], cp = S.E[7];
+    out[x] = G.coord == 1 ? make_double2(dot_2(t.x, cp, t.y, sp, -1.0), dot_2(t.y, cp, -t.x, sp, 0.0))
+                          : make_double2(t.x - S.Xs[2], 0.0);
 }
 
 // trilinear cell and weights at a continuous position (clamped to the grid)
@@ -814,13 +851,13 @@ constexpr int kPre = 4;       // forward: steps are long (the full update)
 constexpr int kPreAdj = 6;    // adjoint: short steps, so look further ahead
 
 struct FwdSlot {
-    double sx, ma, mb, mc, c2, s2;  // s, the anisotropy block (1 - 2 xi, 2 eta, 1 + 2 xi), axis-2 table
+    double sx, ma, mb, mc, f1, sn;  // s, the anisotropy block (1 - 2 xi, 2 eta, 1 + 2 xi), longitude difference
 };
 
 // unconditional: k' is clamped into the lane's range in the tile, so the address is always valid
 template <int DIR>
 __device__ __forceinline__ void fwd_fetch(const TileCtx& c, const double* __restrict__ mdl,
-                                          const double2* __restrict__ t2, int t, FwdSlot& r) {
+                                          const double2* __restrict__ lon, int t, FwdSlot& r) {
     // the step clamped to the lane's k' range; |rstep| = n1p < 2^23 and the
     // step is below 64, so the product is a 24-bit one
     const int tc = min(max(t, c.tlo), c.thi);
@@ -831,9 +868,9 @@ __device__ __forceinline__ void fwd_fetch(const TileCtx& c, const double* __rest
     r.ma = m0.y;
     r.mb = m1.x;
     r.mc = m1.y;
-    const double2 tv = t2[(unsigned)(c.tt0 + Dir<DIR>::s2 * tc)];
-    r.c2 = tv.x;
-    r.s2 = tv.y;
+    const double2 tv = lon[(unsigned)(c.tt0 + Dir<DIR>::s2 * tc)];
+    r.f1 = tv.x;
+    r.sn = tv.y;
 }
 
 // One step of the forward walk at step t of the slab.  No step has a branch:
@@ -857,7 +894,7 @@ __device__ __forceinline__ void fwd_step(const Geo& G, const Src& S, const LfCol
     const double m0 = D::s0 > 0 ? up_i : dn_i, p0 = D::s0 > 0 ? dn_i : up_i;
     const double m1 = D::s1 > 0 ? up_j : dn_j, p1 = D::s1 > 0 ? dn_j : up_j;
     const double m2 = D::s2 > 0 ? up_k : dn_k, p2 = D::s2 > 0 ? dn_k : up_k;
-    const double nv = lf_update<COORD>(G, S, W, r.c2, r.s2, r.sx, r.ma, r.mb, r.mc, cur, m0, p0, m1, p1, m2, p2);
+    const double nv = lf_update<COORD>(G, S, W, r.f1, r.sn, r.sx, r.ma, r.mb, r.mc, cur, m0, p0, m1, p1, m2, p2);
     const bool on = step_on(c, t);
     lds[HELD ? (on ? own : 0) + (sg > 0 ? t + 1 : Lp - 2 - t) : (on ? o + sg : 0)] = nv;
     eps += on ? fabs(nv - cur) : 0.0;
@@ -871,7 +908,7 @@ __device__ __forceinline__ void fwd_column(const SweepArgs& a, const Geo& G, int
     using Win = Window<DIR, TKC>;
     constexpr int ng = TKC / kPre, nl = Win::nload;
     const double* __restrict__ mdl = a.model + (long long)D::lay * G.Sa * 4;
-    const double2* __restrict__ t2 = a.T.t2;
+    const double2* __restrict__ lon = a.lon + (long long)src * G.n[2];
     const Src S = a.src[src];
     TileCtx c = col_ctx<DIR>(G, S, TI, TJ);
     const Col cl = make_col(G, a.T, c.i, c.j);
@@ -887,7 +924,7 @@ __device__ __forceinline__ void fwd_column(const SweepArgs& a, const Geo& G, int
     win_load<DIR, TKC>(G, c, fld, lo, hi, c.kq0, pf);
     first = win_first<DIR, TKC>(G, c, fld, lo, hi);
 #pragma unroll
-    for (int u = 0; u < kPre; ++u) fwd_fetch<DIR>(c, mdl, t2, c.t0 + u, ring[u]);
+    for (int u = 0; u < kPre; ++u) fwd_fetch<DIR>(c, mdl, lon, c.t0 + u, ring[u]);
     march_column<DIR, true>(a, G, src, TI, TJ, [&](int TK, const Handover& h) {
         slab_ctx<DIR, true>(G, S, c, TK * TKC, TKC);
         if (c.t1 <= c.t0) {  // a ragged column's slab with no nodes
@@ -910,7 +947,7 @@ __device__ __forceinline__ void fwd_column(const SweepArgs& a, const Geo& G, int
 #pragma unroll
             for (int u = 0; u < kPre; ++u) {
                 fwd_step<COORD, DIR, true>(G, S, W, c, lds, own, Win::Lp, g * kPre + u, ring[u], eps);
-                fwd_fetch<DIR>(c, mdl, t2, g * kPre + u + kPre, ring[u]);
+                fwd_fetch<DIR>(c, mdl, lon, g * kPre + u + kPre, ring[u]);
             }
         };
         static_assert(ng == 4, "groups of a slab");
@@ -1060,7 +1097,7 @@ __device__ __forceinline__ void fwd_line_column(const SweepArgs& a, const Geo& G
     using D = Dir<DIR>;
     constexpr int ng = kLine / kPre;
     const double* __restrict__ mdl = a.model + (long long)D::lay * G.Sa * 4;
-    const double2* __restrict__ t2 = a.T.t2;
+    const double2* __restrict__ lon = a.lon + (long long)src * G.n[2];
     const Src S = a.src[src];
     TileCtx c = col_ctx<DIR>(G, S, TI, TJ);
     const Col cl = make_col(G, a.T, c.i, c.j);
@@ -1077,7 +1114,7 @@ __device__ __forceinline__ void fwd_line_column(const SweepArgs& a, const Geo& G
     line_load<DIR>(G, c, fld, 0, pf);
     const int tf = (delta + 1) & ~(kPre - 1);  // the first group with a node, counted from walk 0
 #pragma unroll
-    for (int u = 0; u < kPre; ++u) fwd_fetch<DIR>(c, mdl, t2, tf + u, ring[u]);
+    for (int u = 0; u < kPre; ++u) fwd_fetch<DIR>(c, mdl, lon, tf + u, ring[u]);
     unsigned long long* word = progress_words(a, src) + TI * G.nt[1] + TJ;
     const unsigned long long* up = nullptr;
     if (threadIdx.x == 0 && TI > 0) up = word - G.nt[1];
@@ -1112,14 +1149,14 @@ __device__ __forceinline__ void fwd_line_column(const SweepArgs& a, const Geo& G
                 const double m0 = D::s0 > 0 ? up_i : dn_i, p0 = D::s0 > 0 ? dn_i : up_i;
                 const double m1 = D::s1 > 0 ? up_j : dn_j, p1 = D::s1 > 0 ? dn_j : up_j;
                 const double m2 = D::s2 > 0 ? upk : dnk, p2 = D::s2 > 0 ? dnk : upk;
-                const double nv = lf_update<COORD>(G, S, W, r.c2, r.s2, r.sx, r.ma, r.mb, r.mc, cur, m0, p0, m1, p1, m2, p2);
+                const double nv = lf_update<COORD>(G, S, W, r.f1, r.sn, r.sx, r.ma, r.mb, r.mc, cur, m0, p0, m1, p1, m2, p2);
                 const bool on = step_on(c, t);
                 lds[on ? at : 0] = nv;  // no branch in a step, as in fwd_step
                 eps += on ? fabs(nv - cur) : 0.0;
                 upk = on ? nv : cur;
                 cur = dnk;
                 at = an;
-                fwd_fetch<DIR>(c, mdl, t2, t + kPre, r);
+                fwd_fetch<DIR>(c, mdl, lon, t + kPre, r);
             }
         };
         static_assert(ng == 4, "groups of a walk");
@@ -1169,9 +1206,9 @@ __global__ void __launch_bounds__(64, TKC == 16 ? 2 : 3) k_fwd_sweep(SweepArgs a
         march(a, G, c0, cn, [&](int src, int TI, int TJ) { fwd_column<COORD, DIR, TKC>(a, G, src, TI, TJ, lds); });
     } else {
         const double* __restrict__ mdl = a.model + (long long)D::lay * G.Sa * 4;
-        const double2* __restrict__ t2 = a.T.t2;
         const int Lp = tile_pitch(G.tk);
         march(a, G, c0, cn, [&](int src, int TI, int TJ) {
+            const double2* __restrict__ lon = a.lon + (long long)src * G.n[2];
             const Src S = a.src[src];
             TileCtx c = col_ctx<DIR>(G, S, TI, TJ);
             const Col cl = make_col(G, a.T, c.i, c.j);
@@ -1184,7 +1221,7 @@ __global__ void __launch_bounds__(64, TKC == 16 ? 2 : 3) k_fwd_sweep(SweepArgs a
                 if (c.t1 <= c.t0) return;  // a ragged column's slab with no nodes
                 FwdSlot ring[kPre];
 #pragma unroll
-                for (int u = 0; u < kPre; ++u) fwd_fetch<DIR>(c, mdl, t2, c.t0 + u, ring[u]);
+                for (int u = 0; u < kPre; ++u) fwd_fetch<DIR>(c, mdl, lon, c.t0 + u, ring[u]);
                 wait_upstream(h.up, h.target, h.lost);
                 stage_tile<DIR>(G, c, fld, -(long long)src * G.N, (long long)(a.nsrc - src) * G.N - 2, lds);
                 __syncthreads();
@@ -1194,7 +1231,7 @@ __global__ void __launch_bounds__(64, TKC == 16 ? 2 : 3) k_fwd_sweep(SweepArgs a
 #pragma unroll
                     for (int u = 0; u < kPre; ++u) {
                         fwd_step<COORD, DIR, false>(G, S, W, c, lds, own, Lp, tb + u, ring[u], eps);
-                        fwd_fetch<DIR>(c, mdl, t2, tb + u + kPre, ring[u]);
+                        fwd_fetch<DIR>(c, mdl, lon, tb + u + kPre, ring[u]);
                     }
                 }
                 __syncthreads();
@@ -2103,6 +2140,7 @@ SweepArgs make_args(const Plan& P, const double* s, const double* xi, const doub
     a.T = P.T;
     a.s = s; a.xi = xi; a.eta = eta;
     a.src = P.src;
+    a.lon = P.lon;
     a.field = field;
     a.coef = P.coef;
     a.rhs = P.rhs;
@@ -2148,6 +2186,8 @@ void launch_source_params(const Geo& G, const double* s, const double* xi, const
 
 void launch_fwd_init(const Plan& P, const SweepArgs& a, const double* tau_init, const double* s, const double* xi,
                      const double* eta, hipStream_t st) {
+    const long long nl = (long long)P.nsrc * P.G.n[2];
+    hipLaunchKernelGGL(k_lon, dim3(blocks_for(nl, 256)), dim3(256), 0, st, P.G, P.tab2, P.src, P.lon, nl);
     hipLaunchKernelGGL(k_model_records, dim3(blocks_for(P.G.N, 256)), dim3(256), 0, st, P.G, s, xi, eta, P.model);
     hipLaunchKernelGGL(k_solve_init, dim3(fill_blocks(P.G.N), P.nsrc), dim3(256), 0, st, a, tau_init, 1.0, 1.0);
 }
