@@ -50,7 +50,8 @@ __device__ __align__(256) unsigned char scratch[kScratchBytes];
 // Default tile depths.  A batch of few tile columns is bound by the chain of
 // tiles from the sweep's first corner to its last, which shorter tiles cut
 // finer; one that fills the chip several times over is bound by what its tiles
-// move, which deeper tiles move less of.  Measured at depths 16 and 28
+// move, which deeper tiles move less of (the adjoint's line is drawn finer, at
+// adjoint_deep).  Measured at depths 16 and 28
 // (forward), 16 and 40 (adjoint), in place, ms:
 //   41^3 x 1 source (25 columns)   forward 8.9 / 15.4       adjoint 10.7 / 14.1
 //   61^3 x 16 (1024)                       28.2 / -                 38.6 / 51.0
@@ -151,11 +152,15 @@ bool lines_of(const tt_grid* g, int nsrc) {
 // leaves the chip partly idle at its first and last columns, where a second
 // group's launch can run; a batch of many columns hardly has such ends, and a
 // batch of few never fills the chip, so that groups only take turns.
-// Forward, 1 and 2 groups (ms): 256 columns (61^3 x 4) 24.3 / 25.9; 512 (61^3 x 8)
-// 24.1 / 25.9; 768 to 845 27.5 / 26.9 (61^3 x 12), 21.6 / 20.3 (33 x 25 x 82 x 64), 83 / 93
-// (101^3 x 5); 1014 (101^3 x 6) 80 / 91, 1024 (61^3 x 16) 29.0 / 29.4; 1152 (33 x 25 x 82
-// x 96) 26.0 / 22.9; 1536 30.3 / 25.1; 2048 (61^3 x 32) 43.7 / 36.1; slabs of 28 on 101^3
-// x 128 354 / 355, whole lines on 61^3 x 256 113.2 / 107.1.
+// Forward, 1, 2 and 3 groups (ms): 576 columns (61^3 x 9) 25.3 / 25.0 / 26.7; 768 (61^3 x 12)
+// 26.6 / 27.1 / 27.8; 780 (33 x 25 x 82 x 65) 22.2 / 20.2 / 21.4; 1024 (61^3 x 16) 28.7 / 28.6 / 30.6;
+// 1100 (81^3 x 11) 40.9 / 36.3 / 37.9; 1536 (61^3 x 24) 33.4 / 29.7 / 30.3; 2028 (101^3 x 12) 106.0 /
+// 97.6 / 100.4; 2040 (33 x 25 x 82 x 170) 35.9 / 30.2 / 28.8; 2048 (61^3 x 32) 44.4 / 36.0 / 37.0;
+// 2112 (61^3 x 33) 42.7 / 39.5 / 36.9; 2500 (41^3 x 100) 21.2 / 16.9 / 16.3; 3008 (61^3 x 47) 48.3 /
+// 47.6 / 40.8; 3042 (101^3 x 18) 122.8 / 119.0 / 115.9.  Eight sources or fewer in two: 83 / 93
+// (101^3 x 5), 77 / 85 (101^3 x 8).  Whole lines: 3200 (61^3 x 50) 45.4 / 47.0 / 43.9; 4096 (61^3 x 64)
+// 45.9 / 49.3 / 50.2; 5120 (61^3 x 80) 52.8 / 51.9 / 58.7; 8192 (61^3 x 128) 66.5 / 61.8 / 64.8; 61^3 x
+// 256 113.2 / 107.1 / -.  Slabs of 28: 101^3 x 20 124.0 / 120.5 / 125.0, x 128 354 / 355 / -.
 // Adjoint, 1, 2, 3 and 4 groups: 408 columns (33 x 25 x 82 x 34) 25.8 / 26.2 / 26.2 / 27.0;
 // 512 (61^3 x 8) 30.0 / 32.5 / - / 35.9; 576 (61^3 x 9) 40.6 / 35.2 / 37.4 / 38.5; 600
 // (41^3 x 24) 15.5 / 15.2 / 15.2 / 15.7; 1024 (61^3 x 16) 43.5 / 38.8 / 42.5 / 44.1; 1472 (61^3 x
@@ -174,11 +179,10 @@ int groups_of(const tt_opts* o, const tt_grid* grid, int nsrc, int which, bool l
     else if (o && o->groups > 0)
         g = o->groups;
     else if (which == 0)
-        g = cols < 1024 || (cols >= kDeepColumns && !lines) ? 1 : 2;
+        g = cols < 768 || (cols >= kDeepColumns && !lines) ? 1 : (cols < 2100 || lines ? 2 : 3);
     else
         g = cols < 512 ? 1 : (!adjoint_deep(grid, nsrc) ? 4 : (cols < 8192 ? 3 : 2));
-    // a group of its own for every eight sources (forward: every full eight) at most
-    if (!(o && o->groups > 0)) g = std::max(1, std::min(g, (which == 0 ? nsrc : nsrc + 7) / 8));
+    if (!(o && o->groups > 0)) g = std::min(g, (nsrc + 7) / 8);  // one for every eight sources at most
     return g > nsrc ? nsrc : g;
 }
 
