@@ -2024,13 +2024,17 @@ __global__ void k_sample(Geo G, Tabs T, const Src* __restrict__ srcs, int nsrc, 
 }
 
 // Kernels of Eqs. (6)-(8), summed over the sources in order.  A thread takes
-// kAccI nodes in a row along axis 0, lanes run along (j, k): of a node's seven tau
+// NI nodes in a row along axis 0, lanes run along (j, k): of a node's seven tau
 // values axis 0's are shared with the next node and axis 2's come from the lanes
 // beside it.  Consecutive workgroups go to different XCDs, so each XCD takes a
 // contiguous run of blocks, planes fastest, whose neighbours are then its own.
-// Bound by its L1 accesses (eight reads a node, in the order of the nodes: 1064 us
-// for 128 sources of 101^3; contiguous runs 866; five reads a node 790).
-constexpr int kAccI = 4;
+// Bound by its L1 accesses where it fills the chip: two nodes a thread, six reads a node,
+// take 718 us for 128 sources of 101^3, one node (eight reads) 792, four (five reads, but
+// half the waves) 807; in the order of the nodes, one a thread, 1055.  A small grid is
+// bound by each thread's walk over the sources, and one node a thread is the shortest
+// (us, one / two / four): 16^3 x 128 99 / 150 / 234, 41^3 x 128 107 / 130 / 198, 55^3 x 128 169 / 199 /
+// 233, 61^3 x 128 212 / 210 / 240, 61^3 x 200 311 / 300 / 351.
+constexpr long long kAccFew = 200000;
 
 __device__ __forceinline__ double lane_below(double v) {  // lane 0: its own value
     const int lo = __double2loint(v), hi = __double2hiint(v);
@@ -2043,15 +2047,15 @@ __device__ __forceinline__ double lane_above(double v) {  // lane 63: its own va
                             __builtin_amdgcn_update_dpp(lo, lo, 0x130, 0xf, 0xf, false));
 }
 
-template <int COORD>
+template <int COORD, int NI>
 __global__ void __launch_bounds__(256) k_kernel_accum(Geo G, Tabs T, const Src* __restrict__ srcs, int nsrc,
                                                       const double* __restrict__ xi, const double* __restrict__ eta,
                                                       const double* __restrict__ tau_all,
                                                       const double* __restrict__ lam_all, double* __restrict__ grad,
                                                       int accumulate) {
-    const int nib = (G.n[0] + kAccI - 1) / kAccI;
+    const int nib = (G.n[0] + NI - 1) / NI;
     const long long blk = (long long)(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-    const int i0 = kAccI * (int)(blk % nib);
+    const int i0 = NI * (int)(blk % nib);
     const long long e = blk / nib * 256 + threadIdx.x, plane = G.si;
     if (blk / nib * 256 >= plane) return;
     const long long jk = e < plane ? e : plane - 1;  // (lanes past the plane keep the last one company)
@@ -2062,15 +2066,15 @@ __global__ void __launch_bounds__(256) k_kernel_accum(Geo G, Tabs T, const Src* 
     // (lanes at the fields' faces read inside them; their sums are dropped)
     const long long jm = j > 0 ? -G.sj : 0, jp = j < G.n[1] - 1 ? G.sj : 0;
     const long long ke = lane == 0 ? (jk > 0 ? -1 : 0) : (jk < plane - 1 ? 1 : 0);
-    double gs[kAccI] = {}, gx[kAccI] = {}, ge[kAccI] = {};
+    double gs[NI] = {}, gx[NI] = {}, ge[NI] = {};
     if (nsrc > 0) {  // (no tables without a source)
-        Col c[kAccI];
-        double ma[kAccI], mb[kAccI], mc[kAccI];
-        long long xo[kAccI + 2];
+        Col c[NI];
+        double ma[NI], mb[NI], mc[NI];
+        long long xo[NI + 2];
 #pragma unroll
-        for (int u = 0; u < kAccI + 2; ++u) xo[u] = min(max(i0 + u - 1, 0), G.n[0] - 1) * G.si + jk;
+        for (int u = 0; u < NI + 2; ++u) xo[u] = min(max(i0 + u - 1, 0), G.n[0] - 1) * G.si + jk;
 #pragma unroll
-        for (int u = 0; u < kAccI; ++u) {
+        for (int u = 0; u < NI; ++u) {
             c[u] = make_col(G, T, min(i0 + u, G.n[0] - 1), j);
             ma[u] = 1.0 - 2.0 * xi[xo[u + 1]];
             mb[u] = 2.0 * eta[xo[u + 1]];
@@ -2081,22 +2085,22 @@ __global__ void __launch_bounds__(256) k_kernel_accum(Geo G, Tabs T, const Src* 
             const Src S = srcs[n];
             const double* tau = tau_all + (long long)n * G.N;
             const double* lam = lam_all + (long long)n * G.N;
-            double v[kAccI + 2], l[kAccI], vm[kAccI], vp[kAccI], vk[kAccI];
+            double v[NI + 2], l[NI], vm[NI], vp[NI], vk[NI];
 #pragma unroll
-            for (int u = 0; u < kAccI + 2; ++u) v[u] = tau[xo[u]];
+            for (int u = 0; u < NI + 2; ++u) v[u] = tau[xo[u]];
 #pragma unroll
-            for (int u = 0; u < kAccI; ++u) {
+            for (int u = 0; u < NI; ++u) {
                 vm[u] = tau[xo[u + 1] + jm];
                 vp[u] = tau[xo[u + 1] + jp];
                 l[u] = lam[xo[u + 1]];
             }
 #pragma unroll
-            for (int u = 0; u < kAccI; ++u) vk[u] = 0.0;
+            for (int u = 0; u < NI; ++u) vk[u] = 0.0;
             if (end)
 #pragma unroll
-                for (int u = 0; u < kAccI; ++u) vk[u] = tau[xo[u + 1] + ke];
+                for (int u = 0; u < NI; ++u) vk[u] = tau[xo[u + 1] + ke];
 #pragma unroll
-            for (int u = 0; u < kAccI; ++u) {
+            for (int u = 0; u < NI; ++u) {
                 const double tx = v[u + 1];
                 const double km = lane_below(tx), kp = lane_above(tx);
                 double T0, t[3];
@@ -2117,7 +2121,7 @@ __global__ void __launch_bounds__(256) k_kernel_accum(Geo G, Tabs T, const Src* 
     }
     if (e >= plane) return;
 #pragma unroll
-    for (int u = 0; u < kAccI; ++u) {
+    for (int u = 0; u < NI; ++u) {
         const int i = i0 + u;
         if (i >= G.n[0]) return;
         const bool on = in && i > 0 && i < G.n[0] - 1;
@@ -2369,16 +2373,25 @@ void launch_sample(const Plan& P, const double* tau, int nrec, const double* rec
                            nrec, rec, out);
 }
 
-void launch_kernel_accum(const Plan& P, const double* xi, const double* eta, const double* tau, const double* lam,
-                         double* grad, int accumulate, hipStream_t st) {
-    const long long blocks = (long long)blocks_for(P.G.si, 256) * ((P.G.n[0] + kAccI - 1) / kAccI);
+template <int NI>
+static void accum(const Plan& P, const double* xi, const double* eta, const double* tau, const double* lam, double* grad,
+                  int accumulate, hipStream_t st) {
+    const long long blocks = (long long)blocks_for(P.G.si, 256) * ((P.G.n[0] + NI - 1) / NI);
     const dim3 grid((unsigned)((blocks + 7) / 8 * 8));
     if (P.G.coord == 1)
-        hipLaunchKernelGGL(k_kernel_accum<1>, grid, dim3(256), 0, st, P.G, P.T, P.src,
-                           P.nsrc, xi, eta, tau, lam, grad, accumulate);
+        hipLaunchKernelGGL((k_kernel_accum<1, NI>), grid, dim3(256), 0, st, P.G, P.T, P.src, P.nsrc, xi, eta, tau, lam,
+                           grad, accumulate);
     else
-        hipLaunchKernelGGL(k_kernel_accum<0>, grid, dim3(256), 0, st, P.G, P.T, P.src,
-                           P.nsrc, xi, eta, tau, lam, grad, accumulate);
+        hipLaunchKernelGGL((k_kernel_accum<0, NI>), grid, dim3(256), 0, st, P.G, P.T, P.src, P.nsrc, xi, eta, tau, lam,
+                           grad, accumulate);
+}
+
+void launch_kernel_accum(const Plan& P, const double* xi, const double* eta, const double* tau, const double* lam,
+                         double* grad, int accumulate, hipStream_t st) {
+    if (P.G.N < kAccFew)
+        accum<1>(P, xi, eta, tau, lam, grad, accumulate, st);
+    else
+        accum<2>(P, xi, eta, tau, lam, grad, accumulate, st);
 }
 
 }  // namespace tt
