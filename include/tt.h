@@ -206,7 +206,8 @@ int tt_forward(const tt_grid* grid, const double* s, const double* xi, const dou
  * the process ends.  The call allocates nothing (no device, pinned or graph
  * memory, no streams or events): one source group on `stream`, asynchronous.
  * Limits and errors: TT_EINVAL if the workspace this grid, batch and tile
- * depth need (tt_workspace_size with groups = 1) exceeds the array, or if
+ * depth need (tt_workspace_size with groups = 1, less 16 n[2] + 32 bytes a source
+ * for tables that a batch solved in parts shares) exceeds the array, or if
  * opts asks for TT_FLAG_POLL, TT_FLAG_TIME_SWEEPS or TT_FLAG_GRAPH (each
  * needs an allocation); otherwise as tt_forward.  Every call on one device
  * shares that device's array, whose contents are whatever the last call left

@@ -39,7 +39,8 @@ using tt::fail;
 // stand-in for the symbol): its device address comes from
 // hipGetSymbolAddress, once per device (scratch_ptr below).
 constexpr size_t kScratchBytes = (size_t)64 << 20;
-__device__ __align__(256) unsigned char scratch[kScratchBytes];
+constexpr size_t kScratchRoom = (size_t)192 << 10;  // for one source's longitude table (8192 nodes) beside that
+__device__ __align__(256) unsigned char scratch[kScratchBytes + kScratchRoom];
 
 #define TT_HIP(call)                                                                          \
     do {                                                                                      \
@@ -853,16 +854,30 @@ int tt_forward_noalloc(const tt_grid* grid, const double* s, const double* xi, c
     if (opts->flags & (TT_FLAG_POLL | TT_FLAG_TIME_SWEEPS | TT_FLAG_GRAPH))
         return fail(TT_EINVAL, "tt_forward_noalloc: TT_FLAG_POLL, TT_FLAG_TIME_SWEEPS and TT_FLAG_GRAPH need "
                                "allocations (pinned memory, events, graphs) and are not available here");
-    const size_t need = grouped_total(make_geo(grid, tile_k_of(opts, 0, grid, nsrc)), nsrc, 1, 0);
+    // The limit leaves out the sources' longitude tables and kept roundings: where the whole
+    // batch does not fit with them, it is solved in parts, one after the other on the stream.
+    const tt::Geo geo = make_geo(grid, tile_k_of(opts, 0, grid, nsrc));
+    const size_t extra = (sizeof(double2) * (size_t)grid->n[2] + 32) * (size_t)nsrc;
+    const size_t need = grouped_total(geo, nsrc, 1, 0) - extra;
     if (need > kScratchBytes)
         return fail(TT_EINVAL, "tt_forward_noalloc: this grid and batch need %zu bytes of workspace, more than the "
                                "%zu-byte scratch; use tt_forward with a caller workspace", need, kScratchBytes);
+    constexpr size_t room = kScratchBytes + kScratchRoom;
+    int part = nsrc;
+    while (part > 1 && grouped_total(geo, part, 1, 0) > room) part = (part + 1) / 2;
     void* ws = nullptr;
     if ((rc = scratch_ptr(&ws))) return rc;
-    tt_opts one = *opts;
-    one.groups = 1;
-    return forward_run(forward_form(grid, nsrc, &one, kScratchBytes), s, xi, eta, nsrc, src_pos, src_par, tau_init, opts,
-                       tau, status, ws, kScratchBytes, (hipStream_t)stream);
+    for (int q = 0; q < nsrc && !rc; q += part) {
+        const int n = std::min(part, nsrc - q);
+        tt_opts one = *opts;
+        one.groups = 1;
+        if (one.budgets) one.budgets += q;
+        if (one.eps_hist) one.eps_hist += (long long)q * one.max_iter;
+        rc = forward_run(forward_form(grid, n, &one, room), s, xi, eta, n, src_pos + 3LL * q, src_par + 3LL * q,
+                         tau_init ? tau_init + (long long)q * geo.N : nullptr, &one, tau + (long long)q * geo.N, status + q,
+                         ws, room, (hipStream_t)stream);
+    }
+    return rc;
 }
 
 size_t tt_forward_noalloc_limit(void) { return kScratchBytes; }
